@@ -105,7 +105,8 @@ typedef struct {
     int32_t depth;
     int32_t max_leaf;
     double sah_cost;      /* C_trav = C_isect = 1, normalised by the root area */
-    int64_t device_bytes; /* nodes (6 link sets x 16 B) + triangle records (48 B) */
+    int64_t device_bytes; /* nodes (6 link sets x 16 B) + triangle records (48 B); the four-child nodes
+                             of the default walk come on top (about a sixth of the nodes' bytes) */
     double build_ms;      /* host build + threading time */
     float grid_lo[3];     /* node boxes: coordinate = grid_lo + q * grid_step */
     float grid_step[3];
@@ -174,7 +175,11 @@ PM_API int pm_trace_rays(const pm_bvh *bvh, const float *rays, int64_t n, int32_
  * the per-ray walk); or the postponed walk over a slice of consecutive rays
  * per wavefront (the order of reorder, else the input order), a lane taking
  * the slice's next ray when its own has ended.  All return the same
- * result. */
+ * result.
+ * AUTO, POSTPONED and PACKET walk four-child nodes merged from the binary tree
+ * (kept on the device beside it, 64 bytes each) one ray per lane, unless a
+ * link set is forced or the counters are asked for, which name the binary
+ * tree's walk, or the tree is too deep for them. */
 enum {
     PM_TRACE_AUTO = 0,
     PM_TRACE_PER_RAY = 1,

@@ -493,6 +493,7 @@ int build_bvh_gpu(const float *verts_h, const uint32_t *mats_h, int64_t n_tri, i
     b->sah_cost = st.sah;
     b->pos_of.assign((size_t)n, 0);
     for (int k = 0; k < n; ++k) b->pos_of[order_h[(size_t)k]] = k;
+    if (int rc = build_wide(b, s)) return rc;
     b->build_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     return PM_OK;
 }

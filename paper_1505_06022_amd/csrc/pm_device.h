@@ -238,9 +238,11 @@ __device__ __forceinline__ int link_set(V3 d) {
 
 struct Bvh {
     const uint4 *nodes;   // [6][n_nodes] 16-byte nodes, then a pad node
+    const uint4 *wide;    // [n_wide][4] four-child nodes (see wide_walk), or NULL
     const float4 *tris;   // [n_tri][3] float4
     uint32_t n_nodes;
     float qlo[3], qstep[3];  // node box grid: coordinate = qlo + q * qstep
+    float inv_max[3];        // largest reciprocal direction used in the slab test (2^100 / qstep)
 };
 
 struct TraceStats {
@@ -263,7 +265,7 @@ struct WalkerT {
     V3 o, d;
     Shear sh;                      // the triangle test's shear
     float sx, sy, sz, bx, by, bz;  // slab planes: t = q * s + b per axis
-    uint32_t rx, ry, rz;           // 16 where the axis is walked backwards (near plane = hi), else 0
+    uint32_t rx, ry, rz;           // byte selectors of each axis's entry plane (see plane)
     float tmin, tbest;
     int32_t best, exclude;
     uint32_t best_k;
@@ -276,25 +278,47 @@ struct WalkerT {
         o = o_;
         d = d_;
         sh = ray_shear(d_);
-        // reciprocal direction; zero components replaced by a tiny signed value
+        // reciprocal direction; zero components replaced by a tiny signed
+        // value, and the reciprocal kept small enough for 2^23 s to stay finite
+        // (an axis so clamped moves less than a grid step, half the padding,
+        // over any t below 2^100)
         float dx = fabsf(d.x) > 1e-30f ? d.x : copysignf(1e-30f, d.x);
         float dy = fabsf(d.y) > 1e-30f ? d.y : copysignf(1e-30f, d.y);
         float dz = fabsf(d.z) > 1e-30f ? d.z : copysignf(1e-30f, d.z);
-        float ix = 1.0f / dx, iy = 1.0f / dy, iz = 1.0f / dz;
+        const float ix = clamp_inverse(1.0f / dx, bvh.inv_max[0]), iy = clamp_inverse(1.0f / dy, bvh.inv_max[1]),
+                    iz = clamp_inverse(1.0f / dz, bvh.inv_max[2]);
         sx = bvh.qstep[0] * ix;
         sy = bvh.qstep[1] * iy;
         sz = bvh.qstep[2] * iz;
-        bx = (bvh.qlo[0] - o.x) * ix;
-        by = (bvh.qlo[1] - o.y) * iy;
-        bz = (bvh.qlo[2] - o.z) * iz;
-        rx = sx < 0.0f ? 16u : 0u;
-        ry = sy < 0.0f ? 16u : 0u;
-        rz = sz < 0.0f ? 16u : 0u;
+        // the planes come as 2^23 + q (see plane)
+        bx = fmaf(-0x1p23f, sx, (bvh.qlo[0] - o.x) * ix);
+        by = fmaf(-0x1p23f, sy, (bvh.qlo[1] - o.y) * iy);
+        bz = fmaf(-0x1p23f, sz, (bvh.qlo[2] - o.z) * iz);
+        select_planes();
         tmin = tmin_;
         tbest = tmax_;
         best = -1;
         best_k = 0;
         exclude = exclude_;
+    }
+
+    __device__ __forceinline__ static float clamp_inverse(float i, float most) { return fminf(fmaxf(i, -most), most); }
+
+    // A 16-bit plane coordinate q as the float 2^23 + q, taken from either
+    // half of an axis's word by one byte permute: the entry plane is the low
+    // half, or the high one where the ray runs towards -axis, so entry and
+    // exit distances need no min/max per axis.  (Rotating the word and
+    // converting both halves took three instructions a plane pair instead of
+    // two; the wide walk, 9 of 10 of its time in vector instructions, went
+    // from 0.829 to 0.811 ms on the soup's 2^21 incoherent rays.)
+    static constexpr uint32_t kLowHalf = 0x07060100u, kHighHalf = 0x07060302u;
+    __device__ __forceinline__ void select_planes() {
+        rx = sx < 0.0f ? kHighHalf : kLowHalf;
+        ry = sy < 0.0f ? kHighHalf : kLowHalf;
+        rz = sz < 0.0f ? kHighHalf : kLowHalf;
+    }
+    __device__ __forceinline__ static float plane(uint32_t word, uint32_t select) {
+        return __uint_as_float(__builtin_amdgcn_perm(0x4b000000u, word, select));
     }
 
     __device__ __forceinline__ bool done() const { return i >= n; }
@@ -317,29 +341,36 @@ struct WalkerT {
     }
 
     // Slab test of a quantised node box against [tmin, tbest].  Each word
-    // holds one axis as lo | hi << 16; rotating it by 16 where the ray runs
-    // towards -axis puts that axis's entry plane in the low half, so the
-    // entry and exit distances need no min/max per axis (the values equal
-    // min/max of the two plane distances).
+    // holds one axis as lo | hi << 16; plane() takes the entry and the exit
+    // plane from the halves that the ray's direction names.
     //
-    // Conservative: a plane distance fma(q, s, b), with s and b rounded once
-    // each, is within 4u |t| + 2u ext / |d_a| of the exact one (u = 2^-24,
-    // ext the scene extent, for any ray origin).  An accepted triangle hit at
+    // Conservative: a plane distance fma(2^23 + q, s, b) is within 5u |t| +
+    // 2u ext / |d_a| + s / 2 of the exact one (u = 2^-24, ext the scene
+    // extent, for any ray origin): s is rounded once, and b = (lo - o) / d -
+    // 2^23 s, with the same rounded s, once at the size of 2^23 s (the s / 2,
+    // half a grid step, 128u ext / |d_a|) and once at that of (lo - o) / d.
+    // An accepted triangle hit at
     // t puts o + t d within 22u (|t d_a| + L) of a point of the triangle along
     // each axis (see wt_hit), so inside the triangle's box grown by that
-    // much.  The absolute parts (2u ext, 22u L) are covered many times over by
-    // the padding of every box (at least 2^-15 ext), and the relative parts,
-    // at most 52u |t| in all, by the slack kBoxSlack = 256u on the exit
+    // much.  The absolute parts (2u ext, 128u ext, 22u L: at most 169u ext in
+    // all) are covered three times over by
+    // the padding of every box (at least 2^-15 ext = 512u ext), and the relative parts,
+    // at most 54u |t| in all, by the slack kBoxSlack = 256u on the exit
     // distance: every box that holds a triangle with an accepted hit at a t
     // in (tmin, tbest] passes, so the walk finds the brute-force closest hit.
     static constexpr float kBoxSlack = 0x1p-16f;
     __device__ __forceinline__ bool box_hit(const uint4 &q) const {
-        const uint32_t ax = __builtin_rotateright32(q.x, rx), ay = __builtin_rotateright32(q.y, ry),
-                       az = __builtin_rotateright32(q.z, rz);
-        const float nx = fmaf((float)(ax & 0xffffu), sx, bx), fx = fmaf((float)(ax >> 16), sx, bx);
-        const float ny = fmaf((float)(ay & 0xffffu), sy, by), fy = fmaf((float)(ay >> 16), sy, by);
-        const float nz = fmaf((float)(az & 0xffffu), sz, bz), fz = fmaf((float)(az >> 16), sz, bz);
-        const float tn = fmaxf(fmaxf(nx, ny), fmaxf(nz, tmin));
+        float tn;
+        return box_near(q, tn);
+    }
+
+    // The same test, with the entry distance in tn.
+    __device__ __forceinline__ bool box_near(const uint4 &q, float &tn) const {
+        constexpr uint32_t kOther = kLowHalf ^ kHighHalf;
+        const float nx = fmaf(plane(q.x, rx), sx, bx), fx = fmaf(plane(q.x, rx ^ kOther), sx, bx);
+        const float ny = fmaf(plane(q.y, ry), sy, by), fy = fmaf(plane(q.y, ry ^ kOther), sy, by);
+        const float nz = fmaf(plane(q.z, rz), sz, bz), fz = fmaf(plane(q.z, rz ^ kOther), sz, bz);
+        tn = fmaxf(fmaxf(nx, ny), fmaxf(nz, tmin));
         const float tf = fminf(fminf(fx, fy), fminf(fz, tbest));
         return tn <= fmaf(fabsf(tf), kBoxSlack, tf);
     }
@@ -377,6 +408,17 @@ struct WalkerT {
             best = tr.id;
             best_k = rec;
         }
+    }
+
+    // A ray of the wide walk whose stack ran out: the stackless walk from the
+    // root, keeping the closest hit found so far (testing a triangle again
+    // changes nothing).
+    __device__ __forceinline__ void finish_binary(const Bvh &bvh) {
+        nodes = bvh.nodes + (size_t)link_set(d) * bvh.n_nodes;
+        n = bvh.n_nodes;
+        i = 0;
+        TraceStats st{0u, 0u};
+        while (!done()) step<false>(bvh.tris, st);
     }
 
     // Up to two node visits per memory round trip: nodes i and i + 1 are
@@ -450,6 +492,307 @@ struct WalkerT {
     __device__ __forceinline__ float t_hit() const { return best >= 0 ? tbest : __builtin_inff(); }
 };
 using Walker = WalkerT<false>;
+
+// ---------------------------------------------------------------------------
+// Wide walk: the closest hit through nodes of four children (64 bytes: four
+// records in the layout of the binary node, whose link word names an inner
+// child's wide node or a leaf's triangles).  The nodes are the binary tree of
+// link set 0 with levels merged (build_wide), so the boxes and the box test,
+// and with them the proof that no accepted hit is culled, are those of the
+// binary walk; children are taken by entry distance and the rest wait on a
+// stack in LDS.  The closest hit under the lower-index tie rule does not
+// depend on the order, so the result is that of the stackless walk.
+//
+// The binary walks are bound by their chain of dependent node reads (every
+// read names the next): an incoherent ray of the 2^20-triangle soup makes 111.
+// Here it makes 24, to one array of 23 MB instead of six of 147 MB together.
+// 2^21 such rays, bucketing included, went from 1.83 to 0.82 ms, the camera's
+// 2^21 in 8x8 tiles from 0.34 (packets) to 0.27 ms; the vector units, busy 98%
+// of the time with 36% of their lanes, now bind (64 box tests of a wave take
+// as many instructions as before; 8 children a node would test half as many
+// boxes again).
+//
+// Two shapes of the same walk:
+//  * one ray per lane (four boxes per lane and step), leaf tests held until at
+//    most `late` lanes still look for a leaf;
+//  * four lanes per ray (quads), each lane testing one child box or one
+//    triangle.  A wave with at most kQuadRays unfinished rays moves them to
+//    quads: a step then costs half the instructions of the lane form, a leaf's
+//    tests a quarter, so the last rays of a wave, whose latency nothing hides,
+//    end sooner (without quads the 2^21 rays take 1.08 ms, with them for the
+//    last 8 rays of a wave 0.90).
+// ---------------------------------------------------------------------------
+constexpr uint32_t kWideNone = 0x7fffffffu;  // no node: the walk has ended
+// Stack entries per ray: 21 in use at most (a visit may write three more); the
+// soups and the 250k-triangle scene need up to 18.  A ray that needs more
+// takes the binary walk (with 16 entries the 2^18-triangle soup's 1% of such
+// rays made its walk 30% slower; 32 leave fewer waves resident, 9% slower).
+constexpr int kWideStack = 24;
+constexpr uint32_t kQuadRays = 16;
+// Kernels with the wide walk ask for 6 wavefronts per SIMD (at most 80
+// registers): its stacks leave room for 26 per compute unit.
+#define PM_WIDE_WAVES __attribute__((amdgpu_waves_per_eu(6)))
+
+__device__ __forceinline__ uint32_t lane_index() {
+    return __builtin_amdgcn_mbcnt_hi(0xffffffffu, __builtin_amdgcn_mbcnt_lo(0xffffffffu, 0u));
+}
+
+// The value of the lane whose index in the quad differs by kXor (1, 2 or 3).
+template <int kXor>
+__device__ __forceinline__ int quad_xor(int v) {
+    constexpr int kCtrl = kXor == 1 ? 0xB1 : (kXor == 2 ? 0x4E : 0x1B);
+    return __builtin_amdgcn_mov_dpp(v, kCtrl, 0xf, 0xf, true);
+}
+__device__ __forceinline__ float quad_min(float v) {
+    v = fminf(v, __int_as_float(quad_xor<1>(__float_as_int(v))));
+    return fminf(v, __int_as_float(quad_xor<2>(__float_as_int(v))));
+}
+__device__ __forceinline__ uint32_t quad_min(uint32_t v) {
+    v = min(v, (uint32_t)quad_xor<1>((int)v));
+    return min(v, (uint32_t)quad_xor<2>((int)v));
+}
+__device__ __forceinline__ float pull(uint32_t lane, float v) {
+    return __int_as_float(__builtin_amdgcn_ds_bpermute((int)(lane << 2), __float_as_int(v)));
+}
+__device__ __forceinline__ uint32_t pull(uint32_t lane, uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(lane << 2), (int)v);
+}
+
+// Orders (ka, ra), (kb, rb) by key.
+__device__ __forceinline__ void sort_pair(int &ka, uint32_t &ra, int &kb, uint32_t &rb) {
+    const bool s = kb < ka;
+    const int k0 = min(ka, kb), k1 = max(ka, kb);
+    const uint32_t r0 = s ? rb : ra, r1 = s ? ra : rb;
+    ka = k0;
+    kb = k1;
+    ra = r0;
+    rb = r1;
+}
+
+// One visit of wide node cur by one lane: the nearest child hit becomes cur,
+// the others go on the stack, farthest first; with no hit the top of the
+// stack does.  Entry e of a ray's stack is col[64 e]; entry 0 is kWideNone.
+template <class W>
+__device__ __forceinline__ void wide_step(W &w, const uint4 *__restrict__ wide, uint32_t *col, uint32_t &cur,
+                                          uint32_t &sp, bool &overflow) {
+    const uint4 *p = wide + 4 * (size_t)cur;
+    const uint4 q0 = p[0], q1 = p[1], q2 = p[2], q3 = p[3];
+    const uint32_t top = col[(sp - 1u) * 64u];
+    float t0, t1, t2, t3;
+    const bool h0 = w.box_near(q0, t0), h1 = w.box_near(q1, t1), h2 = w.box_near(q2, t2), h3 = w.box_near(q3, t3);
+    uint32_t r0 = h0 ? q0.w : kWideNone, r1 = h1 ? q1.w : kWideNone, r2 = h2 ? q2.w : kWideNone,
+             r3 = h3 ? q3.w : kWideNone;
+    // distances order as their bits (negative ones, possible with tmin < 0, among themselves in reverse, which only
+    // costs time); misses are above every distance, so the hits come first
+    int k0 = h0 ? __float_as_int(t0) : 0x7fffffff, k1 = h1 ? __float_as_int(t1) : 0x7fffffff,
+        k2 = h2 ? __float_as_int(t2) : 0x7fffffff, k3 = h3 ? __float_as_int(t3) : 0x7fffffff;
+    sort_pair(k0, r0, k1, r1);
+    sort_pair(k2, r2, k3, r3);
+    sort_pair(k0, r0, k2, r2);
+    sort_pair(k1, r1, k3, r3);
+    sort_pair(k1, r1, k2, r2);
+    col[sp * 64u] = r3;
+    sp += r3 != kWideNone ? 1u : 0u;
+    col[sp * 64u] = r2;
+    sp += r2 != kWideNone ? 1u : 0u;
+    col[sp * 64u] = r1;
+    sp += r1 != kWideNone ? 1u : 0u;
+    const bool none = r0 == kWideNone;  // then nothing was pushed
+    cur = none ? top : r0;
+    sp -= none ? 1u : 0u;
+    if (sp > (uint32_t)kWideStack - 3u) {  // a visit writes entries sp .. sp + 2
+        overflow = true;
+        cur = kWideNone;
+    }
+}
+
+// The last rays of a wave (at most kQuadRays lanes with cur != kWideNone),
+// four lanes each.  Called by all lanes of the wave; each ray's result returns
+// to the lane it came from.  stk is the wave's stack; a ray keeps its lane's
+// column.  All four lanes of a quad hold the same ray and the same cur and sp.
+template <class W>
+__device__ __forceinline__ void wide_quads(W &w, const uint4 *__restrict__ wide, const float4 *__restrict__ tris,
+                                           uint32_t *stk, uint32_t &cur_io, uint32_t sp_io, bool &overflow_io) {
+    const uint32_t lane = lane_index(), c = lane & 3u;
+    const uint64_t busy0 = __ballot(cur_io != kWideNone);
+    const uint32_t n_rays = (uint32_t)__popcll(busy0);
+    const uint32_t rank0 = __builtin_amdgcn_mbcnt_hi((uint32_t)(busy0 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)busy0, 0u));
+    const bool mine = cur_io != kWideNone;
+    // quad g takes the g-th unfinished ray: its lane tells the quad's first lane
+    // its own index (finished lanes address lane 3 of quad 15, which no ray uses as first lane)
+    uint32_t owner = (uint32_t)__builtin_amdgcn_ds_permute((int)((mine ? 4u * rank0 : 63u) << 2), (int)lane);
+    owner = (uint32_t)__builtin_amdgcn_mov_dpp((int)owner, 0x00, 0xf, 0xf, true);
+    const bool has = (lane >> 2) < n_rays;
+    owner = has ? owner : 0u;
+    W x;
+    x.o = v3(pull(owner, w.o.x), pull(owner, w.o.y), pull(owner, w.o.z));
+    x.sh.sx = pull(owner, w.sh.sx);
+    x.sh.sy = pull(owner, w.sh.sy);
+    x.sh.sz = pull(owner, w.sh.sz);
+    x.sh.kz = pull(owner, w.sh.kz);
+    x.sx = pull(owner, w.sx);
+    x.sy = pull(owner, w.sy);
+    x.sz = pull(owner, w.sz);
+    x.bx = pull(owner, w.bx);
+    x.by = pull(owner, w.by);
+    x.bz = pull(owner, w.bz);
+    x.select_planes();
+    x.tmin = pull(owner, w.tmin);
+    x.tbest = pull(owner, w.tbest);
+    x.best = (int32_t)pull(owner, (uint32_t)w.best);
+    x.best_k = pull(owner, w.best_k);
+    x.exclude = (int32_t)pull(owner, (uint32_t)w.exclude);
+    uint32_t cur = pull(owner, cur_io), sp = pull(owner, sp_io);
+    cur = has ? cur : kWideNone;
+    uint32_t *col = stk + owner;
+    bool overflow = false;
+    for (;;) {
+        const uint64_t busy = __ballot(cur != kWideNone);
+        if (busy == 0ull) break;
+        if (cur < kWideNone) {
+            const uint4 q = wide[4 * (size_t)cur + c];
+            const uint32_t top = col[(sp - 1u) * 64u];
+            float tn;
+            const bool h = x.box_near(q, tn);
+            // unique keys: the entry distance's bits with the lane in the last two; a miss is above every distance
+            const int key = h ? ((__float_as_int(tn) & ~3) | (int)c) : (int)(0x7ffffffcu | c);
+            const uint32_t rank = (quad_xor<1>(key) < key ? 1u : 0u) + (quad_xor<2>(key) < key ? 1u : 0u) +
+                                  (quad_xor<3>(key) < key ? 1u : 0u);
+            const uint32_t nh = (uint32_t)__popc((uint32_t)(__ballot(h) >> (lane & 60u)) & 15u);
+            if (h && rank != 0u) col[(sp + nh - 1u - rank) * 64u] = q.w;
+            uint32_t nearest = (h && rank == 0u) ? q.w : 0u;  // no child's word is 0 (node 0 is the root)
+            nearest |= (uint32_t)quad_xor<1>((int)nearest);
+            nearest |= (uint32_t)quad_xor<2>((int)nearest);
+            cur = nh != 0u ? nearest : top;
+            sp = sp + nh - 1u;
+            if (sp > (uint32_t)kWideStack - 3u) {
+                overflow = true;
+                cur = kWideNone;
+            }
+            // the quad's lanes read each other's entries
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+        const uint64_t inner = __ballot(cur < kWideNone);
+        if (2u * (uint32_t)__popcll(inner) > (uint32_t)__popcll(busy)) continue;
+        if ((cur >> 31) != 0u) {
+            const uint32_t first = (cur >> 3) & 0x0fffffffu, cnt = cur & 7u;
+            float bt = __builtin_inff();
+            uint32_t bid = 0xffffffffu, bk = 0xffffffffu;
+            for (uint32_t k = c; k < cnt; k += 4u) {
+                const Tri tr = load_tri(tris, first + k);
+                float t;
+                if (wt_hit(x.o, x.sh, tr, t) && tr.id != x.exclude && accept_hit(t, tr.id, x.tmin, x.tbest, x.best) &&
+                    (t < bt || (t == bt && (uint32_t)tr.id < bid))) {
+                    bt = t;
+                    bid = (uint32_t)tr.id;
+                    bk = first + k;
+                }
+            }
+            const float m = quad_min(bt);
+            const uint32_t id = quad_min(bt == m ? bid : 0xffffffffu);
+            const uint32_t rec = quad_min(bt == m && bid == id ? bk : 0xffffffffu);
+            if (id != 0xffffffffu) {
+                x.tbest = m;
+                x.best = (int32_t)id;
+                x.best_k = rec;
+            }
+            cur = col[(sp - 1u) * 64u];
+            sp -= 1u;
+        }
+    }
+    const uint32_t from = 4u * rank0 & 63u;  // first lane of this lane's quad (unfinished lanes only)
+    const float tb = pull(from, x.tbest);
+    const uint32_t bi = pull(from, (uint32_t)x.best), bk = pull(from, x.best_k), ov = pull(from, overflow ? 1u : 0u);
+    if (mine) {
+        w.tbest = tb;
+        w.best = (int32_t)bi;
+        w.best_k = bk;
+        overflow_io = overflow_io || ov != 0u;
+        cur_io = kWideNone;
+    }
+}
+
+// Node visits between two votes of the wave in the lane form (1 costs 8% on
+// bucketed incoherent rays, 4 gains 1% there and loses 4% on camera rays).
+constexpr int kWideSteps = 2;
+
+// One lane's walk between two rounds: the node or leaf it goes on with, its
+// stack, and a leaf set aside (0: none).
+struct WideState {
+    uint32_t cur = kWideNone, sp = 1u, held = 0u;
+    bool overflow = false;
+
+    __device__ __forceinline__ void start(uint32_t *col) {
+        col[0] = kWideNone;
+        cur = 0u;
+        sp = 1u;
+        held = 0u;
+        overflow = false;
+    }
+    __device__ __forceinline__ bool busy() const { return cur != kWideNone || held != 0u; }
+};
+
+// One round of the lane form, called by all lanes of a wave of which some are
+// busy: either kWideSteps node visits by the lanes at inner nodes, or, once
+// at most `late` lanes are and some lane holds a leaf, the held leaves' tests.
+// A lane that reaches a leaf sets it aside and goes on until it meets a second
+// one (most leaves hold no hit, so the visits are rarely in vain).
+template <class W>
+__device__ __forceinline__ void wide_round(W &w, const uint4 *__restrict__ wide, const float4 *__restrict__ tris,
+                                           uint32_t *col, WideState &s, uint32_t late) {
+    const uint64_t inner = __ballot(s.cur < kWideNone);
+    if (inner != 0ull && ((uint32_t)__popcll(inner) > late || __ballot(s.held != 0u) == 0ull)) {
+#pragma unroll
+        for (int u = 0; u < kWideSteps; ++u)
+            if (s.cur < kWideNone) wide_step(w, wide, col, s.cur, s.sp, s.overflow);
+    } else {
+        TraceStats st{0u, 0u};
+        if (s.held != 0u) w.template leaf_tris<false>(tris, s.held, st);
+        s.held = 0u;
+    }
+    if ((s.cur >> 31) != 0u && s.held == 0u) {
+        s.held = s.cur;
+        s.cur = col[(s.sp - 1u) * 64u];
+        s.sp -= 1u;
+    }
+}
+
+// The last rays of a wave: on quads (at most kQuadRays lanes are busy).
+template <class W>
+__device__ __forceinline__ void wide_drain(W &w, const uint4 *__restrict__ wide, const float4 *__restrict__ tris,
+                                           uint32_t *stk, WideState &s) {
+    if (s.held != 0u) {  // the leaf set aside comes first
+        if (s.cur != kWideNone) {
+            stk[lane_index() + s.sp * 64u] = s.cur;
+            s.sp += 1u;
+        } else {
+            s.sp = 1u;  // entry 0, taken when the walk ended, is still there
+        }
+        s.cur = s.held;
+        s.held = 0u;
+    }
+    // the quads read the columns their lanes wrote
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    wide_quads(w, wide, tris, stk, s.cur, s.sp, s.overflow);
+}
+
+// The whole walk of one ray per lane, called by all lanes of a wave (active:
+// this lane has a ray, initialised in w).  stk: the wave's stack in LDS, 64
+// kWideStack words.  Returns true when this lane's stack ran out: the caller
+// then finishes the ray with the binary walk from the root, which keeps the
+// hits found so far.
+template <class W>
+__device__ __forceinline__ bool wide_walk(W &w, const uint4 *__restrict__ wide, const float4 *__restrict__ tris,
+                                          uint32_t *stk, bool active, uint32_t late) {
+    uint32_t *col = stk + lane_index();
+    WideState s;
+    if (active) s.start(col);
+    while ((uint32_t)__popcll(__ballot(s.busy())) > kQuadRays) wide_round(w, wide, tris, col, s, late);
+    if (__ballot(s.busy()) != 0ull) wide_drain(w, wide, tris, stk, s);
+    return s.overflow;
+}
 
 // Packet walk, for a wave whose lanes all walk one link set (nodes = that
 // set's node array, the same on every lane): the wave follows one node index,

@@ -37,6 +37,8 @@ struct pm_bvh {
     float lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
     float qlo[3] = {0, 0, 0}, qstep[3] = {1, 1, 1};
     uint4 *d_nodes = nullptr;   // [6][n_nodes] 16-byte nodes, then kPadNodes zeroed nodes
+    uint4 *d_wide = nullptr;    // [n_wide][4] four-child nodes of the wide walk (NULL: binary walks only)
+    int64_t n_wide = 0;
     float4 *d_tris = nullptr;   // [n_refs][3]
     uint32_t *d_next = nullptr; // work counter of the persistent traversal kernel
     uint32_t *d_perm = nullptr; // ray order of the reordering traversal (perm_cap entries)
@@ -74,6 +76,10 @@ int build_bvh_gpu(const float *verts, const uint32_t *mats, int64_t n_tri, int m
 // Upload a host-built BVH; fills b (device buffers owned by b).
 int upload_bvh(const HostBvh &h, hipStream_t s, pm_bvh *b);
 void free_bvh(pm_bvh *b);
+
+// Merge the binary tree of b's link set 0 (already on the device, enqueued on
+// s) into the four-child nodes of the wide walk; synchronises s.
+int build_wide(pm_bvh *b, hipStream_t s);
 
 // Validated arguments of one traced batch.  link_set < 0 selects by
 // direction; block: threads per workgroup of the one-ray-per-lane kernels

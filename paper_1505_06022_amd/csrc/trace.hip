@@ -121,6 +121,38 @@ __device__ __forceinline__ void trace_slot(const pmd::Bvh &bvh, const float4 *__
     }
 }
 
+// Rays through the four-child nodes (pmd::wide_walk), in the order of perm, of
+// the input, or of the 8x8 tiles of an image tile_w wide.  A wave takes the
+// kRays slots from kRays * wave on: 64, one per lane, or 16, which the walk
+// then puts on quads from the start.  Called by all lanes of a wave; stk is
+// the wave's stack.
+template <bool kPerm, uint32_t kRays>
+__device__ __forceinline__ void trace_wide(const pmd::Bvh &bvh, const float4 *__restrict__ rays,
+                                           const uint32_t *__restrict__ perm, uint64_t wave, uint64_t n,
+                                           int32_t *__restrict__ hit, float *__restrict__ tout, uint32_t late,
+                                           uint32_t tile_w, uint32_t *stk) {
+    const uint32_t lane = pmd::lane_index();
+    const uint64_t slot = wave * kRays + lane;
+    bool active = lane < kRays;
+    size_t r = 0;
+    if (!kPerm && tile_w > 0) {
+        const uint64_t tile = slot >> 6, l = slot & 63u, tiles_x = (tile_w + 7u) / 8u;
+        const uint64_t x = (tile % tiles_x) * 8u + (l & 7u), y = (tile / tiles_x) * 8u + (l >> 3);
+        active = active && x < tile_w && y < n / tile_w;
+        r = (size_t)(y * tile_w + x);
+    } else {
+        active = active && slot < n;
+        if (active) r = kPerm ? __builtin_nontemporal_load(perm + slot) : slot;
+    }
+    pmd::Walker w{};
+    if (active) start_walk(w, bvh, rays, r, 0);
+    const bool overflow = pmd::wide_walk(w, bvh.wide, bvh.tris, stk, active, late);
+    if (active) {
+        if (overflow) w.finish_binary(bvh);
+        finish_walk<false>(w, pmd::TraceStats{0u, 0u}, r, hit, tout, nullptr);
+    }
+}
+
 // Postponed-leaf walk over one wavefront's slice of the ray order: rays
 // begin .. end - 1 of perm (or of the input order without perm).  A lane
 // whose ray has ended takes the next ray of the slice, so lanes do not idle
@@ -215,6 +247,18 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace(pmd::Bvh bvh, const float
     const uint64_t lane = (uint64_t)pmd::xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     trace_slot<kStats, kWalk, false>(bvh, rays, nullptr, lane, (uint64_t)n, hit, tout, force_set, counters, late,
                                      tile_w);
+}
+
+// LDS: wide_lds(blockDim.x) bytes.
+template <bool kPerm, uint32_t kRays>
+__global__ __launch_bounds__(kTraceBlock) PM_WIDE_WAVES void k_trace_wide(pmd::Bvh bvh, const float4 *__restrict__ rays,
+                                                            const uint32_t *__restrict__ perm, int64_t n,
+                                                            int32_t *__restrict__ hit, float *__restrict__ tout,
+                                                            uint32_t late, uint32_t tile_w) {
+    extern __shared__ uint32_t wide_stack[];
+    const uint64_t lane = (uint64_t)pmd::xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+    trace_wide<kPerm, kRays>(bvh, rays, perm, lane >> 6, (uint64_t)n, hit, tout, late, tile_w,
+                             wide_stack + (threadIdx.x >> 6) * (64 * pmd::kWideStack));
 }
 
 // Persistent wavefronts with ray replacement (the scheduling idea of the
@@ -509,20 +553,31 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_perm(pmd::Bvh bvh, const 
 // tile_w wide, one 8x8 pixel tile per wavefront, as packets.  The dispatcher
 // hands out B's workgroups once all of A's are running, so B fills the
 // device as A's last wavefronts drain.
-template <bool kStats>
-__global__ __launch_bounds__(kTraceBlock) void k_trace_perm_then_tiles(
+// kWide: both batches go through the four-child nodes, B's tiles one ray per
+// lane.
+template <bool kStats, bool kWide>
+__global__ __launch_bounds__(kTraceBlock) PM_WIDE_WAVES void k_trace_perm_then_tiles(
     pmd::Bvh bvh, uint32_t blocksA, const float4 *__restrict__ raysA, const uint32_t *__restrict__ perm, uint32_t nA,
     int32_t *__restrict__ hitA, float *__restrict__ tA, int32_t setA, uint32_t *__restrict__ countersA, uint32_t late,
     const float4 *__restrict__ raysB, int64_t nB, int32_t *__restrict__ hitB, float *__restrict__ tB, int32_t setB,
-    uint32_t *__restrict__ countersB, uint32_t tile_w) {
+    uint32_t *__restrict__ countersB, uint32_t tile_w, uint32_t lateB) {
+    extern __shared__ uint32_t wide_stack[];
     if (blockIdx.x < blocksA) {
         const uint64_t lane = (uint64_t)pmd::xcd_block(blockIdx.x, blocksA) * blockDim.x + threadIdx.x;
-        trace_slot<kStats, kWalkPostponed, true>(bvh, raysA, perm, lane, nA, hitA, tA, setA, countersA, late, 0u);
+        if constexpr (kWide)
+            trace_wide<true, 64>(bvh, raysA, perm, lane >> 6, nA, hitA, tA, late, 0u,
+                                 wide_stack + (threadIdx.x >> 6) * (64 * pmd::kWideStack));
+        else
+            trace_slot<kStats, kWalkPostponed, true>(bvh, raysA, perm, lane, nA, hitA, tA, setA, countersA, late, 0u);
     } else {
         const uint64_t lane =
             (uint64_t)pmd::xcd_block(blockIdx.x - blocksA, gridDim.x - blocksA) * blockDim.x + threadIdx.x;
-        trace_slot<kStats, kWalkPacket, false>(bvh, raysB, nullptr, lane, (uint64_t)nB, hitB, tB, setB, countersB, 0u,
-                                               tile_w);
+        if constexpr (kWide)
+            trace_wide<false, 64>(bvh, raysB, nullptr, lane >> 6, (uint64_t)nB, hitB, tB, lateB, tile_w,
+                                  wide_stack + (threadIdx.x >> 6) * (64 * pmd::kWideStack));
+        else
+            trace_slot<kStats, kWalkPacket, false>(bvh, raysB, nullptr, lane, (uint64_t)nB, hitB, tB, setB, countersB,
+                                                   0u, tile_w);
     }
 }
 
@@ -533,11 +588,13 @@ namespace pm {
 pmd::Bvh make_device_bvh(const pm_bvh *b) {
     pmd::Bvh d;
     d.nodes = b->d_nodes;
+    d.wide = b->d_wide;
     d.tris = b->d_tris;
     d.n_nodes = (uint32_t)b->n_nodes;
     for (int a = 0; a < 3; ++a) {
         d.qlo[a] = b->qlo[a];
         d.qstep[a] = b->qstep[a];
+        d.inv_max[a] = 0x1p100f / b->qstep[a];
     }
     return d;
 }
@@ -571,13 +628,13 @@ int upload_bvh(const HostBvh &h, hipStream_t s, pm_bvh *b) {
     PM_HIP(hipMalloc(&b->d_next, 64));
     PM_HIP(hipMemcpyAsync(b->d_nodes, h.nodes.data(), nb, hipMemcpyHostToDevice, s));
     PM_HIP(hipMemcpyAsync(b->d_tris, h.tris.data(), tb, hipMemcpyHostToDevice, s));
-    // host vectors are freed by the caller: wait for the copies
-    PM_HIP(hipStreamSynchronize(s));
-    return PM_OK;
+    // host vectors are freed by the caller: build_wide waits for the copies
+    return build_wide(b, s);
 }
 
 void free_bvh(pm_bvh *b) {
     if (b->d_nodes) (void)hipFree(b->d_nodes);
+    if (b->d_wide) (void)hipFree(b->d_wide);
     if (b->d_tris) (void)hipFree(b->d_tris);
     if (b->d_next) (void)hipFree(b->d_next);
     if (b->d_perm) (void)hipFree(b->d_perm);
@@ -594,6 +651,7 @@ void free_bvh(pm_bvh *b) {
     b->d_order = nullptr;
     b->perm_cap = 0;
     b->d_nodes = nullptr;
+    b->d_wide = nullptr;
     b->d_tris = nullptr;
     b->d_next = nullptr;
 }
@@ -643,6 +701,49 @@ static int launch_slices(const pm_bvh *b, const pmd::Bvh &bvh, const float *rays
     if (blocks > 0x7fffffffull) return set_error("too many rays for one launch"), PM_ERR_ARG;
     hipLaunchKernelGGL(counters ? k_trace_slices<true> : k_trace_slices<false>, dim3((uint32_t)blocks), dim3(block),
                        0, s, bvh, (const float4 *)rays, perm, n, hit, t, link_set, counters, late, per);
+    PM_HIP(hipGetLastError());
+    return PM_OK;
+}
+
+// The wide walk takes the rays of the default, the postponed and the packet kernel.  A
+// forced link set walks that set's binary tree (that is what it asks for) and
+// the counters count the binary tree's tests, so both keep the binary walk; so
+// does a BVH without four-child nodes.
+static bool takes_wide(const pm_bvh *b, int kernel, int link_set, const uint32_t *counters) {
+    return b->d_wide && (kernel == PM_TRACE_AUTO || kernel == PM_TRACE_POSTPONED || kernel == PM_TRACE_PACKET) &&
+           link_set < 0 && !counters;
+}
+
+// The wide walk's threshold for held leaf tests: the postponed kernel's is its refill option.
+// (The default 24: 16 and 32 are within 2% of it on every batch tried.)
+constexpr uint32_t kAutoLate = 24;
+static uint32_t wide_late(int kernel, int refill) {
+    return kernel == PM_TRACE_POSTPONED ? (uint32_t)refill : kAutoLate;
+}
+
+static uint32_t wide_lds(uint32_t block) { return block * pmd::kWideStack * (uint32_t)sizeof(uint32_t); }
+
+// Default workgroup of the wide walk: one wave, so that a finished wave frees its slot (and its stack) at once.
+constexpr uint32_t kWideBlock = 64;
+
+// Rays up to which a wave takes 16 rays, on quads from the start, instead of
+// 64: below it the device holds all the waves either way, and a quad's step is
+// shorter (2^18-triangle soup, us with 16 and with 64 rays a wave: 68 and 88
+// for 1,009 rays, 114 and 134 for 32,768, 138 and 150 for 65,536; 201 and 170
+// for 131,072).
+constexpr int64_t kWideSmall = 1 << 16;
+
+// n rays (with tiles: n pixels in `slots` tile slots) in the order of perm or, without it, of the input.
+static int launch_wide(const pmd::Bvh &bvh, const float *rays, const uint32_t *perm, int64_t n, int64_t slots,
+                       int32_t *hit, float *t, uint32_t late, uint32_t tile_w, uint32_t block, hipStream_t s) {
+    const uint32_t per_wave = slots <= kWideSmall ? 16u : 64u;
+    const uint64_t waves = ((uint64_t)slots + per_wave - 1) / per_wave;
+    const uint64_t blocks = (waves * 64 + block - 1) / block;
+    if (blocks > 0x7fffffffull) return set_error("too many rays for one launch"), PM_ERR_ARG;
+    auto kern = per_wave == 16u ? (perm ? k_trace_wide<true, 16> : k_trace_wide<false, 16>)
+                                : (perm ? k_trace_wide<true, 64> : k_trace_wide<false, 64>);
+    hipLaunchKernelGGL(kern, dim3((uint32_t)blocks), dim3(block), wide_lds(block), s, bvh, (const float4 *)rays, perm,
+                       n, hit, t, late, tile_w);
     PM_HIP(hipGetLastError());
     return PM_OK;
 }
@@ -762,6 +863,9 @@ static int launch_trace_reordered(const pm_bvh *b, const BucketScratch &sc, cons
     int rc = bucket_rays(b, sc, rays, n, link_set, reorder, s);
     if (rc) return rc;
     const uint32_t nn = (uint32_t)n;
+    if (takes_wide(b, kernel, link_set, counters)) {
+        return launch_wide(bvh, rays, sc.perm, n, n, hit, t, wide_late(kernel, (int)late), 0u, block, s);
+    }
     if (kernel == PM_TRACE_PERSISTENT)
         return launch_persistent(b, bvh, rays, nn, hit, t, link_set, counters, (int)late, sc.perm, s);
     if (kernel == PM_TRACE_SLICES)
@@ -827,6 +931,8 @@ int launch_trace(const pm_bvh *b, const TraceArgs &a, hipStream_t s) {
         return launch_trace_reordered(b, sc, bvh, a.rays, n, a.hit, a.t, a.link_set, a.counters, kernel, late,
                                       a.reorder, (uint32_t)block, a.slice, s);
     }
+    const bool wide = takes_wide(b, kernel, a.link_set, a.counters);
+    const uint32_t w_late = wide_late(kernel, a.refill);
     if (kernel == 0) kernel = PM_TRACE_PER_RAY;
     if (kernel == PM_TRACE_PERSISTENT || kernel == PM_TRACE_SLICES) {
         if (n >= (int64_t(1) << 31)) {
@@ -850,6 +956,10 @@ int launch_trace(const pm_bvh *b, const TraceArgs &a, hipStream_t s) {
         set_error("too many rays for one launch");
         return PM_ERR_ARG;
     }
+    if (wide) {
+        return launch_wide(bvh, a.rays, nullptr, n, lanes, a.hit, a.t, w_late, (uint32_t)a.tile_w,
+                           a.block == 0 ? kWideBlock : (uint32_t)block, s);
+    }
     using Kern = void (*)(pmd::Bvh, const float4 *, int64_t, int32_t *, float *, int32_t, uint32_t *, uint32_t,
                           uint32_t);
     Kern kern = a.counters ? pick_walk<Kern>(wk, k_trace<true, kWalkStep>, k_trace<true, kWalkPaired>,
@@ -872,15 +982,18 @@ static int launch_perm_then_tiles(pm_bvh *b, const TraceArgs &A, const TraceArgs
     if (rc) return rc;
     const pmd::Bvh bvh = make_device_bvh(b);
     const uint32_t nA = (uint32_t)A.n;
+    const bool wide = takes_wide(b, A.kernel, A.link_set, A.counters) && takes_wide(b, B.kernel, B.link_set, B.counters);
     const uint64_t blocksA = ((uint64_t)nA + block - 1) / block;
     const int64_t tiles = (((int64_t)B.tile_w + 7) / 8) * ((B.n / B.tile_w + 7) / 8);
     const uint64_t blocksB = ((uint64_t)tiles * 64 + block - 1) / block;
     if (blocksA + blocksB > 0x7fffffffull) return set_error("too many rays for one launch"), PM_ERR_ARG;
-    hipLaunchKernelGGL(A.counters ? k_trace_perm_then_tiles<true> : k_trace_perm_then_tiles<false>,
-                       dim3((uint32_t)(blocksA + blocksB)), dim3(block), 0, s, bvh, (uint32_t)blocksA,
+    auto kern = A.counters ? k_trace_perm_then_tiles<true, false>
+                : wide     ? k_trace_perm_then_tiles<false, true>
+                           : k_trace_perm_then_tiles<false, false>;
+    hipLaunchKernelGGL(kern, dim3((uint32_t)(blocksA + blocksB)), dim3(block), wide ? wide_lds(block) : 0, s, bvh, (uint32_t)blocksA,
                        (const float4 *)A.rays, (const uint32_t *)sc.perm, nA, A.hit, A.t, A.link_set, A.counters,
                        (uint32_t)A.refill, (const float4 *)B.rays, B.n, B.hit, B.t, B.link_set, B.counters,
-                       (uint32_t)B.tile_w);
+                       (uint32_t)B.tile_w, kAutoLate);
     PM_HIP(hipGetLastError());
     return PM_OK;
 }
