@@ -64,8 +64,13 @@ __device__ __forceinline__ int64_t stage_elems(const SppmDev &d) {
 // stage's item count is exhausted (each item is taken exactly once, so every
 // workgroup reaches the exit).
 template <int kStage, int kBs>
-__global__ __launch_bounds__(kBs) void k_batch(BatchDev b) {
+__global__ __launch_bounds__(kBs) __attribute__((amdgpu_waves_per_eu(kStage <= kStPhoton ? 4 : 1)))
+void k_batch(BatchDev b) {
     __shared__ uint32_t s_item;
+    // the wide walk's stacks (the stages that trace rays)
+    __shared__ uint32_t wide_stack[kStage == kStEye || kStage == kStPhoton ? kBs / 64 : 1]
+                                  [kStage == kStEye || kStage == kStPhoton ? kStackWords : 1];
+    uint32_t *const stk = kStage == kStEye || kStage == kStPhoton ? wide_stack[threadIdx.x >> 6] : nullptr;
     const uint32_t *off = b.item_off + kStage * (b.S + 1);
     const uint32_t total = off[b.S];
     const uint32_t k = *b.iter;
@@ -84,7 +89,7 @@ __global__ __launch_bounds__(kBs) void k_batch(BatchDev b) {
             constexpr int kWaves = kBs / 64;
             const int64_t span = (end - e0 + kWaves - 1) / kWaves;
             const int64_t w0 = min(e0 + (int64_t)(threadIdx.x >> 6) * span, end), w1 = min(w0 + span, end);
-            photon_regen_range(d, k, (uint32_t)w0, (uint32_t)w1, d.refill);
+            photon_regen_range(d, k, (uint32_t)w0, (uint32_t)w1, d.refill, stk);
             continue;
         }
         if (kStage == kStRmax) {
@@ -113,10 +118,13 @@ __global__ __launch_bounds__(kBs) void k_batch(BatchDev b) {
             }
             continue;
         }
-        for (int64_t e = e0 + threadIdx.x; e < end; e += kBs) {
-            if (kStage == kStEye) eye_elem(d, k, e, true);
-            if (kStage == kStUpdate) update_elem(d, e, nullptr);
+        if (kStage == kStEye) {
+            // every lane of the workgroup takes part in each round
+            for (int64_t e = e0; e < end; e += kBs) eye_elem(d, k, e + threadIdx.x, e + threadIdx.x < end, true, stk);
+            continue;
         }
+        for (int64_t e = e0 + threadIdx.x; e < end; e += kBs)
+            if (kStage == kStUpdate) update_elem(d, e, nullptr);
     }
 }
 

@@ -16,9 +16,15 @@ namespace {
 
 using namespace pmd;
 
-__global__ __launch_bounds__(kBlock) void k_eye(SppmDev d, uint32_t k, int32_t accumulate_D) {
+// The wide walk's stacks of a workgroup, and its wave's share.
+#define PM_STACK()                                           \
+    __shared__ uint32_t wide_stack[kBlock / 64][kStackWords]; \
+    uint32_t *const stk = wide_stack[threadIdx.x >> 6]
+
+__global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_eye(SppmDev d, uint32_t k, int32_t accumulate_D) {
     int64_t p = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
-    if (p < d.P) eye_elem(d, k, p, accumulate_D != 0);
+    PM_STACK();
+    eye_elem(d, k, p, p < d.P, accumulate_D != 0, stk);
 }
 
 // The statistics variants (PM_PROFILE_COUNT): the same work, plus counts of
@@ -27,49 +33,57 @@ __global__ __launch_bounds__(kBlock) void k_eye(SppmDev d, uint32_t k, int32_t a
 __global__ __launch_bounds__(kBlock) void k_eye_stats(SppmDev d, uint32_t k, int32_t accumulate_D) {
     int64_t p = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
     LaneStats ls;
-    if (p < d.P) eye_elem<true>(d, k, p, accumulate_D != 0, &ls);
+    eye_elem<true>(d, k, p, p < d.P, accumulate_D != 0, nullptr, &ls);
     wave_stats_flush(d.stats + kStatEyePaths, ls);
 }
 
 template <bool kRecord>
-__global__ __launch_bounds__(kBlock) void k_photon(SppmDev d, uint32_t k, uint16_t *__restrict__ mat_tab,
+__global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon(SppmDev d, uint32_t k, uint16_t *__restrict__ mat_tab,
                                                    long long *__restrict__ adj_tab) {
     uint32_t n = xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
-    if (n < d.n_paths) photon_elem<kRecord>(d, k, n, mat_tab, adj_tab);
+    PM_STACK();
+    photon_elem<kRecord>(d, k, n, n < d.n_paths, mat_tab, adj_tab, stk);
 }
 
 // Persistent photon lanes with path regeneration.
-__global__ __launch_bounds__(kBlock) void k_photon_regen(SppmDev d, uint32_t k) { photon_regen_loop(d, k, d.refill); }
+__global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_regen(SppmDev d, uint32_t k) {
+    PM_STACK();
+    photon_regen_loop(d, k, d.refill, stk);
+}
 
 __global__ __launch_bounds__(kBlock) void k_photon_regen_stats(SppmDev d, uint32_t k) {
-    photon_regen_loop<false, true>(d, k, d.refill);
+    photon_regen_loop<false, true>(d, k, d.refill, nullptr);
 }
 
 // Two-phase photon pass (PM_PHOTON_TWO_PHASE): regeneration that sets the
 // last paths of each wavefront aside once the path counter has run out, then
 // regeneration over the paths set aside.
 template <bool kStats>
-__global__ __launch_bounds__(kBlock) void k_photon_head(SppmDev d, uint32_t k, PathQueue q) {
-    photon_regen_loop<false, kStats, true, false>(d, k, d.refill, nullptr, nullptr, q);
+__global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_head(SppmDev d, uint32_t k, PathQueue q) {
+    PM_STACK();
+    photon_regen_loop<false, kStats, true, false>(d, k, d.refill, stk, nullptr, nullptr, q);
 }
 
 template <bool kStats>
-__global__ __launch_bounds__(kBlock) void k_photon_tail(SppmDev d, uint32_t k, PathQueue q) {
-    photon_regen_loop<false, kStats, false, true>(d, k, d.refill, nullptr, nullptr, q);
+__global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_tail(SppmDev d, uint32_t k, PathQueue q) {
+    PM_STACK();
+    photon_regen_loop<false, kStats, false, true>(d, k, d.refill, stk, nullptr, nullptr, q);
 }
 
 // The same two launches, recording each path's stored-photon materials for
 // the adjoint (a queued path keeps its row of the tables).
-__global__ __launch_bounds__(kBlock) void k_photon_head_rec(SppmDev d, uint32_t k, PathQueue q,
+__global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_head_rec(SppmDev d, uint32_t k, PathQueue q,
                                                             uint16_t *__restrict__ mat_tab,
                                                             long long *__restrict__ adj_tab) {
-    photon_regen_loop<true, false, true, false>(d, k, d.refill, mat_tab, adj_tab, q);
+    PM_STACK();
+    photon_regen_loop<true, false, true, false>(d, k, d.refill, stk, mat_tab, adj_tab, q);
 }
 
-__global__ __launch_bounds__(kBlock) void k_photon_tail_rec(SppmDev d, uint32_t k, PathQueue q,
+__global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_tail_rec(SppmDev d, uint32_t k, PathQueue q,
                                                             uint16_t *__restrict__ mat_tab,
                                                             long long *__restrict__ adj_tab) {
-    photon_regen_loop<true, false, false, true>(d, k, d.refill, mat_tab, adj_tab, q);
+    PM_STACK();
+    photon_regen_loop<true, false, false, true>(d, k, d.refill, stk, mat_tab, adj_tab, q);
 }
 
 // Regeneration from a queue of started paths in LDS (PM_PHOTON_POOL): each
@@ -90,15 +104,17 @@ __global__ __launch_bounds__(kBlock) void k_photon_stream_stats(SppmDev d, uint3
 }
 
 // The same, recording each path's stored-photon materials for the adjoint.
-__global__ __launch_bounds__(kBlock) void k_photon_regen_rec(SppmDev d, uint32_t k, uint16_t *__restrict__ mat_tab,
+__global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_regen_rec(SppmDev d, uint32_t k, uint16_t *__restrict__ mat_tab,
                                                              long long *__restrict__ adj_tab) {
-    photon_regen_loop<true>(d, k, d.refill, mat_tab, adj_tab);
+    PM_STACK();
+    photon_regen_loop<true>(d, k, d.refill, stk, mat_tab, adj_tab);
 }
 
 // One pass of the one-bounce-per-pass schedule; the grid covers the slots
 // with the same workgroup-to-slot map in every pass.
-__global__ __launch_bounds__(kBlock) void k_photon_pass(SppmDev d, uint32_t k, PassSlots ps) {
-    photon_pass_elem(d, k, ps, xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x);
+__global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_pass(SppmDev d, uint32_t k, PassSlots ps) {
+    PM_STACK();
+    photon_pass_elem(d, k, ps, xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x, stk);
 }
 
 // Paths no pass started, before the drain adds the paths still in flight.
@@ -106,8 +122,9 @@ __global__ void k_pass_tally(SppmDev d) {
     if (threadIdx.x == 0) d.counters[3] = d.n_paths - min(d.counters[2], d.n_paths);
 }
 
-__global__ __launch_bounds__(kBlock) void k_photon_drain(SppmDev d, uint32_t k, PassSlots ps) {
-    photon_drain_elem(d, k, ps, xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x);
+__global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_drain(SppmDev d, uint32_t k, PassSlots ps) {
+    PM_STACK();
+    photon_drain_elem(d, k, ps, xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x, stk);
 }
 
 // Start of a photon pass: clear its store's photon count and the path counter.

@@ -91,24 +91,65 @@ __device__ __forceinline__ int ray_set(const SppmDev &d, V3 dir) {
     return d.force_set >= 0 ? d.force_set : link_set(dir);
 }
 
+// Words of a wave's stack in LDS for the wide walk.
+constexpr int kStackWords = 64 * kWideStack;
+// The wide walk's threshold for held leaf tests in the SPPM passes.
+constexpr uint32_t kSppmLate = 24;
+// Wavefronts per SIMD that the kernels with a path and a walk ask for: at most
+// 128 registers.  At 5 (96 registers) up to 27 of them spill: 7.2 against 6.3
+// ms for a 333x187 render, 9.6 and 9.7 for 8 iterations at 1280x720; at 6
+// every case is slower than at 5.
+#define PM_PASS_WAVES __attribute__((amdgpu_waves_per_eu(4)))
+
+// Closest hits of one ray per lane, called by all lanes of a wave (active:
+// this lane has a ray; the others return -1).  stk is the wave's stack
+// (kStackWords words of LDS) or NULL: without it, with one link set forced,
+// when counting (the counts are the binary tree's) and on a BVH without
+// four-child nodes the rays take the binary walk.
+template <bool kStats, bool kPairTris>
+__device__ __forceinline__ int32_t wave_closest_hit(const SppmDev &d, uint32_t *stk, bool active, V3 org, V3 dir,
+                                                    float tmin, int32_t excl, float &t, uint32_t &kp, TraceStats &st) {
+    const Bvh &bvh = d.sc.bvh;
+    t = __builtin_inff();
+    kp = 0u;
+    if (!kStats && stk != nullptr && bvh.wide != nullptr && d.force_set < 0) {
+        Walker w{};
+        if (active) w.init(bvh, 0, org, dir, tmin, __builtin_inff(), excl);
+        const bool overflow = wide_walk(w, bvh.wide, bvh.tris, stk, active, kSppmLate);
+        if (!active) return -1;
+        if (overflow) w.finish_binary(bvh);
+        t = w.t_hit();
+        kp = w.best_k;
+        return w.best;
+    }
+    if (!active) return -1;
+    return closest_hit<kStats, kPairTris>(bvh, ray_set(d, dir), org, dir, tmin, __builtin_inff(), excl, t, kp, st,
+                                          d.paired_walk != 0);
+}
+
 // ---------------------------------------------------------------------------
 // Eye pass: a jittered pinhole ray followed through mirror and glass to the
 // first diffuse (rho > 0) surface, which becomes the pixel's hit point;
 // directly seen emission is accumulated into D (skipped when replaying).
+// Called by all lanes of a wave; active: this lane has pixel p.
 // ---------------------------------------------------------------------------
 template <bool kStats = false>
-__device__ __forceinline__ void eye_elem(const SppmDev &d, uint32_t k, int64_t p, bool accumulate_D,
-                                        LaneStats *ls = nullptr) {
+__device__ __forceinline__ void eye_elem(const SppmDev &d, uint32_t k, int64_t p, bool active, bool accumulate_D,
+                                         uint32_t *stk, LaneStats *ls = nullptr) {
     const SceneDev &sc = d.sc;
-    int32_t px = (int32_t)(p % sc.W), py = (int32_t)(p / sc.W);
-    Rng g = rng_seed(d.seed, kKindEye, k, (uint64_t)p);
-    float j0 = rng_next(g), j1 = rng_next(g);
-    float fx = ((float)px + j0) / (float)sc.W;
-    float fy = ((float)py + j1) / (float)sc.H;
-    float sx = (2.0f * fx - 1.0f) * (sc.tanh_fov * sc.aspect);
-    float sy = (1.0f - 2.0f * fy) * sc.tanh_fov;
-    V3 dir = vnorm(v3((sc.cf.x + sx * sc.cr.x) + sy * sc.cu.x, (sc.cf.y + sx * sc.cr.y) + sy * sc.cu.y,
-                      (sc.cf.z + sx * sc.cr.z) + sy * sc.cu.z));
+    Rng g{1, 1, 1, 1};
+    V3 dir = v3(0.0f, 0.0f, 0.0f);
+    if (active) {
+        int32_t px = (int32_t)(p % sc.W), py = (int32_t)(p / sc.W);
+        g = rng_seed(d.seed, kKindEye, k, (uint64_t)p);
+        float j0 = rng_next(g), j1 = rng_next(g);
+        float fx = ((float)px + j0) / (float)sc.W;
+        float fy = ((float)py + j1) / (float)sc.H;
+        float sx = (2.0f * fx - 1.0f) * (sc.tanh_fov * sc.aspect);
+        float sy = (1.0f - 2.0f * fy) * sc.tanh_fov;
+        dir = vnorm(v3((sc.cf.x + sx * sc.cr.x) + sy * sc.cu.x, (sc.cf.y + sx * sc.cr.y) + sy * sc.cu.y,
+                       (sc.cf.z + sx * sc.cr.z) + sy * sc.cu.z));
+    }
     V3 org = sc.cpos;
     float tmin = 0.0f, thr = 1.0f;
     int32_t excl = -1;
@@ -116,13 +157,15 @@ __device__ __forceinline__ void eye_elem(const SppmDev &d, uint32_t k, int64_t p
     float4 pos = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     float4 nrm = make_float4(0.0f, 0.0f, 0.0f, __int_as_float(-1));
     TraceStats st{0u, 0u};
-    for (int depth = 0; depth < d.max_depth; ++depth) {
+    bool going = active;
+    for (int depth = 0; depth < d.max_depth && __ballot(going) != 0ull; ++depth) {
         float t;
         uint32_t kp;
-        int32_t h = closest_hit<kStats>(sc.bvh, ray_set(d, dir), org, dir, tmin, __builtin_inff(), excl, t, kp, st,
-                                        d.paired_walk != 0);
+        const int32_t h = wave_closest_hit<kStats, false>(d, stk, going, org, dir, tmin, excl, t, kp, st);
+        if (!going) continue;
         if (kStats) ls->rays++;
-        if (h < 0) break;
+        going = h >= 0;
+        if (!going) continue;
         V3 x = vray(org, t, dir);
         Tri tr = load_tri(sc.bvh.tris, kp);
         V3 n = tri_normal(tr);
@@ -138,7 +181,7 @@ __device__ __forceinline__ void eye_elem(const SppmDev &d, uint32_t k, int64_t p
                 pos = make_float4(x.x, x.y, x.z, (thr * rho) * kInvPiF);
                 nrm = make_float4(nh.x, nh.y, nh.z, __uint_as_float(m));
             }
-            break;
+            going = false;
         } else if (type == PM_MAT_MIRROR) {
             dir = reflect(dir, n);
         } else {
@@ -148,6 +191,7 @@ __device__ __forceinline__ void eye_elem(const SppmDev &d, uint32_t k, int64_t p
         tmin = sc.eps;
         excl = h;
     }
+    if (!active) return;
     d.hp_pos[p] = pos;
     d.hp_nrm[p] = nrm;
     if (accumulate_D) d.D[p] += dadd;
@@ -229,21 +273,22 @@ __device__ __forceinline__ bool photon_shade(const SppmDev &d, PhotonPath &P, in
                                              uint16_t *__restrict__ mat_tab, long long *__restrict__ adj_tab,
                                              LaneStats *ls);
 
+// Called by all lanes of a wave; live: this lane has a path.
 template <bool kRecord, bool kStats = false>
-__device__ __forceinline__ bool photon_bounce(const SppmDev &d, PhotonPath &P, uint16_t *__restrict__ mat_tab,
-                                              long long *__restrict__ adj_tab, LaneStats *ls = nullptr) {
+__device__ __forceinline__ bool photon_bounce(const SppmDev &d, PhotonPath &P, bool live,
+                                              uint16_t *__restrict__ mat_tab, long long *__restrict__ adj_tab,
+                                              uint32_t *stk, LaneStats *ls = nullptr) {
     const SceneDev &sc = d.sc;
     float t;
     uint32_t kp;
     TraceStats st{0u, 0u};
-    int32_t h = closest_hit<kStats, true>(sc.bvh, ray_set(d, P.dir), P.org, P.dir, sc.eps, __builtin_inff(), P.excl,
-                                          t, kp, st, d.paired_walk != 0);
-    if (kStats) {
+    const int32_t h = wave_closest_hit<kStats, true>(d, stk, live, P.org, P.dir, sc.eps, P.excl, t, kp, st);
+    if (kStats && live) {
         ls->rays++;
         ls->boxes += st.boxes;
         ls->tris += st.tris;
     }
-    return photon_shade<kRecord, kStats>(d, P, h, t, kp, mat_tab, adj_tab, ls);
+    return live && photon_shade<kRecord, kStats>(d, P, h, t, kp, mat_tab, adj_tab, ls);
 }
 
 // The rest of a bounce once the closest hit (h, t, kp) of the ray from P.org
@@ -305,15 +350,16 @@ __device__ __forceinline__ void photon_finish(const SppmDev &d, const PhotonPath
     if (kRecord && P.last + 1 < d.max_bounces) mat_tab[(size_t)P.n * d.max_bounces + P.last + 1] = kMatEnd;
 }
 
-// Photon path n traced to its end by one lane.
+// Photon path n traced to its end by one lane (active: n is a path).  Called
+// by all lanes of a wave.
 template <bool kRecord>
-__device__ __forceinline__ void photon_elem(const SppmDev &d, uint32_t k, uint32_t n, uint16_t *__restrict__ mat_tab,
-                                            long long *__restrict__ adj_tab) {
-    PhotonPath P;
-    if (photon_emit(d, k, n, P))
-        while (photon_bounce<kRecord>(d, P, mat_tab, adj_tab)) {
-        }
-    photon_finish<kRecord>(d, P, mat_tab);
+__device__ __forceinline__ void photon_elem(const SppmDev &d, uint32_t k, uint32_t n, bool active,
+                                            uint16_t *__restrict__ mat_tab, long long *__restrict__ adj_tab,
+                                            uint32_t *stk) {
+    PhotonPath P{};
+    bool live = active && photon_emit(d, k, n, P);
+    while (__ballot(live) != 0ull) live = photon_bounce<kRecord>(d, P, live, mat_tab, adj_tab, stk);
+    if (active) photon_finish<kRecord>(d, P, mat_tab);
 }
 
 // Path state in device memory (56 B per slot, structure of arrays), used by
@@ -387,11 +433,11 @@ struct PathQueue {
 // lanes take the queued paths (counted by queue.cnt[1]) instead of starting
 // new ones.
 template <bool kRecord = false, bool kStats = false, bool kPark = false, bool kQueue = false>
-__device__ __forceinline__ void photon_regen_loop(const SppmDev &d, uint32_t k, uint32_t refill,
+__device__ __forceinline__ void photon_regen_loop(const SppmDev &d, uint32_t k, uint32_t refill, uint32_t *stk,
                                                   uint16_t *__restrict__ mat_tab = nullptr,
                                                   long long *__restrict__ adj_tab = nullptr,
                                                   PathQueue queue = PathQueue{}) {
-    PhotonPath P;
+    PhotonPath P{};
     LaneStats ls;
     bool live = false, exhausted = false;
     uint32_t n_queued = 0u;
@@ -431,10 +477,9 @@ __device__ __forceinline__ void photon_regen_loop(const SppmDev &d, uint32_t k, 
                 break;
             }
         }
-        if (live) {
-            live = photon_bounce<kRecord, kStats>(d, P, mat_tab, adj_tab, &ls);
-            if (kRecord && !live) photon_finish<true>(d, P, mat_tab);
-        }
+        const bool was_live = live;
+        live = photon_bounce<kRecord, kStats>(d, P, live, mat_tab, adj_tab, stk, &ls);
+        if (kRecord && was_live && !live) photon_finish<true>(d, P, mat_tab);
     }
     if (kStats) {
         wave_stats_flush(d.stats + kStatPhotonPaths, ls);
@@ -485,7 +530,7 @@ __device__ __forceinline__ void pool_get(const uint32_t *pool, uint32_t slot, Ph
 
 template <bool kStats = false>
 __device__ __forceinline__ void photon_pool_loop(const SppmDev &d, uint32_t k, uint32_t *__restrict__ pool) {
-    PhotonPath P;
+    PhotonPath P{};
     LaneStats ls;
     bool live = false, exhausted = false;
     uint32_t queued = 0;  // paths in the queue (wave-uniform)
@@ -528,7 +573,8 @@ __device__ __forceinline__ void photon_pool_loop(const SppmDev &d, uint32_t k, u
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
         if (__ballot(live) == 0ull && exhausted && queued == 0u) break;
-        if (live) live = photon_bounce<false, kStats>(d, P, nullptr, nullptr, &ls);
+        // (the binary walk: the queue and the wide walk's stacks together would halve the resident wavefronts)
+        live = photon_bounce<false, kStats>(d, P, live, nullptr, nullptr, nullptr, &ls);
     }
     if (kStats) {
         wave_stats_flush(d.stats + kStatPhotonPaths, ls);
@@ -618,8 +664,8 @@ __device__ __forceinline__ void photon_stream_loop(const SppmDev &d, uint32_t k,
 // without atomics.  Called by every lane of a wave; the loop ends once the
 // range is handed out and no path is live.
 __device__ __forceinline__ void photon_regen_range(const SppmDev &d, uint32_t k, uint32_t n0, uint32_t n1,
-                                                   uint32_t refill) {
-    PhotonPath P;
+                                                   uint32_t refill, uint32_t *stk) {
+    PhotonPath P{};
     bool live = false;
     uint32_t next = n0;
     for (;;) {
@@ -634,7 +680,7 @@ __device__ __forceinline__ void photon_regen_range(const SppmDev &d, uint32_t k,
             live_mask = __ballot(live);
         }
         if (live_mask == 0ull && next >= n1) break;
-        if (live) live = photon_bounce<false>(d, P, nullptr, nullptr);
+        live = photon_bounce<false>(d, P, live, nullptr, nullptr, stk);
     }
 }
 
@@ -654,9 +700,10 @@ __device__ __forceinline__ uint32_t paths_handed_out(const SppmDev &d) {
 
 // One pass of slot s.  Called by every lane of a wave; lanes with s >= S
 // only take part in the wave's votes.
-__device__ __forceinline__ void photon_pass_elem(const SppmDev &d, uint32_t k, const PassSlots &ps, uint32_t s) {
+__device__ __forceinline__ void photon_pass_elem(const SppmDev &d, uint32_t k, const PassSlots &ps, uint32_t s,
+                                                 uint32_t *stk) {
     const bool in = s < ps.S;
-    PhotonPath P;
+    PhotonPath P{};
     const bool was_live = in && slot_load(ps, s, P);
     bool live = was_live;
     const bool want = in && !was_live;
@@ -665,19 +712,20 @@ __device__ __forceinline__ void photon_pass_elem(const SppmDev &d, uint32_t k, c
         const uint32_t n = wave_fetch_add(&d.counters[2], want_mask, want);
         if (want && n < d.n_paths) live = photon_emit(d, k, n, P);
     }
-    if (live) live = photon_bounce<false>(d, P, nullptr, nullptr);
+    live = photon_bounce<false>(d, P, live, nullptr, nullptr, stk);
     if (in && (live || was_live)) slot_store(ps, s, P, live);
 }
 
 // After the last pass: the paths still in flight are traced to their end and
 // the paths no pass started are taken by regenerating lanes.  Called by every
 // lane of a wave.
-__device__ __forceinline__ void photon_drain_elem(const SppmDev &d, uint32_t k, const PassSlots &ps, uint32_t s) {
-    PhotonPath P;
+__device__ __forceinline__ void photon_drain_elem(const SppmDev &d, uint32_t k, const PassSlots &ps, uint32_t s,
+                                                  uint32_t *stk) {
+    PhotonPath P{};
     bool live = s < ps.S && slot_load(ps, s, P);
     if (live) wave_append(&d.counters[3]);
-    while (live) live = photon_bounce<false>(d, P, nullptr, nullptr);
-    if (paths_handed_out(d) < d.n_paths) photon_regen_loop(d, k, d.refill);
+    while (__ballot(live) != 0ull) live = photon_bounce<false>(d, P, live, nullptr, nullptr, stk);
+    if (paths_handed_out(d) < d.n_paths) photon_regen_loop(d, k, d.refill, stk);
 }
 
 // ---------------------------------------------------------------------------
