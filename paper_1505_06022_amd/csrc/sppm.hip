@@ -1066,10 +1066,11 @@ int sppm_iterate(pm_sppm *s, int32_t n_iter, hipStream_t st) {
             hipLaunchKernelGGL(k_sh_clear, dim3(std::min<uint32_t>(blocks_for(T), 4096u)), dim3(kBlock), 0, st, dk, T);
             hipLaunchKernelGGL(k_sh_insert, dim3(ph_blocks), dim3(kBlock), 0, st, dk, k, s->cell_count);
             hipLaunchKernelGGL(k_sh_pick, dim3(ph_blocks), dim3(kBlock), 0, st, dk, k);
-            if (pipe) PM_HIP(hipEventRecord(s->ev_scat[k & 1u], st));
             if (timed) PM_HIP(hipEventRecord(ev[6], st));
             hipLaunchKernelGGL(k_sh_gather, dim3(blocks_for(s->P)), dim3(kBlock), 0, st, dk,
                                (const uint32_t *)s->cell_count);
+            // this gather reads the photon store itself: only now may the pass of k + 2 refill it
+            if (pipe) PM_HIP(hipEventRecord(s->ev_scat[k & 1u], st));
         } else {
             hipLaunchKernelGGL(k_count, dim3(ph_blocks), dim3(kBlock), 0, st, dk, s->cell_count);
             launch_bucket_scan(s->cell_count, s->cell_start, s->cell_fill, s->bsum, T, st);
