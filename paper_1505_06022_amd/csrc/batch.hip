@@ -32,12 +32,27 @@ enum Stage : int { kStEye = 0, kStPhoton, kStRmax, kStCount, kStScatter, kStGath
 // workgroup's wavefronts, which regenerate paths within their share.
 constexpr uint32_t kPhotonItem = 8;
 
+// Batches of at most kBatchSmall pixels in all: hit points per wave of the
+// range query, whose items are then one round of the workgroup (an item of
+// 1,024 pixels leaves most compute units without one: 8 scenes of 200,000
+// pixels in all took 3.7 ms a stage, now 0.44 with the wave's scan of whole
+// discs).
+constexpr int kBatchHits = 16;
+constexpr int64_t kBatchSmall = 1 << 19;
+
+// Elements of one item of a stage.
+__host__ __device__ inline int64_t item_elems(int stage, uint32_t chunk, int hits, int block) {
+    if (stage == kStPhoton) return (int64_t)chunk * kPhotonItem;
+    if (stage == kStGather && hits != 64) return block / 64 * kBatchHits;
+    return chunk;
+}
+
 struct BatchDev {
     const SppmDev *scenes;  // [S]
     int32_t S;
     uint32_t *queue;        // [kNumStages] work counters
     const uint32_t *item_off;  // [kNumStages][S + 1] first item of each scene
-    uint32_t chunk;         // elements per item
+    uint32_t chunk;         // elements per item (item_elems)
     uint32_t *iter;         // iteration index k
     uint32_t *cell_count, *cell_start, *cell_fill;
     float4 *sorted;
@@ -62,8 +77,8 @@ __device__ __forceinline__ int64_t stage_elems(const SppmDev &d) {
 
 // Persistent stage kernel: every workgroup loops taking items until the
 // stage's item count is exhausted (each item is taken exactly once, so every
-// workgroup reaches the exit).
-template <int kStage, int kBs>
+// workgroup reaches the exit).  kHits: hit points per wave of the range query.
+template <int kStage, int kBs, int kHits = 64>
 __global__ __launch_bounds__(kBs) __attribute__((amdgpu_waves_per_eu(kStage <= kStPhoton ? 4 : 1)))
 void k_batch(BatchDev b) {
     __shared__ uint32_t s_item;
@@ -82,7 +97,7 @@ void k_batch(BatchDev b) {
         if (it >= total) break;
         const int s = __builtin_amdgcn_readfirstlane(find_scene(off, b.S, it));
         const SppmDev &d = b.scenes[s];
-        const int64_t per = kStage == kStPhoton ? (int64_t)b.chunk * kPhotonItem : (int64_t)b.chunk;
+        const int64_t per = item_elems(kStage, b.chunk, kHits, kBs);
         const int64_t e0 = (int64_t)(it - off[s]) * per;
         const int64_t end = min(e0 + per, stage_elems<kStage>(d));
         if (kStage == kStPhoton) {
@@ -104,9 +119,11 @@ void k_batch(BatchDev b) {
         if (kStage == kStGather) {
             // every lane of the workgroup takes part in each round (p = P: no pixel)
             Grid gr = make_grid(d);
-            for (int64_t e = e0; e < end; e += kBs) {
-                const int64_t p = e + threadIdx.x;
-                gather_wave(d, gr, p < end ? p : d.P, b.cell_start, b.sorted);
+            constexpr int kWaves = kBs / 64;
+            const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+            for (int64_t e = e0; e < end; e += kWaves * kHits) {
+                const int64_t p = e + wave * kHits + lane;
+                gather_wave<kHits>(d, gr, p < end ? p : d.P, b.cell_start, b.sorted);
             }
             continue;
         }
@@ -175,6 +192,7 @@ struct pm_batch {
     int32_t K = 0;
     uint32_t chunk = 1024;
     int32_t block = 256;
+    int32_t hits = 64;  // hit points per wave of the range query
     bool use_graph = true;
     // device
     SppmDev *d_scenes = nullptr;
@@ -219,7 +237,9 @@ int occupancy_grids(pm_batch *b) {
     PM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     const void *kern[kNumStages] = {(const void *)k_batch<kStEye, kBs>, (const void *)k_batch<kStPhoton, kBs>,
                                     (const void *)k_batch<kStRmax, kBs>, (const void *)k_batch<kStCount, kBs>,
-                                    (const void *)k_batch<kStScatter, kBs>, (const void *)k_batch<kStGather, kBs>,
+                                    (const void *)k_batch<kStScatter, kBs>,
+                                    b->hits == 64 ? (const void *)k_batch<kStGather, kBs>
+                                                  : (const void *)k_batch<kStGather, kBs, kBatchHits>,
                                     (const void *)k_batch<kStUpdate, kBs>};
     for (int st = 0; st < kNumStages; ++st) {
         int per_cu = 0;
@@ -238,7 +258,10 @@ void enqueue_stage(const pm_batch *b, int stage, const BatchDev &bd, hipStream_t
         case kStRmax: hipLaunchKernelGGL((k_batch<kStRmax, kBs>), g, blk, 0, st, bd); break;
         case kStCount: hipLaunchKernelGGL((k_batch<kStCount, kBs>), g, blk, 0, st, bd); break;
         case kStScatter: hipLaunchKernelGGL((k_batch<kStScatter, kBs>), g, blk, 0, st, bd); break;
-        case kStGather: hipLaunchKernelGGL((k_batch<kStGather, kBs>), g, blk, 0, st, bd); break;
+        case kStGather:
+            if (b->hits == 64) hipLaunchKernelGGL((k_batch<kStGather, kBs>), g, blk, 0, st, bd);
+            else hipLaunchKernelGGL((k_batch<kStGather, kBs, kBatchHits>), g, blk, 0, st, bd);
+            break;
         default: hipLaunchKernelGGL((k_batch<kStUpdate, kBs>), g, blk, 0, st, bd); break;
     }
 }
@@ -287,7 +310,7 @@ int upload_items(pm_batch *b, hipStream_t st) {
             off[(size_t)stg * (S + 1) + s] = acc;
             const pm_sppm *m = b->members[s];
             int64_t n = stg == kStPhoton ? m->prm.n_photons : (stg == kStCount || stg == kStScatter ? 0 : m->P);
-            const int64_t per = stg == kStPhoton ? (int64_t)b->chunk * kPhotonItem : (int64_t)b->chunk;
+            const int64_t per = item_elems(stg, b->chunk, b->hits, b->block);
             acc += (uint32_t)((n + per - 1) / per);
         }
         off[(size_t)stg * (S + 1) + S] = acc;
@@ -491,17 +514,20 @@ int batch_create(const pm_scene_desc *const *descs, const pm_sppm_params *const 
     }
     // shared bucket arrays: scene s owns [table_off_s, table_off_s + T_s)
     uint64_t tot = 0, cap = 0;
+    int64_t pixels = 0;
     std::vector<SppmDev> devs(n);
     for (int32_t i = 0; i < n; ++i) {
         pm_sppm *m = b->members[i];
         m->dev.table_off = (uint32_t)tot;
         tot += uint64_t(1) << m->table_bits;
         cap += m->cap;
+        pixels += m->P;
         devs[i] = m->dev;
     }
     if (tot >= (uint64_t(1) << 31) || cap >= (uint64_t(1) << 31))
         return set_error("batch too large for 32-bit bucket offsets"), fail(PM_ERR_ARG);
     b->total_buckets = (uint32_t)tot;
+    b->hits = pixels <= kBatchSmall ? kBatchHits : 64;
     const uint32_t nbt = b->total_buckets / kScanTile;
     hipError_t e;
 #define PM_HIPB(call)                                           \

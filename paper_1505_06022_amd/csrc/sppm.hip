@@ -187,19 +187,14 @@ __global__ __launch_bounds__(kBlock) void k_scatter(SppmDev d, const uint32_t *_
         scatter_elem(d, j, start, sorted);
 }
 
+// Every lane takes part (the wave may scan a dense hit point together); a wave
+// takes kHits pixels.
+template <int kHits, bool kStats>
 __global__ __launch_bounds__(kBlock) void k_gather(SppmDev d, const uint32_t *__restrict__ start,
                                                    const float4 *__restrict__ sorted) {
-    // every lane takes part (the wave may scan a dense hit point together)
-    const int64_t p = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
+    const int64_t wave = (int64_t)xcd_block(blockIdx.x, gridDim.x) * (kBlock / 64) + (threadIdx.x >> 6);
     Grid gr = make_grid(d);
-    gather_wave(d, gr, p, start, sorted);
-}
-
-__global__ __launch_bounds__(kBlock) void k_gather_stats(SppmDev d, const uint32_t *__restrict__ start,
-                                                         const float4 *__restrict__ sorted) {
-    const int64_t p = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
-    Grid gr = make_grid(d);
-    gather_wave<true>(d, gr, p, start, sorted);
+    gather_wave<kHits, kStats>(d, gr, wave * kHits + (threadIdx.x & 63), start, sorted);
 }
 
 // Stochastic spatial hashing: clear the keys, insert every stored photon
@@ -1078,12 +1073,13 @@ int sppm_iterate(pm_sppm *s, int32_t n_iter, hipStream_t st) {
                                s->sorted);
             if (pipe) PM_HIP(hipEventRecord(s->ev_scat[k & 1u], st));
             if (timed) PM_HIP(hipEventRecord(ev[6], st));
-            if (count)
-                hipLaunchKernelGGL(k_gather_stats, dim3(blocks_for(s->P)), dim3(kBlock), 0, st, dk,
-                                   (const uint32_t *)s->cell_start, (const float4 *)s->sorted);
-            else
-                hipLaunchKernelGGL(k_gather, dim3(blocks_for(s->P)), dim3(kBlock), 0, st, dk,
-                                   (const uint32_t *)s->cell_start, (const float4 *)s->sorted);
+            const int hits = hits_per_wave(s->P);
+            auto gather = count        ? k_gather<64, true>
+                          : hits == 64 ? k_gather<64, false>
+                          : hits == 16 ? k_gather<16, false>
+                                       : k_gather<4, false>;
+            hipLaunchKernelGGL(gather, dim3(blocks_for(s->P * (64 / (count ? 64 : hits)))), dim3(kBlock), 0, st, dk,
+                               (const uint32_t *)s->cell_start, (const float4 *)s->sorted);
         }
         if (timed) PM_HIP(hipEventRecord(ev[7], st));
         double *hist = (int32_t)k < s->rec_iters ? s->R2_hist + (size_t)k * s->P : nullptr;

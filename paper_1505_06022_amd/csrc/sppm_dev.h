@@ -993,12 +993,25 @@ __device__ __forceinline__ void sh_gather_elem(const SppmDev &d, const Grid &gr,
 
 // Range query: per hit point, M photons and their flux, each term rounded to
 // 2^-shift fixed point and summed as integers (order independent).  Called
-// by every lane of a wave, one pixel per lane (p >= P: no pixel).  A hit
-// point whose buckets hold at least kCoopMin photons is scanned by the whole
-// wave, 64 consecutive photons per step, and the lanes' partial counts and
-// sums are added up; the others are scanned by their own lane.  Both give the
-// same M and flux.
-constexpr uint32_t kCoopMin = 256;
+// by every lane of a wave for its kHits pixels, one per lane (p >= P, or a lane
+// from kHits on: no pixel).  A hit point whose buckets hold at least
+// coop_min(kHits) photons is scanned by the whole wave and the lanes' partial
+// counts and sums are added up; the others are scanned by their own lane.
+// Both give the same M and flux.
+//
+// What bounds it is latency: a lane's scan waits for a bucket's bounds, then
+// for each photon.  The wave's scan therefore reads the bounds of all of a hit
+// point's buckets at once, one per lane, and takes the photons of all of them
+// as one run, kScanLoads loads in flight per lane.  A small image gives each
+// wave fewer hit points (hits_per_wave).
+constexpr uint32_t coop_min(int hits) { return 4u * (uint32_t)hits; }
+constexpr int kScanLoads = 4;
+
+// Hit points per wave of the range query: enough waves to fill the device (at
+// 2^14 pixels 4 give 4,096 waves, four per SIMD; at 2^17 16 give 8,192).
+__host__ __device__ inline int hits_per_wave(int64_t pixels) {
+    return pixels <= (1 << 14) ? 4 : (pixels <= (1 << 17) ? 16 : 64);
+}
 
 __device__ __forceinline__ uint32_t lane_id() {
     return __builtin_amdgcn_mbcnt_hi(0xffffffffu, __builtin_amdgcn_mbcnt_lo(0xffffffffu, 0u));
@@ -1007,11 +1020,107 @@ __device__ __forceinline__ uint32_t lane_id() {
 __device__ __forceinline__ float readlane_f(float v, int l) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
 }
+__device__ __forceinline__ double readlane_d(double v, int l) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    return __longlong_as_double(
+        (long long)(((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l) << 32) |
+                    (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l)));
+}
 
-template <bool kStats = false>
+// First photon of bucket hb (counted from table_off) and the one after its last.
+__device__ __forceinline__ uint2 bucket_range(const SppmDev &d, uint32_t hb, const uint32_t *__restrict__ start) {
+    uint2 r;
+    __builtin_memcpy(&r, start + d.table_off + hb, sizeof(r));
+    return r;
+}
+
+// Photons in the buckets of dc's cells.
+__device__ __forceinline__ uint32_t disc_load(const SppmDev &d, const Grid &gr, const DiscCells &dc,
+                                              const uint32_t *__restrict__ start) {
+    uint32_t load = 0u;
+#pragma unroll
+    for (int z = 0; z < 27; z += 9) {  // nine cells' bounds in flight
+        uint2 r[9];
+#pragma unroll
+        for (int j = 0; j < 9; ++j) {
+            r[j] = make_uint2(0u, 0u);
+            if ((dc.uniq >> (z + j)) & 1u) r[j] = bucket_range(d, disc_cell_bucket(gr, dc.c0, z + j), start);
+        }
+#pragma unroll
+        for (int j = 0; j < 9; ++j) load += r[j].y - r[j].x;
+    }
+    return load;
+}
+
+// The photons inside the disc of lane L's hit point that arrived from the eye's
+// side, by the whole wave: f(a, b) on the lane that holds the photon.
+template <typename F>
+__device__ __forceinline__ void wave_scan(const SppmDev &d, const Grid &gr, int L, float4 hx, float4 hn, double r2,
+                                          const DiscCells &dc, const uint32_t *__restrict__ start,
+                                          const float4 *__restrict__ sorted, F &&f) {
+    const uint32_t lane = lane_id();
+    const float4 xl = make_float4(readlane_f(hx.x, L), readlane_f(hx.y, L), readlane_f(hx.z, L), 0.0f);
+    const float4 nl = make_float4(readlane_f(hn.x, L), readlane_f(hn.y, L), readlane_f(hn.z, L), 0.0f);
+    const double r2l = readlane_d(r2, L);
+    const int32_t c0l[3] = {__builtin_amdgcn_readlane(dc.c0[0], L), __builtin_amdgcn_readlane(dc.c0[1], L),
+                            __builtin_amdgcn_readlane(dc.c0[2], L)};
+    const uint32_t uniql = (uint32_t)__builtin_amdgcn_readlane((int)dc.uniq, L);
+    // one bucket per lane; photon i of the run is photon i + shift of the bucket with excl <= i
+    uint2 range = make_uint2(0u, 0u);
+    if (lane < 27u && ((uniql >> lane) & 1u)) range = bucket_range(d, disc_cell_bucket(gr, c0l, (int)lane), start);
+    const uint32_t len = range.y - range.x;
+    uint32_t incl = len;
+#pragma unroll
+    for (int off = 1; off < 32; off <<= 1) {
+        const uint32_t v = __shfl_up(incl, off);
+        if ((int)lane >= off) incl += v;
+    }
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 26);
+    const uint32_t excl = incl - len, shift = range.x - excl;
+    const uint64_t filled = __ballot(len != 0u);
+    for (uint32_t base = 0; base < total; base += 64u * kScanLoads) {
+        uint32_t at[kScanLoads];
+#pragma unroll
+        for (int u = 0; u < kScanLoads; ++u) at[u] = 0u;
+        for (uint64_t m = filled; m != 0ull; m &= m - 1ull) {
+            const int b = __ffsll((unsigned long long)m) - 1;
+            const uint32_t e = (uint32_t)__builtin_amdgcn_readlane((int)excl, b),
+                           s = (uint32_t)__builtin_amdgcn_readlane((int)shift, b);
+#pragma unroll
+            for (int u = 0; u < kScanLoads; ++u) {
+                const uint32_t i = base + 64u * u + lane;
+                at[u] = i >= e ? i + s : at[u];
+            }
+        }
+        float4 a[kScanLoads], c[kScanLoads];
+        bool in[kScanLoads];
+#pragma unroll
+        for (int u = 0; u < kScanLoads; ++u) {
+            in[u] = base + 64u * u + lane < total;
+            a[u] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (in[u]) a[u] = sorted[2 * (size_t)at[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < kScanLoads; ++u) {
+            const float dx = a[u].x - xl.x, dy = a[u].y - xl.y, dz = a[u].z - xl.z;
+            const float d2 = (dx * dx + dy * dy) + dz * dz;
+            in[u] = in[u] && (double)d2 < r2l;
+            c[u] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (in[u]) c[u] = sorted[2 * (size_t)at[u] + 1];
+        }
+#pragma unroll
+        for (int u = 0; u < kScanLoads; ++u) {
+            const float c2 = (c[u].x * nl.x + c[u].y * nl.y) + c[u].z * nl.z;
+            if (in[u] && c2 < 0.0f) f(a[u], c[u]);
+        }
+    }
+}
+
+template <int kHits, bool kStats = false>
 __device__ __forceinline__ void gather_wave(const SppmDev &d, const Grid &gr, int64_t p,
                                             const uint32_t *__restrict__ start, const float4 *__restrict__ sorted) {
-    const bool in = p < d.P;
+    const uint32_t lane = lane_id();
+    const bool in = p < d.P && lane < (uint32_t)kHits;
     const float4 hn = in ? d.hp_nrm[p] : make_float4(0.0f, 0.0f, 0.0f, __int_as_float(-1));
     const bool valid = in && __float_as_int(hn.w) >= 0;
     float4 hx = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -1022,16 +1131,13 @@ __device__ __forceinline__ void gather_wave(const SppmDev &d, const Grid &gr, in
         hx = d.hp_pos[p];
         r2 = d.R2[p];
         dc = disc_cells(gr, hx, r2);
-        for (uint32_t m = dc.uniq; m != 0u; m &= m - 1u) {
-            const uint32_t hb = d.table_off + disc_cell_bucket(gr, dc.c0, __builtin_ctz(m));
-            load += start[hb + 1] - start[hb];
-        }
+        load = disc_load(d, gr, dc, start);
     }
     const double scale = d.scale;
     uint32_t M = 0u;
     unsigned long long F = 0ull;
     bool bad = false;
-    const bool coop = load >= kCoopMin;
+    const bool coop = load >= coop_min(kHits);
     if (valid && !coop) {
         const double wk = (double)hx.w;
         auto add = [&](const float4 &a, const float4 &) {
@@ -1041,39 +1147,16 @@ __device__ __forceinline__ void gather_wave(const SppmDev &d, const Grid &gr, in
         for (uint32_t m = dc.uniq; m != 0u; m &= m - 1u)
             photons_of_bucket(d, disc_cell_bucket(gr, dc.c0, __builtin_ctz(m)), hx, hn, r2, start, sorted, add);
     }
-    const uint32_t lane = lane_id();
     for (uint64_t todo = __ballot(coop); todo != 0ull; todo &= todo - 1ull) {
         const int L = __ffsll((unsigned long long)todo) - 1;
-        const float4 xl = make_float4(readlane_f(hx.x, L), readlane_f(hx.y, L), readlane_f(hx.z, L), readlane_f(hx.w, L));
-        const float4 nl = make_float4(readlane_f(hn.x, L), readlane_f(hn.y, L), readlane_f(hn.z, L), 0.0f);
-        const unsigned long long r2b = (unsigned long long)__double_as_longlong(r2);
-        const double r2l = __longlong_as_double(
-            (long long)(((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(r2b >> 32), L) << 32) |
-                        (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)r2b, L)));
-        const int32_t c0l[3] = {__builtin_amdgcn_readlane(dc.c0[0], L), __builtin_amdgcn_readlane(dc.c0[1], L),
-                                __builtin_amdgcn_readlane(dc.c0[2], L)};
-        const uint32_t uniql = (uint32_t)__builtin_amdgcn_readlane((int)dc.uniq, L);
-        const double wk = (double)xl.w;
+        const double wk = (double)readlane_f(hx.w, L);
         uint32_t m = 0u;
         unsigned long long f = 0ull;
         bool fbad = false;
-        for (uint32_t bits = uniql; bits != 0u; bits &= bits - 1u) {
-            const uint32_t hb = d.table_off + disc_cell_bucket(gr, c0l, __builtin_ctz(bits));
-            const uint32_t q1 = start[hb + 1];
-            for (uint32_t q = start[hb] + lane; q < q1; q += 64u) {
-                const float4 a = sorted[2 * (size_t)q];
-                const float dx = a.x - xl.x, dy = a.y - xl.y, dz = a.z - xl.z;
-                const float d2 = (dx * dx + dy * dy) + dz * dz;
-                if ((double)d2 < r2l) {
-                    const float4 b = sorted[2 * (size_t)q + 1];
-                    const float c2 = (b.x * nl.x + b.y * nl.y) + b.z * nl.z;
-                    if (c2 < 0.0f) {
-                        m++;
-                        flux_add(f, (wk * (double)a.w) * scale, 1u, fbad);
-                    }
-                }
-            }
-        }
+        wave_scan(d, gr, L, hx, hn, r2, dc, start, sorted, [&](const float4 &a, const float4 &) {
+            m++;
+            flux_add(f, (wk * (double)a.w) * scale, 1u, fbad);
+        });
         for (int off = 32; off > 0; off >>= 1) {
             m += __shfl_xor(m, off);
             const unsigned long long s = f + __shfl_xor(f, off);
