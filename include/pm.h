@@ -399,7 +399,9 @@ enum { PM_GATHER_EXACT = 0, PM_GATHER_STOCHASTIC = 1 };
  * second launch continues them.  A path that reflects inside a glass object
  * can run to max_photon_bounces, so the last paths of a pass leave the device
  * almost idle: on a pipelined handle the second launch runs on a stream of
- * its own, beside the next iteration's first launch. */
+ * its own, beside the next iteration's first launch.  AUTO runs a pass of few
+ * paths (up to 64 for each wavefront the device holds) in one launch instead,
+ * the paths spread evenly over the wavefronts. */
 enum {
     PM_PHOTON_AUTO = 0,
     PM_PHOTON_PER_PATH = 1,

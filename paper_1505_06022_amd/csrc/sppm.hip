@@ -20,6 +20,10 @@ using namespace pmd;
 #define PM_STACK()                                           \
     __shared__ uint32_t wide_stack[kBlock / 64][kStackWords]; \
     uint32_t *const stk = wide_stack[threadIdx.x >> 6]
+// The same for the photons on their way to the store.
+#define PM_SINK()                                   \
+    __shared__ float4 photon_buf[kBlock / 64][kSinkWords]; \
+    const PhotonSink sink{photon_buf[threadIdx.x >> 6], 0u}
 
 __global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_eye(SppmDev d, uint32_t k, int32_t accumulate_D) {
     int64_t p = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
@@ -37,37 +41,50 @@ __global__ __launch_bounds__(kBlock) void k_eye_stats(SppmDev d, uint32_t k, int
     wave_stats_flush(d.stats + kStatEyePaths, ls);
 }
 
+// The wave's place in the grid, each XCD owning a contiguous range.
+__device__ __forceinline__ int64_t wave_index() {
+    return (int64_t)xcd_block(blockIdx.x, gridDim.x) * (kBlock / 64) + (threadIdx.x >> 6);
+}
+
+// One path per lane, the first per_wave lanes of each wave.
 template <bool kRecord>
-__global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon(SppmDev d, uint32_t k, uint16_t *__restrict__ mat_tab,
-                                                   long long *__restrict__ adj_tab) {
-    uint32_t n = xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
+__global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon(SppmDev d, uint32_t k, uint32_t per_wave,
+                                                               uint16_t *__restrict__ mat_tab,
+                                                               long long *__restrict__ adj_tab) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const int64_t n = wave_index() * per_wave + lane;
     PM_STACK();
-    photon_elem<kRecord>(d, k, n, n < d.n_paths, mat_tab, adj_tab, stk);
+    PM_SINK();
+    photon_elem<kRecord>(d, k, (uint32_t)n, lane < per_wave && n < d.n_paths, mat_tab, adj_tab, stk, sink);
 }
 
 // Persistent photon lanes with path regeneration.
 __global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_regen(SppmDev d, uint32_t k) {
     PM_STACK();
-    photon_regen_loop(d, k, d.refill, stk);
+    PM_SINK();
+    photon_regen_loop(d, k, d.refill, stk, sink);
 }
 
 __global__ __launch_bounds__(kBlock) void k_photon_regen_stats(SppmDev d, uint32_t k) {
-    photon_regen_loop<false, true>(d, k, d.refill, nullptr);
+    PM_SINK();
+    photon_regen_loop<false, true>(d, k, d.refill, nullptr, sink);
 }
 
 // Two-phase photon pass (PM_PHOTON_TWO_PHASE): regeneration that sets the
 // last paths of each wavefront aside once the path counter has run out, then
-// regeneration over the paths set aside.
+// a launch over the paths set aside.
 template <bool kStats>
 __global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_head(SppmDev d, uint32_t k, PathQueue q) {
     PM_STACK();
-    photon_regen_loop<false, kStats, true, false>(d, k, d.refill, stk, nullptr, nullptr, q);
+    PM_SINK();
+    photon_regen_loop<false, kStats, true>(d, k, d.refill, stk, sink, nullptr, nullptr, q);
 }
 
 template <bool kStats>
-__global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_tail(SppmDev d, uint32_t k, PathQueue q) {
+__global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_tail(SppmDev d, PathQueue q) {
     PM_STACK();
-    photon_regen_loop<false, kStats, false, true>(d, k, d.refill, stk, nullptr, nullptr, q);
+    PM_SINK();
+    photon_queue_loop<false, kStats>(d, q, (uint32_t)wave_index(), gridDim.x * (kBlock / 64), stk, sink, nullptr, nullptr);
 }
 
 // The same two launches, recording each path's stored-photon materials for
@@ -76,14 +93,16 @@ __global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_head_rec(SppmDe
                                                             uint16_t *__restrict__ mat_tab,
                                                             long long *__restrict__ adj_tab) {
     PM_STACK();
-    photon_regen_loop<true, false, true, false>(d, k, d.refill, stk, mat_tab, adj_tab, q);
+    PM_SINK();
+    photon_regen_loop<true, false, true>(d, k, d.refill, stk, sink, mat_tab, adj_tab, q);
 }
 
-__global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_tail_rec(SppmDev d, uint32_t k, PathQueue q,
+__global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_tail_rec(SppmDev d, PathQueue q,
                                                             uint16_t *__restrict__ mat_tab,
                                                             long long *__restrict__ adj_tab) {
     PM_STACK();
-    photon_regen_loop<true, false, false, true>(d, k, d.refill, stk, mat_tab, adj_tab, q);
+    PM_SINK();
+    photon_queue_loop<true, false>(d, q, (uint32_t)wave_index(), gridDim.x * (kBlock / 64), stk, sink, mat_tab, adj_tab);
 }
 
 // Regeneration from a queue of started paths in LDS (PM_PHOTON_POOL): each
@@ -107,14 +126,16 @@ __global__ __launch_bounds__(kBlock) void k_photon_stream_stats(SppmDev d, uint3
 __global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_regen_rec(SppmDev d, uint32_t k, uint16_t *__restrict__ mat_tab,
                                                              long long *__restrict__ adj_tab) {
     PM_STACK();
-    photon_regen_loop<true>(d, k, d.refill, stk, mat_tab, adj_tab);
+    PM_SINK();
+    photon_regen_loop<true>(d, k, d.refill, stk, sink, mat_tab, adj_tab);
 }
 
 // One pass of the one-bounce-per-pass schedule; the grid covers the slots
 // with the same workgroup-to-slot map in every pass.
 __global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_pass(SppmDev d, uint32_t k, PassSlots ps) {
     PM_STACK();
-    photon_pass_elem(d, k, ps, xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x, stk);
+    PM_SINK();
+    photon_pass_elem(d, k, ps, xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x, stk, sink);
 }
 
 // Paths no pass started, before the drain adds the paths still in flight.
@@ -124,14 +145,16 @@ __global__ void k_pass_tally(SppmDev d) {
 
 __global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_drain(SppmDev d, uint32_t k, PassSlots ps) {
     PM_STACK();
-    photon_drain_elem(d, k, ps, xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x, stk);
+    PM_SINK();
+    photon_drain_elem(d, k, ps, xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x, stk, sink);
 }
 
-// Start of a photon pass: clear its store's photon count and the path counter.
-__global__ void k_photon_begin(SppmDev d) {
+// Start of a photon pass: clear its store's photon count; handed: paths that
+// are handed out from the start (all, in a pass without the path counter).
+__global__ void k_photon_begin(SppmDev d, uint32_t handed) {
     if (threadIdx.x == 0) {
         d.counters[0] = 0u;
-        d.counters[2] = 0u;
+        d.counters[2] = handed;
     }
 }
 
@@ -488,6 +511,10 @@ __global__ __launch_bounds__(kMaxAdjMat) void k_collect_grad(const double *__res
 }
 
 inline uint32_t blocks_for(int64_t n) { return (uint32_t)((n + kBlock - 1) / kBlock); }
+// Workgroups for n elements, per_wave to a wave.
+inline uint32_t blocks_for_waves(int64_t n, uint32_t per_wave) {
+    return (uint32_t)((n + (int64_t)per_wave * (kBlock / 64) - 1) / ((int64_t)per_wave * (kBlock / 64)));
+}
 
 // host float3 helpers with the same evaluation order as the device
 struct H3 {
@@ -594,6 +621,15 @@ int sppm_validate(const pm_scene_desc *d, const pm_sppm_params *p) {
         return set_error("the adjoint supports images below 2^24 pixels"), PM_ERR_ARG;
     return PM_OK;
 }
+
+// A default photon pass of at most this many paths for each wave the device
+// holds (4,096) runs in one launch that spreads them evenly over the waves
+// (k_photon), the passes of even and odd iterations on two streams.  It ends
+// with its longest path either way, but the two launches of full waves came one
+// after another for every iteration.  Calls, two launches and one (ms): 8
+// iterations of 100,003 paths 6.6 and 4.6, 4 of 2^18 paths 2.4 and 2.0.  Beyond
+// 64 paths a wave the regenerating launch fills its lanes better.
+constexpr uint32_t kThinPaths = 64;
 
 // The photon schedule a handle runs: the default is the two-phase pass on
 // single-scene handles and regeneration for a batch member (whose photon
@@ -849,9 +885,18 @@ int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t 
         PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_tail_rec, kBlock, 0));
         s->tail_grid_rec = (uint32_t)std::max(1, cus * std::max(1, per_cu));
     }
+    {
+        const int64_t waves = (int64_t)s->head_grid * (kBlock / 64);
+        auto spread = [&](int64_t n) {
+            return (uint32_t)std::max<int64_t>((n + waves - 1) / waves, (int64_t)kMinPathsPerWave);
+        };
+        if (own_grid && p->photon_kernel == PM_PHOTON_AUTO && !(p->profile & PM_PROFILE_COUNT) &&
+            spread(p->n_photons) <= kThinPaths)
+            s->thin = spread(p->n_photons);
+    }
     if (dv.photon_kernel == PM_PHOTON_TWO_PHASE) {
         // per store parity: a queue slot for every lane of the first launch
-        // (each parks at most one path), then the queue's two counters
+        // (each parks at most one path), then the queue's count
         const uint32_t S = (uint32_t)std::min<int64_t>(
             p->n_photons, (int64_t)std::max(s->head_grid, s->head_grid_rec) * kBlock);
         const size_t per = (size_t)56 * S + 256;
@@ -927,10 +972,16 @@ static SppmDev iteration_view(const pm_sppm *s, uint32_t k) {
 // The pass has ended once tq's work enqueued so far is done.
 static int enqueue_photon(pm_sppm *s, const SppmDev &dk, uint32_t k, bool count, hipStream_t q, hipStream_t tq) {
     const uint32_t np = (uint32_t)s->prm.n_photons;
-    hipLaunchKernelGGL(k_photon_begin, dim3(1), dim3(64), 0, q, dk);
+    hipLaunchKernelGGL(k_photon_begin, dim3(1), dim3(64), 0, q, dk, s->thin ? np : 0u);
+    if (s->thin) {
+        hipLaunchKernelGGL(k_photon<false>, dim3(blocks_for_waves(np, s->thin)), dim3(kBlock), 0, q, dk, k, s->thin,
+                           (uint16_t *)nullptr, (long long *)nullptr);
+        PM_HIP(hipGetLastError());
+        return PM_OK;
+    }
     if (dk.photon_kernel == PM_PHOTON_TWO_PHASE) {
         const PathQueue &pq = s->queue[s->store2 ? (k & 1u) : 0u];
-        hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, q, pq.cnt, 2u, 0u);
+        hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, q, pq.cnt, 1u, 0u);
         if (count)
             hipLaunchKernelGGL(k_photon_head<true>, dim3(s->head_grid), dim3(kBlock), 0, q, dk, k, pq);
         else
@@ -940,9 +991,9 @@ static int enqueue_photon(pm_sppm *s, const SppmDev &dk, uint32_t k, bool count,
             PM_HIP(hipStreamWaitEvent(tq, s->ev_head[k & 1u], 0));
         }
         if (count)
-            hipLaunchKernelGGL(k_photon_tail<true>, dim3(s->tail_grid), dim3(kBlock), 0, tq, dk, k, pq);
+            hipLaunchKernelGGL(k_photon_tail<true>, dim3(s->tail_grid), dim3(kBlock), 0, tq, dk, pq);
         else
-            hipLaunchKernelGGL(k_photon_tail<false>, dim3(s->tail_grid), dim3(kBlock), 0, tq, dk, k, pq);
+            hipLaunchKernelGGL(k_photon_tail<false>, dim3(s->tail_grid), dim3(kBlock), 0, tq, dk, pq);
     } else if (dk.photon_kernel == PM_PHOTON_RAY_REGEN) {
         if (count)
             hipLaunchKernelGGL(k_photon_stream_stats, dim3(s->stream_grid), dim3(kBlock), 0, q, dk, k);
@@ -967,7 +1018,7 @@ static int enqueue_photon(pm_sppm *s, const SppmDev &dk, uint32_t k, bool count,
         hipLaunchKernelGGL(k_pass_tally, dim3(1), dim3(64), 0, q, dk);
         hipLaunchKernelGGL(k_photon_drain, dim3(blocks_for(ps.S)), dim3(kBlock), 0, q, dk, k, ps);
     } else {
-        hipLaunchKernelGGL(k_photon<false>, dim3(blocks_for(np)), dim3(kBlock), 0, q, dk, k, (uint16_t *)nullptr,
+        hipLaunchKernelGGL(k_photon<false>, dim3(blocks_for(np)), dim3(kBlock), 0, q, dk, k, 64u, (uint16_t *)nullptr,
                            (long long *)nullptr);
     }
     PM_HIP(hipGetLastError());
@@ -1000,6 +1051,10 @@ int sppm_iterate(pm_sppm *s, int32_t n_iter, hipStream_t st) {
     // the two-phase pass's second launch runs on its own stream, so that the
     // next pass's first launch can start beside it
     hipStream_t tq = s->tails ? s->tails : s->phs;
+    // a pass in one launch of few paths a wave: the streams of the two
+    // launches take the passes of even and odd iterations
+    auto head_stream = [&](uint32_t kk) { return s->thin && (kk & 1u) ? tq : s->phs; };
+    auto tail_stream = [&](uint32_t kk) { return s->thin ? head_stream(kk) : tq; };
     auto eye_pass = [&](const SppmDev &dv, uint32_t kk, hipStream_t q) {
         if (count)
             hipLaunchKernelGGL(k_eye_stats, dim3(blocks_for(s->P)), dim3(kBlock), 0, q, dv, kk, 1);
@@ -1010,9 +1065,10 @@ int sppm_iterate(pm_sppm *s, int32_t n_iter, hipStream_t st) {
         // photon pass and eye pass of the first iteration, each on its stream
         PM_HIP(hipEventRecord(s->ev_fork, st));
         PM_HIP(hipStreamWaitEvent(s->phs, s->ev_fork, 0));
+        if (s->thin) PM_HIP(hipStreamWaitEvent(tq, s->ev_fork, 0));
         PM_HIP(hipStreamWaitEvent(s->side, s->ev_fork, 0));
-        if ((rc = enqueue_photon(s, iteration_view(s, k0), k0, count, s->phs, tq))) return rc;
-        PM_HIP(hipEventRecord(s->ev_ph[k0 & 1u], tq));
+        if ((rc = enqueue_photon(s, iteration_view(s, k0), k0, count, head_stream(k0), tail_stream(k0)))) return rc;
+        PM_HIP(hipEventRecord(s->ev_ph[k0 & 1u], tail_stream(k0)));
         eye_pass(iteration_view(s, k0), k0, s->side);
         PM_HIP(hipEventRecord(s->ev_eye[k0 & 1u], s->side));
     }
@@ -1021,9 +1077,10 @@ int sppm_iterate(pm_sppm *s, int32_t n_iter, hipStream_t st) {
         const SppmDev dk = iteration_view(s, k);
         if (pipe && it + 1 < n_iter) {
             // the next photon pass refills the store (and queue) that the scatter of k - 1 read
-            if (it >= 1) PM_HIP(hipStreamWaitEvent(s->phs, s->ev_scat[(k + 1u) & 1u], 0));
-            if ((rc = enqueue_photon(s, iteration_view(s, k + 1u), k + 1u, count, s->phs, tq))) return rc;
-            PM_HIP(hipEventRecord(s->ev_ph[(k + 1u) & 1u], tq));
+            hipStream_t hq = head_stream(k + 1u);
+            if (it >= 1) PM_HIP(hipStreamWaitEvent(hq, s->ev_scat[(k + 1u) & 1u], 0));
+            if ((rc = enqueue_photon(s, iteration_view(s, k + 1u), k + 1u, count, hq, tail_stream(k + 1u)))) return rc;
+            PM_HIP(hipEventRecord(s->ev_ph[(k + 1u) & 1u], tail_stream(k + 1u)));
             // the next eye pass refills the hit points that the update of k - 1 read
             if (it >= 1) PM_HIP(hipStreamWaitEvent(s->side, s->ev_upd[(k + 1u) & 1u], 0));
             eye_pass(iteration_view(s, k + 1u), k + 1u, s->side);
@@ -1190,19 +1247,23 @@ static int adjoint_overlapped(pm_sppm *s, const float *g, hipStream_t st) {
     // its first launch there and the second on the tail stream, beside the
     // first launch of the next replay; the flux maximum follows the pass
     const bool two = s->dev.photon_kernel == PM_PHOTON_TWO_PHASE && s->tails;
-    hipStream_t tq = two ? s->tails : s->phs;
+    hipStream_t tails = two ? s->tails : s->phs;
     auto replay = [&](uint32_t k) -> int {
         const SppmDev dk = iteration_view(s, k);
-        hipLaunchKernelGGL(k_photon_begin, dim3(1), dim3(64), 0, s->phs, dk);
-        hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s->phs, (uint32_t *)(max_of(k) + 1), 2u, 0u);
-        if (two) {
+        hipStream_t hq = s->thin && (k & 1u) ? s->tails : s->phs, tq = s->thin ? hq : tails;
+        hipLaunchKernelGGL(k_photon_begin, dim3(1), dim3(64), 0, hq, dk, s->thin ? np : 0u);
+        hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, hq, (uint32_t *)(max_of(k) + 1), 2u, 0u);
+        if (s->thin) {
+            hipLaunchKernelGGL(k_photon<true>, dim3(blocks_for_waves(np, s->thin)), dim3(kBlock), 0, hq, dk, k, s->thin,
+                               mat_of(k), tab_of(k));
+        } else if (two) {
             const PathQueue &pq = s->queue[k & 1u];
-            hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s->phs, pq.cnt, 2u, 0u);
+            hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s->phs, pq.cnt, 1u, 0u);
             hipLaunchKernelGGL(k_photon_head_rec, dim3(s->head_grid_rec), dim3(kBlock), 0, s->phs, dk, k, pq,
                                mat_of(k), tab_of(k));
             PM_HIP(hipEventRecord(s->ev_head[k & 1u], s->phs));
             PM_HIP(hipStreamWaitEvent(tq, s->ev_head[k & 1u], 0));
-            hipLaunchKernelGGL(k_photon_tail_rec, dim3(s->tail_grid_rec), dim3(kBlock), 0, tq, dk, k, pq, mat_of(k),
+            hipLaunchKernelGGL(k_photon_tail_rec, dim3(s->tail_grid_rec), dim3(kBlock), 0, tq, dk, pq, mat_of(k),
                                tab_of(k));
         } else {
             hipLaunchKernelGGL(k_photon_regen_rec, dim3(s->regen_grid_rec), dim3(kBlock), 0, s->phs, dk, k,
@@ -1232,6 +1293,7 @@ static int adjoint_overlapped(pm_sppm *s, const float *g, hipStream_t st) {
     };
     PM_HIP(hipEventRecord(s->ev_fork, st));
     PM_HIP(hipStreamWaitEvent(s->phs, s->ev_fork, 0));
+    if (s->thin) PM_HIP(hipStreamWaitEvent(s->tails, s->ev_fork, 0));
     PM_HIP(hipStreamWaitEvent(s->side, s->ev_fork, 0));
     int rc = replay(0);
     if (rc) return rc;
@@ -1241,7 +1303,8 @@ static int adjoint_overlapped(pm_sppm *s, const float *g, hipStream_t st) {
         const double *R2k = s->R2_hist + (size_t)k * s->P;
         if (k + 1 < K) {
             // the replay of k + 1 reuses the store and tables that iteration k - 1 read
-            if (k >= 1) PM_HIP(hipStreamWaitEvent(s->phs, s->ev_scat[(k + 1u) & 1u], 0));
+            if (k >= 1)
+                PM_HIP(hipStreamWaitEvent(s->thin && (k + 1u) & 1u ? s->tails : s->phs, s->ev_scat[(k + 1u) & 1u], 0));
             if ((rc = replay(k + 1))) return rc;
             // and its eye pass the hit points, R_max and maxima that the range query of k - 1 read
             if (k >= 1) PM_HIP(hipStreamWaitEvent(s->side, s->ev_upd[(k + 1u) & 1u], 0));

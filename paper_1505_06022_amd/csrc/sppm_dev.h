@@ -214,6 +214,70 @@ __device__ __forceinline__ uint32_t wave_append(uint32_t *counter) {
     return base + lane_rank;
 }
 
+// Photons of a wave on their way to the store.  Every photon takes a slot from
+// one counter, and returning atomics on one address leave the device one every
+// 6 ns or so: with one per wave and bounce, 75,000 of them bound a pass of
+// 2^20 paths.  A wave therefore collects its photons in LDS (buf, 2
+// kPhotonBuf float4 words) and takes slots for all of them at once when the
+// next bounce might not fit.  Without buf (NULL) each bounce takes its own.
+// The photon pass alone, without and with buf: 0.135 and 0.105 ms for 2^14
+// paths in the box scene, 1.345 and 1.232 ms for 2^20 in the 250k scene.
+constexpr uint32_t kPhotonBuf = 112;
+constexpr int kSinkWords = 2 * (int)kPhotonBuf;  // float4 words of LDS per wave
+
+struct PhotonSink {
+    float4 *buf;
+    uint32_t n;  // photons in buf (wave-uniform)
+};
+
+// Called by all lanes of a wave.
+__device__ __forceinline__ void sink_flush(const SppmDev &d, PhotonSink &sink) {
+    if (sink.buf == nullptr || sink.n == 0u) return;
+    // the lanes read what other lanes of the wave wrote
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t lane = lane_index();
+    uint32_t base = 0u;
+    if (lane == 0u) base = atomicAdd(&d.counters[0], sink.n);
+    base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+    for (uint32_t i = lane; i < sink.n; i += 64u) {
+        const uint32_t slot = base + i;
+        if (slot < d.cap) {
+            d.store[2 * (size_t)slot] = sink.buf[2u * i];
+            d.store[2 * (size_t)slot + 1] = sink.buf[2u * i + 1u];
+        } else {
+            atomicOr(&d.counters[1], 1u);
+        }
+    }
+    sink.n = 0u;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Room for one photon of each of the wave's `live` paths (wave-uniform count).
+__device__ __forceinline__ void sink_room(const SppmDev &d, PhotonSink &sink, uint32_t live) {
+    if (sink.buf != nullptr && sink.n + live > kPhotonBuf) sink_flush(d, sink);
+}
+
+// The photon of each lane that calls it.
+__device__ __forceinline__ void sink_put(const SppmDev &d, const PhotonSink &sink, float4 a, float4 b) {
+    if (sink.buf != nullptr) {
+        const uint64_t mask = __ballot(1);
+        const uint32_t i = sink.n + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+        sink.buf[2u * i] = a;
+        sink.buf[2u * i + 1u] = b;
+        return;
+    }
+    const uint32_t slot = wave_append(&d.counters[0]);
+    if (slot < d.cap) {
+        d.store[2 * (size_t)slot] = a;
+        d.store[2 * (size_t)slot + 1] = b;
+    } else {
+        atomicOr(&d.counters[1], 1u);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Photon path n (Sec. 2, Sec. 3.3): emitter by power, point by folding,
 // cosine direction, then bounces until a miss, an absorbing surface, Russian
@@ -271,24 +335,28 @@ __device__ __forceinline__ bool photon_emit(const SppmDev &d, uint32_t k, uint32
 template <bool kRecord, bool kStats>
 __device__ __forceinline__ bool photon_shade(const SppmDev &d, PhotonPath &P, int32_t h, float t, uint32_t kp,
                                              uint16_t *__restrict__ mat_tab, long long *__restrict__ adj_tab,
-                                             LaneStats *ls);
+                                             const PhotonSink &sink, bool &stored, LaneStats *ls);
 
 // Called by all lanes of a wave; live: this lane has a path.
 template <bool kRecord, bool kStats = false>
 __device__ __forceinline__ bool photon_bounce(const SppmDev &d, PhotonPath &P, bool live,
                                               uint16_t *__restrict__ mat_tab, long long *__restrict__ adj_tab,
-                                              uint32_t *stk, LaneStats *ls = nullptr) {
+                                              uint32_t *stk, PhotonSink &sink, LaneStats *ls = nullptr) {
     const SceneDev &sc = d.sc;
     float t;
     uint32_t kp;
     TraceStats st{0u, 0u};
+    sink_room(d, sink, (uint32_t)__popcll(__ballot(live)));
     const int32_t h = wave_closest_hit<kStats, true>(d, stk, live, P.org, P.dir, sc.eps, P.excl, t, kp, st);
     if (kStats && live) {
         ls->rays++;
         ls->boxes += st.boxes;
         ls->tris += st.tris;
     }
-    return live && photon_shade<kRecord, kStats>(d, P, h, t, kp, mat_tab, adj_tab, ls);
+    bool stored = false;
+    live = live && photon_shade<kRecord, kStats>(d, P, h, t, kp, mat_tab, adj_tab, sink, stored, ls);
+    if (sink.buf != nullptr) sink.n += (uint32_t)__popcll(__ballot(stored));
+    return live;
 }
 
 // The rest of a bounce once the closest hit (h, t, kp) of the ray from P.org
@@ -298,7 +366,7 @@ __device__ __forceinline__ bool photon_bounce(const SppmDev &d, PhotonPath &P, b
 template <bool kRecord, bool kStats>
 __device__ __forceinline__ bool photon_shade(const SppmDev &d, PhotonPath &P, int32_t h, float t, uint32_t kp,
                                              uint16_t *__restrict__ mat_tab, long long *__restrict__ adj_tab,
-                                             LaneStats *ls) {
+                                             const PhotonSink &sink, bool &stored, LaneStats *ls) {
     const SceneDev &sc = d.sc;
     const int32_t mb = d.max_bounces;
     const int b = P.b;
@@ -321,13 +389,9 @@ __device__ __forceinline__ bool photon_shade(const SppmDev &d, PhotonPath &P, in
             adj_tab[(size_t)P.n * mb + b] = 0;
         }
         if (kStats) ls->stored++;
-        uint32_t slot = wave_append(&d.counters[0]);
-        if (slot < d.cap) {
-            d.store[2 * (size_t)slot] = make_float4(x.x, x.y, x.z, P.phi);
-            d.store[2 * (size_t)slot + 1] = make_float4(P.dir.x, P.dir.y, P.dir.z, __uint_as_float((P.n << 5) | (uint32_t)b));
-        } else {
-            atomicOr(&d.counters[1], 1u);
-        }
+        stored = true;
+        sink_put(d, sink, make_float4(x.x, x.y, x.z, P.phi),
+                 make_float4(P.dir.x, P.dir.y, P.dir.z, __uint_as_float((P.n << 5) | (uint32_t)b)));
         float u = rng_next(P.g);
         float q = sc.mat_q[m];
         if (!(u < q)) return false;
@@ -355,10 +419,11 @@ __device__ __forceinline__ void photon_finish(const SppmDev &d, const PhotonPath
 template <bool kRecord>
 __device__ __forceinline__ void photon_elem(const SppmDev &d, uint32_t k, uint32_t n, bool active,
                                             uint16_t *__restrict__ mat_tab, long long *__restrict__ adj_tab,
-                                            uint32_t *stk) {
+                                            uint32_t *stk, PhotonSink sink) {
     PhotonPath P{};
     bool live = active && photon_emit(d, k, n, P);
-    while (__ballot(live) != 0ull) live = photon_bounce<kRecord>(d, P, live, mat_tab, adj_tab, stk);
+    while (__ballot(live) != 0ull) live = photon_bounce<kRecord>(d, P, live, mat_tab, adj_tab, stk, sink);
+    sink_flush(d, sink);
     if (active) photon_finish<kRecord>(d, P, mat_tab);
 }
 
@@ -410,77 +475,110 @@ __device__ __forceinline__ void slot_store(const PassSlots &ps, uint32_t s, cons
 // paths, so the first launch of the next iteration can start beside it.
 // Each path consumes its random stream as in photon_elem, so the photons are
 // the same.
-#ifndef PM_PARK_LIVE
-#define PM_PARK_LIVE 32
-#endif
-constexpr uint32_t kParkLive = PM_PARK_LIVE;
+constexpr uint32_t kParkLive = 32;
 
 struct PathQueue {
     PassSlots s;    // s.S slots: at least the first launch's lanes
-    uint32_t *cnt;  // [0] paths queued, [1] queued paths taken by the second launch
+    uint32_t *cnt;  // paths queued
 };
 
+// Paths that a wave gets at least when a pass has too few of them to fill the
+// device with full waves: 16, one for each quad of the wide walk (with 4 the
+// box scene's 2^14 paths take 0.235 instead of 0.138 ms: more waves, and so more
+// atomics on the store's counter).
+constexpr uint32_t kMinPathsPerWave = 16;
+
 // Photon paths with regeneration (Sec. 3.3): persistent lanes trace one bounce
-// per step; a lane whose path ended takes the next path index from the
-// counter d.counters[2] once at least `refill` lanes of its wave are idle (or
-// all are).  Every step advances each live path by one bounce and paths are
+// per step; a lane whose path ended takes the next path index once at least
+// `refill` lanes of its wave are idle (or all are).  A wave takes kPathGrab
+// indices at a time from the counter d.counters[2] (the same one-address limit
+// as the store's: a refill of 32 lanes each took 32,000 atomics a pass).  Every step advances each live path by one bounce and paths are
 // bounded by max_bounces, so every wave exits once the counter passes n_paths.
 // Called by every lane of a wave; the wave's lanes must share one scene.
 // kRecord (adjoint replay): paths also write their rows of mat_tab / adj_tab
 // as in photon_elem.  kPark (first launch of the two-phase pass): once the
 // path counter has run out and at most kParkLive lanes hold a path, those
-// paths go to the queue and the wave stops.  kQueue (second launch): the
-// lanes take the queued paths (counted by queue.cnt[1]) instead of starting
-// new ones.
-template <bool kRecord = false, bool kStats = false, bool kPark = false, bool kQueue = false>
+// paths go to the queue and the wave stops.
+constexpr uint32_t kPathGrab = 64;
+
+template <bool kRecord = false, bool kStats = false, bool kPark = false>
 __device__ __forceinline__ void photon_regen_loop(const SppmDev &d, uint32_t k, uint32_t refill, uint32_t *stk,
-                                                  uint16_t *__restrict__ mat_tab = nullptr,
+                                                  PhotonSink sink, uint16_t *__restrict__ mat_tab = nullptr,
                                                   long long *__restrict__ adj_tab = nullptr,
                                                   PathQueue queue = PathQueue{}) {
     PhotonPath P{};
     LaneStats ls;
-    bool live = false, exhausted = false;
-    uint32_t n_queued = 0u;
-    if constexpr (kQueue) n_queued = queue.cnt[0];
+    bool live = false;
+    uint32_t next = 0u, end = 0u;  // path indices taken and not started (wave-uniform)
+    bool out = false;              // the counter has run out (wave-uniform)
     for (;;) {
-        bool idle = !live && !exhausted;
-        uint64_t idle_mask = __ballot(idle);
-        uint64_t live_mask = __ballot(live);
-        if (idle_mask != 0ull && (live_mask == 0ull || (uint32_t)__popcll(idle_mask) >= refill)) {
-            uint32_t n = wave_fetch_add(kQueue ? &queue.cnt[1] : &d.counters[2], idle_mask, idle);
-            if (idle) {
-                if constexpr (kQueue) {
-                    if (n < n_queued) {
-                        live = slot_load(queue.s, n, P);
-                        // recording: a live path's last written bounce is the one before its next
-                        if (kRecord) P.last = P.b - 1;
-                    } else {
-                        exhausted = true;
-                    }
-                } else if (n < d.n_paths) {
+        const uint64_t idle_mask = __ballot(!live);
+        uint64_t live_mask = ~idle_mask;
+        if (!out && idle_mask != 0ull && (live_mask == 0ull || (uint32_t)__popcll(idle_mask) >= refill)) {
+            if (next == end) {
+                uint32_t base = 0u;
+                if (lane_index() == 0u) base = atomicAdd(&d.counters[2], kPathGrab);
+                next = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+                end = min(next + kPathGrab, d.n_paths);
+                out = next >= end;
+            }
+            if (!out) {
+                const uint32_t n = next + __builtin_amdgcn_mbcnt_hi((uint32_t)(idle_mask >> 32),
+                                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)idle_mask, 0u));
+                if (!live && n < end) {
                     live = photon_emit(d, k, n, P);
                     if (kStats) ls.paths++;
                     if (kRecord && !live) photon_finish<true>(d, P, mat_tab);
-                } else {
-                    exhausted = true;
                 }
+                next = min(next + (uint32_t)__popcll(idle_mask), end);
+                live_mask = __ballot(live);
             }
-            live_mask = __ballot(live);
         }
-        if (live_mask == 0ull && __ballot(!exhausted) == 0ull) break;
+        if (live_mask == 0ull) {
+            if (out) break;
+            continue;
+        }
         if constexpr (kPark) {
-            if (__ballot(exhausted) != 0ull && (uint32_t)__popcll(live_mask) <= kParkLive) {
-                if (live_mask != 0ull) {
-                    const uint32_t v = wave_fetch_add(&queue.cnt[0], live_mask, live);
-                    if (live) slot_store(queue.s, v, P, true);
-                }
+            if (out && (uint32_t)__popcll(live_mask) <= kParkLive) {
+                const uint32_t v = wave_fetch_add(queue.cnt, live_mask, live);
+                if (live) slot_store(queue.s, v, P, true);
                 break;
             }
         }
         const bool was_live = live;
-        live = photon_bounce<kRecord, kStats>(d, P, live, mat_tab, adj_tab, stk, &ls);
+        live = photon_bounce<kRecord, kStats>(d, P, live, mat_tab, adj_tab, stk, sink, &ls);
         if (kRecord && was_live && !live) photon_finish<true>(d, P, mat_tab);
     }
+    sink_flush(d, sink);
+    if (kStats) {
+        wave_stats_flush(d.stats + kStatPhotonPaths, ls);
+        wave_stat_add(d.stats + kStatPhotonStored, ls.stored);
+    }
+}
+
+// Second launch of the two-phase pass: the queued paths, spread evenly over
+// all waves of the launch (a bounce waits for the wave's longest walk, so few
+// paths a wave end sooner than 64), each traced to its end.  Called by all
+// lanes of a wave; wave: its index among `waves`.
+template <bool kRecord, bool kStats>
+__device__ __forceinline__ void photon_queue_loop(const SppmDev &d, PathQueue queue, uint32_t wave, uint32_t waves,
+                                                  uint32_t *stk, PhotonSink sink, uint16_t *__restrict__ mat_tab,
+                                                  long long *__restrict__ adj_tab) {
+    PhotonPath P{};
+    LaneStats ls;
+    const uint32_t n = *queue.cnt, lane = lane_index();
+    const uint32_t per_wave = min(max((n + waves - 1u) / waves, kMinPathsPerWave), 64u);
+    for (uint64_t first = (uint64_t)wave * per_wave; first < n; first += (uint64_t)waves * per_wave) {
+        bool live = lane < per_wave && first + lane < n && slot_load(queue.s, (uint32_t)first + lane, P);
+        // recording: a live path's last written bounce is the one before its next
+        if (kRecord) P.last = P.b - 1;
+        while (__ballot(live) != 0ull) {
+            const bool was_live = live;
+            live = photon_bounce<kRecord, kStats>(d, P, live, mat_tab, adj_tab, stk, sink, &ls);
+            if (kRecord && was_live && !live) photon_finish<true>(d, P, mat_tab);
+        }
+    }
+    sink_flush(d, sink);
     if (kStats) {
         wave_stats_flush(d.stats + kStatPhotonPaths, ls);
         wave_stat_add(d.stats + kStatPhotonStored, ls.stored);
@@ -531,6 +629,7 @@ __device__ __forceinline__ void pool_get(const uint32_t *pool, uint32_t slot, Ph
 template <bool kStats = false>
 __device__ __forceinline__ void photon_pool_loop(const SppmDev &d, uint32_t k, uint32_t *__restrict__ pool) {
     PhotonPath P{};
+    PhotonSink sink{nullptr, 0u};
     LaneStats ls;
     bool live = false, exhausted = false;
     uint32_t queued = 0;  // paths in the queue (wave-uniform)
@@ -574,7 +673,7 @@ __device__ __forceinline__ void photon_pool_loop(const SppmDev &d, uint32_t k, u
         __builtin_amdgcn_wave_barrier();
         if (__ballot(live) == 0ull && exhausted && queued == 0u) break;
         // (the binary walk: the queue and the wide walk's stacks together would halve the resident wavefronts)
-        live = photon_bounce<false, kStats>(d, P, live, nullptr, nullptr, nullptr, &ls);
+        live = photon_bounce<false, kStats>(d, P, live, nullptr, nullptr, nullptr, sink, &ls);
     }
     if (kStats) {
         wave_stats_flush(d.stats + kStatPhotonPaths, ls);
@@ -610,7 +709,9 @@ __device__ __forceinline__ void photon_stream_loop(const SppmDev &d, uint32_t k,
             P.org = w.o;
             P.dir = w.d;
             P.excl = w.exclude;
-            live = photon_shade<false, kStats>(d, P, w.best, w.t_hit(), w.best_k, nullptr, nullptr, &ls);
+            bool stored = false;
+            live = photon_shade<false, kStats>(d, P, w.best, w.t_hit(), w.best_k, nullptr, nullptr,
+                                               PhotonSink{nullptr, 0u}, stored, &ls);
             if (live) {
                 w.init(sc.bvh, ray_set(d, P.dir), P.org, P.dir, sc.eps, __builtin_inff(), P.excl);
                 walking = true;
@@ -664,7 +765,7 @@ __device__ __forceinline__ void photon_stream_loop(const SppmDev &d, uint32_t k,
 // without atomics.  Called by every lane of a wave; the loop ends once the
 // range is handed out and no path is live.
 __device__ __forceinline__ void photon_regen_range(const SppmDev &d, uint32_t k, uint32_t n0, uint32_t n1,
-                                                   uint32_t refill, uint32_t *stk) {
+                                                   uint32_t refill, uint32_t *stk, PhotonSink sink) {
     PhotonPath P{};
     bool live = false;
     uint32_t next = n0;
@@ -680,8 +781,9 @@ __device__ __forceinline__ void photon_regen_range(const SppmDev &d, uint32_t k,
             live_mask = __ballot(live);
         }
         if (live_mask == 0ull && next >= n1) break;
-        live = photon_bounce<false>(d, P, live, nullptr, nullptr, stk);
+        live = photon_bounce<false>(d, P, live, nullptr, nullptr, stk, sink);
     }
+    sink_flush(d, sink);
 }
 
 // ---------------------------------------------------------------------------
@@ -701,7 +803,7 @@ __device__ __forceinline__ uint32_t paths_handed_out(const SppmDev &d) {
 // One pass of slot s.  Called by every lane of a wave; lanes with s >= S
 // only take part in the wave's votes.
 __device__ __forceinline__ void photon_pass_elem(const SppmDev &d, uint32_t k, const PassSlots &ps, uint32_t s,
-                                                 uint32_t *stk) {
+                                                 uint32_t *stk, PhotonSink sink) {
     const bool in = s < ps.S;
     PhotonPath P{};
     const bool was_live = in && slot_load(ps, s, P);
@@ -712,7 +814,8 @@ __device__ __forceinline__ void photon_pass_elem(const SppmDev &d, uint32_t k, c
         const uint32_t n = wave_fetch_add(&d.counters[2], want_mask, want);
         if (want && n < d.n_paths) live = photon_emit(d, k, n, P);
     }
-    live = photon_bounce<false>(d, P, live, nullptr, nullptr, stk);
+    live = photon_bounce<false>(d, P, live, nullptr, nullptr, stk, sink);
+    sink_flush(d, sink);
     if (in && (live || was_live)) slot_store(ps, s, P, live);
 }
 
@@ -720,12 +823,13 @@ __device__ __forceinline__ void photon_pass_elem(const SppmDev &d, uint32_t k, c
 // the paths no pass started are taken by regenerating lanes.  Called by every
 // lane of a wave.
 __device__ __forceinline__ void photon_drain_elem(const SppmDev &d, uint32_t k, const PassSlots &ps, uint32_t s,
-                                                  uint32_t *stk) {
+                                                  uint32_t *stk, PhotonSink sink) {
     PhotonPath P{};
     bool live = s < ps.S && slot_load(ps, s, P);
     if (live) wave_append(&d.counters[3]);
-    while (__ballot(live) != 0ull) live = photon_bounce<false>(d, P, live, nullptr, nullptr, stk);
-    if (paths_handed_out(d) < d.n_paths) photon_regen_loop(d, k, d.refill, stk);
+    while (__ballot(live) != 0ull) live = photon_bounce<false>(d, P, live, nullptr, nullptr, stk, sink);
+    sink_flush(d, sink);
+    if (paths_handed_out(d) < d.n_paths) photon_regen_loop(d, k, d.refill, stk, sink);
 }
 
 // ---------------------------------------------------------------------------

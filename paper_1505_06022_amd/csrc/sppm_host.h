@@ -25,6 +25,7 @@ struct pm_sppm {
     uint32_t tail_grid = 1;       // and of its second
     uint32_t head_grid_rec = 1;   // the same two launches recording for the adjoint replay
     uint32_t tail_grid_rec = 1;
+    uint32_t thin = 0;            // paths per wave of a small default photon pass (one launch), else 0
     float phi0 = 0.0f;
     // device buffers
     int32_t *mat_type = nullptr;
