@@ -4,6 +4,8 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <system_error>
+#include <thread>
 #include <vector>
 
 #include "runtime.h"
@@ -535,14 +537,7 @@ namespace pm {
 void sppm_free(pm_sppm *s) {
     // kernels of this handle may still be in flight on the caller's stream
     (void)hipDeviceSynchronize();
-    void *bufs[] = {s->mat_type, s->mat_f, s->emit_pos, s->emit_cdf, s->N, s->R2, s->tau, s->D, s->hp_pos,
-                    s->hp_nrm, s->store, s->store2, s->sorted, s->counters, s->r2max, s->cell_count, s->cell_start,
-                    s->cell_fill, s->bsum, s->M, s->Phi, s->R2_hist, s->adj_tab, s->mat_tab, s->adj_tab2,
-                    s->mat_tab2, s->grad_mat,
-                    s->adj_wide, s->adj_max, s->adj_scale, s->le_part, s->stats, s->sh_key, s->sh_surv, s->slot_mem, s->key_rank,
-                    s->queue_mem, s->hp_pos2, s->hp_nrm2};
-    for (void *b : bufs)
-        if (b) (void)hipFree(b);
+    if (s->arena) (void)hipFree(s->arena);
     for (hipEvent_t e : s->prof_ev)
         if (e) (void)hipEventDestroy(e);
     for (int i = 0; i < 2; ++i) {
@@ -639,9 +634,69 @@ static int32_t photon_kernel_of(const pm_sppm_params *p, bool own_grid) {
     return own_grid ? PM_PHOTON_TWO_PHASE : PM_PHOTON_REGEN;
 }
 
+// The buffers of a handle lie in one allocation, each on a 256-byte boundary.
+// Some 30 allocations and releases, up to 268 MB each, took 0.9 ms of a
+// thumbnail render (333x187, 100,003 photons; create 0.82 -> 0.28 ms, release
+// 0.78 -> 0.38) and 4.6 ms of the release of a recording handle at 1280x720
+// with 2^20 photons (5.07 -> 0.47 ms).
+class Arena {
+  public:
+    template <class T>
+    void add(T *&ptr, size_t bytes) {
+        parts_.push_back({&ptr, size_, [](void *at, char *mem) { *static_cast<T **>(at) = reinterpret_cast<T *>(mem); }});
+        size_ += (bytes + 255) & ~(size_t)255;
+    }
+    hipError_t allocate(void **mem) {
+        const hipError_t e = hipMalloc(mem, size_);
+        if (e != hipSuccess) return *mem = nullptr, e;
+        for (const Part &p : parts_) p.set(p.at, (char *)*mem + p.offset);
+        return e;
+    }
+
+  private:
+    struct Part {
+        void *at;
+        size_t offset;
+        void (*set)(void *, char *);
+    };
+    std::vector<Part> parts_;
+    size_t size_ = 0;
+};
+
+// scene_fingerprint is one serial chain of multiplications (2.1 ms for 250,000
+// triangles, against 0.3 ms for the rest of a handle), so large scenes have it
+// on a thread beside the allocations and uploads: create 2.9 -> 2.2 ms.  Below
+// kHashThread triangles it takes no longer than starting a thread (about 50 us).
+// get() waits for it: the description is not read after the call returns.
+class FingerprintTask {
+  public:
+    static constexpr int64_t kHashThread = 8192;
+    explicit FingerprintTask(const pm_scene_desc *d) : d_(d) {
+        if (d->n_tri < kHashThread) return;
+        try {
+            thread_ = std::thread([this] { hash_ = scene_fingerprint(d_); });
+        } catch (const std::system_error &) {  // no thread to be had: get() computes it
+        }
+    }
+    ~FingerprintTask() {
+        if (thread_.joinable()) thread_.join();
+    }
+    uint64_t get() {
+        if (!thread_.joinable()) return scene_fingerprint(d_);
+        thread_.join();
+        return hash_;
+    }
+
+  private:
+    const pm_scene_desc *d_;
+    uint64_t hash_ = 0;
+    std::thread thread_;
+};
+
 int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t st, bool own_grid, pm_sppm **out) {
     int rc = sppm_validate(d, p);
     if (rc) return rc;
+    FingerprintTask fingerprint(d);
     pm_sppm *s = new pm_sppm();
     s->prm = *p;
     auto fail = [&](int code) {
@@ -669,7 +724,6 @@ int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t 
     }
     const pm_bvh *b = s->bvh;
     s->P = (int64_t)d->width * d->height;
-    s->scene_hash = scene_fingerprint(d);
     // emitters in original triangle order, by power = area * Le
     std::vector<uint32_t> epos;
     std::vector<double> ecdf;
@@ -697,22 +751,55 @@ int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t 
     const uint32_t nb = T / kScanTile;
     const int32_t nm = d->n_mat;
 
-    PM_HIPF(hipMalloc(&s->mat_type, sizeof(int32_t) * nm));
-    PM_HIPF(hipMalloc(&s->mat_f, sizeof(float) * 4 * nm));
-    PM_HIPF(hipMalloc(&s->emit_pos, sizeof(uint32_t) * std::max<size_t>(1, epos.size())));
-    PM_HIPF(hipMalloc(&s->emit_cdf, sizeof(double) * std::max<size_t>(1, ecdf.size())));
-    PM_HIPF(hipMalloc(&s->N, sizeof(double) * s->P));
-    PM_HIPF(hipMalloc(&s->R2, sizeof(double) * s->P));
-    PM_HIPF(hipMalloc(&s->tau, sizeof(double) * s->P));
-    PM_HIPF(hipMalloc(&s->D, sizeof(double) * s->P));
-    PM_HIPF(hipMalloc(&s->hp_pos, sizeof(float4) * s->P));
-    PM_HIPF(hipMalloc(&s->hp_nrm, sizeof(float4) * s->P));
-    PM_HIPF(hipMalloc(&s->store, sizeof(float4) * 2 * (size_t)cap64));
-    PM_HIPF(hipMalloc(&s->counters, sizeof(uint32_t) * 8));
-    PM_HIPF(hipMalloc(&s->r2max, sizeof(unsigned long long) * 2));  // one per iteration parity
-    if (own_grid && !(p->profile & PM_PROFILE_TIME)) {
+    {
+        int dev = 0, cus = 0, per_cu = 0;
+        PM_HIPF(hipGetDevice(&dev));
+        PM_HIPF(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_regen, kBlock, 0));
+        s->regen_grid = (uint32_t)std::max(1, cus * std::max(1, per_cu));
+        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_regen_rec, kBlock, 0));
+        s->regen_grid_rec = (uint32_t)std::max(1, cus * std::max(1, per_cu));
+        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_stream, kBlock, 0));
+        s->stream_grid = (uint32_t)std::max(1, cus * std::max(1, per_cu));
+        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_pool<false>, kBlock, 0));
+        s->pool_grid = (uint32_t)std::max(1, cus * std::max(1, per_cu));
+        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_head<false>, kBlock, 0));
+        s->head_grid = (uint32_t)std::max(1, cus * std::max(1, per_cu));
+        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_tail<false>, kBlock, 0));
+        s->tail_grid = (uint32_t)std::max(1, cus * std::max(1, per_cu));
+        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_head_rec, kBlock, 0));
+        s->head_grid_rec = (uint32_t)std::max(1, cus * std::max(1, per_cu));
+        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_tail_rec, kBlock, 0));
+        s->tail_grid_rec = (uint32_t)std::max(1, cus * std::max(1, per_cu));
+    }
+    {
+        const int64_t waves = (int64_t)s->head_grid * (kBlock / 64);
+        auto spread = [&](int64_t n) {
+            return (uint32_t)std::max<int64_t>((n + waves - 1) / waves, (int64_t)kMinPathsPerWave);
+        };
+        if (own_grid && p->photon_kernel == PM_PHOTON_AUTO && !(p->profile & PM_PROFILE_COUNT) &&
+            spread(p->n_photons) <= kThinPaths)
+            s->thin = spread(p->n_photons);
+    }
+    const int32_t photon_kernel = photon_kernel_of(p, own_grid);
+    const bool pipelined = own_grid && !(p->profile & PM_PROFILE_TIME);
+    Arena arena;
+    arena.add(s->mat_type, sizeof(int32_t) * nm);
+    arena.add(s->mat_f, sizeof(float) * 4 * nm);
+    arena.add(s->emit_pos, sizeof(uint32_t) * std::max<size_t>(1, epos.size()));
+    arena.add(s->emit_cdf, sizeof(double) * std::max<size_t>(1, ecdf.size()));
+    arena.add(s->N, sizeof(double) * s->P);
+    arena.add(s->R2, sizeof(double) * s->P);
+    arena.add(s->tau, sizeof(double) * s->P);
+    arena.add(s->D, sizeof(double) * s->P);
+    arena.add(s->hp_pos, sizeof(float4) * s->P);
+    arena.add(s->hp_nrm, sizeof(float4) * s->P);
+    arena.add(s->store, sizeof(float4) * 2 * (size_t)cap64);
+    arena.add(s->counters, sizeof(uint32_t) * 8);
+    arena.add(s->r2max, sizeof(unsigned long long) * 2);  // one per iteration parity
+    if (pipelined) {
         // a second photon store and a photon stream: consecutive iterations overlap
-        PM_HIPF(hipMalloc(&s->store2, sizeof(float4) * 2 * (size_t)cap64));
+        arena.add(s->store2, sizeof(float4) * 2 * (size_t)cap64);
         PM_HIPF(hipStreamCreateWithFlags(&s->phs, hipStreamNonBlocking));
         for (int i = 0; i < 2; ++i) {
             PM_HIPF(hipEventCreateWithFlags(&s->ev_ph[i], hipEventDisableTiming));
@@ -720,9 +807,9 @@ int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t 
             PM_HIPF(hipEventCreateWithFlags(&s->ev_eye[i], hipEventDisableTiming));
             PM_HIPF(hipEventCreateWithFlags(&s->ev_upd[i], hipEventDisableTiming));
         }
-        PM_HIPF(hipMalloc(&s->hp_pos2, sizeof(float4) * s->P));
-        PM_HIPF(hipMalloc(&s->hp_nrm2, sizeof(float4) * s->P));
-        if (photon_kernel_of(p, own_grid) == PM_PHOTON_TWO_PHASE) {
+        arena.add(s->hp_pos2, sizeof(float4) * s->P);
+        arena.add(s->hp_nrm2, sizeof(float4) * s->P);
+        if (photon_kernel == PM_PHOTON_TWO_PHASE) {
             PM_HIPF(hipStreamCreateWithFlags(&s->tails, hipStreamNonBlocking));
             for (int i = 0; i < 2; ++i) PM_HIPF(hipEventCreateWithFlags(&s->ev_head[i], hipEventDisableTiming));
         }
@@ -731,25 +818,50 @@ int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t 
         PM_HIPF(hipStreamCreateWithFlags(&s->side, hipStreamNonBlocking));
         PM_HIPF(hipEventCreateWithFlags(&s->ev_fork, hipEventDisableTiming));
         PM_HIPF(hipEventCreateWithFlags(&s->ev_join, hipEventDisableTiming));
-        PM_HIPF(hipMalloc(&s->cell_count, sizeof(uint32_t) * T));
+        arena.add(s->cell_count, sizeof(uint32_t) * T);
         if (p->gather_mode == PM_GATHER_STOCHASTIC) {
-            PM_HIPF(hipMalloc(&s->sh_key, sizeof(unsigned long long) * T));
-            PM_HIPF(hipMalloc(&s->sh_surv, sizeof(uint32_t) * T));
+            arena.add(s->sh_key, sizeof(unsigned long long) * T);
+            arena.add(s->sh_surv, sizeof(uint32_t) * T);
         } else {
-            PM_HIPF(hipMalloc(&s->sorted, sizeof(float4) * 2 * (size_t)cap64));
-            PM_HIPF(hipMalloc(&s->cell_start, sizeof(uint32_t) * (T + 1)));
-            PM_HIPF(hipMalloc(&s->cell_fill, sizeof(uint32_t) * T));
-            PM_HIPF(hipMalloc(&s->bsum, sizeof(uint32_t) * (nb + 1)));
+            arena.add(s->sorted, sizeof(float4) * 2 * (size_t)cap64);
+            arena.add(s->cell_start, sizeof(uint32_t) * (T + 1));
+            arena.add(s->cell_fill, sizeof(uint32_t) * T);
+            arena.add(s->bsum, sizeof(uint32_t) * (nb + 1));
         }
     }
-    PM_HIPF(hipMalloc(&s->M, sizeof(uint32_t) * s->P));
-    PM_HIPF(hipMalloc(&s->Phi, sizeof(unsigned long long) * s->P));
-    if (p->gather_mode == PM_GATHER_EXACT) PM_HIPF(hipMalloc(&s->key_rank, sizeof(uint2) * (size_t)cap64));
+    arena.add(s->M, sizeof(uint32_t) * s->P);
+    arena.add(s->Phi, sizeof(unsigned long long) * s->P);
+    if (p->gather_mode == PM_GATHER_EXACT) arena.add(s->key_rank, sizeof(uint2) * (size_t)cap64);
+    // one slot per thread of a pass; the paper runs one thread per pixel
+    const uint32_t pass_slots = p->pass_threads > 0 ? (uint32_t)p->pass_threads
+                                                    : (uint32_t)std::min<int64_t>(s->P, int64_t(1) << 26);
+    if (p->photon_kernel == PM_PHOTON_PASSES) arena.add(s->slot_mem, (size_t)56 * pass_slots);
+    // two-phase pass, per store parity: a queue slot for every lane of the first
+    // launch (each parks at most one path), then the queue's count
+    const uint32_t queue_slots =
+        (uint32_t)std::min<int64_t>(p->n_photons, (int64_t)std::max(s->head_grid, s->head_grid_rec) * kBlock);
+    const size_t queue_bytes = (size_t)56 * queue_slots + 256;
+    if (photon_kernel == PM_PHOTON_TWO_PHASE) arena.add(s->queue_mem, 2 * queue_bytes);
+    if (p->profile & PM_PROFILE_COUNT) arena.add(s->stats, sizeof(unsigned long long) * kStatCount);
+    s->rec_iters = p->record_iterations;
+    if (s->rec_iters > 0) {
+        arena.add(s->R2_hist, sizeof(double) * (size_t)s->rec_iters * s->P);
+        arena.add(s->adj_tab, sizeof(long long) * (size_t)p->n_photons * p->max_photon_bounces);
+        arena.add(s->mat_tab, sizeof(uint16_t) * (size_t)p->n_photons * p->max_photon_bounces);
+        arena.add(s->grad_mat, sizeof(double) * (nm + 1));
+        arena.add(s->adj_wide, sizeof(unsigned long long) * 2 * nm);
+        arena.add(s->adj_max, sizeof(unsigned long long) * 4);
+        if (pipelined) {  // the adjoint overlaps consecutive iterations like the forward
+            arena.add(s->adj_tab2, sizeof(long long) * (size_t)p->n_photons * p->max_photon_bounces);
+            arena.add(s->mat_tab2, sizeof(uint16_t) * (size_t)p->n_photons * p->max_photon_bounces);
+        }
+        arena.add(s->adj_scale, sizeof(double));
+        arena.add(s->le_part, sizeof(double) * blocks_for(s->P));
+    }
+    PM_HIPF(arena.allocate(&s->arena));
+
     if (p->photon_kernel == PM_PHOTON_PASSES) {
-        // one slot per thread of a pass; the paper runs one thread per pixel
-        const uint32_t S = p->pass_threads > 0 ? (uint32_t)p->pass_threads
-                                               : (uint32_t)std::min<int64_t>(s->P, int64_t(1) << 26);
-        PM_HIPF(hipMalloc(&s->slot_mem, (size_t)56 * S));
+        const uint32_t S = pass_slots;
         char *m = (char *)s->slot_mem;
         s->slots.g = (int4 *)m;
         s->slots.o = (float4 *)(m + (size_t)16 * S);
@@ -759,29 +871,26 @@ int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t 
         const int64_t auto_pass = (p->n_photons + S - 1) / S + 8;
         s->n_pass = p->passes > 0 ? p->passes : (int32_t)std::min<int64_t>(auto_pass, 1024);
     }
+    if (photon_kernel == PM_PHOTON_TWO_PHASE) {
+        const uint32_t S = queue_slots;
+        for (int i = 0; i < 2; ++i) {
+            char *m = (char *)s->queue_mem + i * queue_bytes;
+            PathQueue &q = s->queue[i];
+            q.s.g = (int4 *)m;
+            q.s.o = (float4 *)(m + (size_t)16 * S);
+            q.s.w = (float4 *)(m + (size_t)32 * S);
+            q.s.nb = (uint2 *)(m + (size_t)48 * S);
+            q.s.S = S;
+            q.cnt = (uint32_t *)(m + (size_t)56 * S);
+        }
+    }
     if (p->profile & PM_PROFILE_COUNT) {
-        PM_HIPF(hipMalloc(&s->stats, sizeof(unsigned long long) * kStatCount));
         PM_HIPF(hipMemsetAsync(s->stats, 0, sizeof(unsigned long long) * kStatCount, st));
     }
     if (p->profile & PM_PROFILE_TIME)
         for (hipEvent_t &e : s->prof_ev) PM_HIPF(hipEventCreate(&e));
     s->n_mat = nm;
     s->rho_host.assign(d->mat_rho, d->mat_rho + nm);
-    s->rec_iters = p->record_iterations;
-    if (s->rec_iters > 0) {
-        PM_HIPF(hipMalloc(&s->R2_hist, sizeof(double) * (size_t)s->rec_iters * s->P));
-        PM_HIPF(hipMalloc(&s->adj_tab, sizeof(long long) * (size_t)p->n_photons * p->max_photon_bounces));
-        PM_HIPF(hipMalloc(&s->mat_tab, sizeof(uint16_t) * (size_t)p->n_photons * p->max_photon_bounces));
-        PM_HIPF(hipMalloc(&s->grad_mat, sizeof(double) * (nm + 1)));
-        PM_HIPF(hipMalloc(&s->adj_wide, sizeof(unsigned long long) * 2 * nm));
-        PM_HIPF(hipMalloc(&s->adj_max, sizeof(unsigned long long) * 4));
-        if (s->store2) {  // the adjoint overlaps consecutive iterations like the forward
-            PM_HIPF(hipMalloc(&s->adj_tab2, sizeof(long long) * (size_t)p->n_photons * p->max_photon_bounces));
-            PM_HIPF(hipMalloc(&s->mat_tab2, sizeof(uint16_t) * (size_t)p->n_photons * p->max_photon_bounces));
-        }
-        PM_HIPF(hipMalloc(&s->adj_scale, sizeof(double)));
-        PM_HIPF(hipMalloc(&s->le_part, sizeof(double) * blocks_for(s->P)));
-    }
     {
         int n_emit_mat = 0;
         double le = 0.0;
@@ -854,7 +963,7 @@ int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t 
     dv.P = s->P;
     dv.mask = T - 1u;
     dv.table_off = 0;
-    dv.photon_kernel = photon_kernel_of(p, own_grid);
+    dv.photon_kernel = photon_kernel;
     dv.refill = p->refill > 0 ? (uint32_t)p->refill : 32u;
     dv.force_set = p->single_link_set - 1;
     // Paired node requests pay off on one large scene (2.65 -> 2.55 ms per
@@ -864,54 +973,6 @@ int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t 
     dv.gather_mode = p->gather_mode;
     dv.sh_key = s->sh_key;
     dv.sh_surv = s->sh_surv;
-    {
-        int dev = 0, cus = 0, per_cu = 0;
-        PM_HIPF(hipGetDevice(&dev));
-        PM_HIPF(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_regen, kBlock, 0));
-        s->regen_grid = (uint32_t)std::max(1, cus * std::max(1, per_cu));
-        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_regen_rec, kBlock, 0));
-        s->regen_grid_rec = (uint32_t)std::max(1, cus * std::max(1, per_cu));
-        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_stream, kBlock, 0));
-        s->stream_grid = (uint32_t)std::max(1, cus * std::max(1, per_cu));
-        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_pool<false>, kBlock, 0));
-        s->pool_grid = (uint32_t)std::max(1, cus * std::max(1, per_cu));
-        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_head<false>, kBlock, 0));
-        s->head_grid = (uint32_t)std::max(1, cus * std::max(1, per_cu));
-        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_tail<false>, kBlock, 0));
-        s->tail_grid = (uint32_t)std::max(1, cus * std::max(1, per_cu));
-        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_head_rec, kBlock, 0));
-        s->head_grid_rec = (uint32_t)std::max(1, cus * std::max(1, per_cu));
-        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_tail_rec, kBlock, 0));
-        s->tail_grid_rec = (uint32_t)std::max(1, cus * std::max(1, per_cu));
-    }
-    {
-        const int64_t waves = (int64_t)s->head_grid * (kBlock / 64);
-        auto spread = [&](int64_t n) {
-            return (uint32_t)std::max<int64_t>((n + waves - 1) / waves, (int64_t)kMinPathsPerWave);
-        };
-        if (own_grid && p->photon_kernel == PM_PHOTON_AUTO && !(p->profile & PM_PROFILE_COUNT) &&
-            spread(p->n_photons) <= kThinPaths)
-            s->thin = spread(p->n_photons);
-    }
-    if (dv.photon_kernel == PM_PHOTON_TWO_PHASE) {
-        // per store parity: a queue slot for every lane of the first launch
-        // (each parks at most one path), then the queue's count
-        const uint32_t S = (uint32_t)std::min<int64_t>(
-            p->n_photons, (int64_t)std::max(s->head_grid, s->head_grid_rec) * kBlock);
-        const size_t per = (size_t)56 * S + 256;
-        PM_HIPF(hipMalloc(&s->queue_mem, 2 * per));
-        for (int i = 0; i < 2; ++i) {
-            char *m = (char *)s->queue_mem + i * per;
-            PathQueue &q = s->queue[i];
-            q.s.g = (int4 *)m;
-            q.s.o = (float4 *)(m + (size_t)16 * S);
-            q.s.w = (float4 *)(m + (size_t)32 * S);
-            q.s.nb = (uint2 *)(m + (size_t)48 * S);
-            q.s.S = S;
-            q.cnt = (uint32_t *)(m + (size_t)56 * S);
-        }
-    }
     dv.hp_pos = s->hp_pos;
     dv.hp_nrm = s->hp_nrm;
     dv.N = s->N;
@@ -929,6 +990,7 @@ int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t 
     PM_HIPF(hipGetLastError());
     // host staging vectors go out of scope: finish the copies first
     PM_HIPF(hipStreamSynchronize(st));
+    s->scene_hash = fingerprint.get();
 #undef PM_HIPF
     *out = s;
     return PM_OK;

@@ -27,7 +27,8 @@ struct pm_sppm {
     uint32_t tail_grid_rec = 1;
     uint32_t thin = 0;            // paths per wave of a small default photon pass (one launch), else 0
     float phi0 = 0.0f;
-    // device buffers
+    // device buffers, all within the one allocation `arena`
+    void *arena = nullptr;
     int32_t *mat_type = nullptr;
     float *mat_f = nullptr;  // rho | q | Le | ior, each n_mat
     uint32_t *emit_pos = nullptr;
