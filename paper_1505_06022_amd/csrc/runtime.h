@@ -27,6 +27,8 @@ int hip_fail(hipError_t e, const char *what);
 // Zeroed nodes after a BVH's six node arrays: a packet walk reads the node
 // after the one it visits.
 constexpr size_t kPadNodes = 1;
+// Room after the triangle records for the work counter.
+constexpr size_t kNextBytes = 64;
 
 }  // namespace pm
 
@@ -40,7 +42,7 @@ struct pm_bvh {
     uint4 *d_wide = nullptr;    // [n_wide][4] four-child nodes of the wide walk (NULL: binary walks only)
     int64_t n_wide = 0;
     float4 *d_tris = nullptr;   // [n_refs][3]
-    uint32_t *d_next = nullptr; // work counter of the persistent traversal kernel
+    uint32_t *d_next = nullptr; // work counter of the persistent traversal kernel, after the triangles
     uint32_t *d_perm = nullptr; // ray order of the reordering traversal (perm_cap entries)
     uint64_t perm_cap = 0;
     uint32_t *d_order = nullptr; // bucket counts / starts / cursors of the ray reordering
@@ -77,9 +79,25 @@ int build_bvh_gpu(const float *verts, const uint32_t *mats, int64_t n_tri, int m
 int upload_bvh(const HostBvh &h, hipStream_t s, pm_bvh *b);
 void free_bvh(pm_bvh *b);
 
-// Merge the binary tree of b's link set 0 (already on the device, enqueued on
-// s) into the four-child nodes of the wide walk; synchronises s.
-int build_wide(pm_bvh *b, hipStream_t s);
+// Merges the binary tree of a BVH's link set 0 into the four-child nodes of the
+// wide walk: launch() enqueues the work once the binary nodes are enqueued on
+// s, finish() synchronises s and fills the handle.  The handle's node count and
+// box grid are read, the nodes must outlive the object.
+class WideBuild {
+  public:
+    WideBuild() = default;
+    WideBuild(const WideBuild &) = delete;
+    ~WideBuild();
+    int launch(const pm_bvh *b, hipStream_t s);
+    int finish(pm_bvh *b, hipStream_t s);
+
+  private:
+    int expand(const pm_bvh *b, hipStream_t s, uint32_t upto);
+    void *mem_ = nullptr;
+    uint2 *list_[2] = {};
+    uint32_t *flag_ = nullptr, *index_ = nullptr, *fill_ = nullptr, *bsum_ = nullptr, *cnt_ = nullptr;
+    uint32_t n_ = 0, tiles_ = 0, launches_ = 0;
+};
 
 // Validated arguments of one traced batch.  link_set < 0 selects by
 // direction; block: threads per workgroup of the one-ray-per-lane kernels

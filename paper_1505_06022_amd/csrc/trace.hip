@@ -624,19 +624,20 @@ int upload_bvh(const HostBvh &h, hipStream_t s, pm_bvh *b) {
     // zeroed pad nodes after the six arrays (a packet walk reads the node after the one it visits)
     PM_HIP(hipMalloc(&b->d_nodes, nb + sizeof(uint4) * pm::kPadNodes));
     PM_HIP(hipMemsetAsync((char *)b->d_nodes + nb, 0, sizeof(uint4) * pm::kPadNodes, s));
-    PM_HIP(hipMalloc(&b->d_tris, tb));
-    PM_HIP(hipMalloc(&b->d_next, 64));
+    PM_HIP(hipMalloc(&b->d_tris, tb + kNextBytes));
+    b->d_next = (uint32_t *)((char *)b->d_tris + tb);
     PM_HIP(hipMemcpyAsync(b->d_nodes, h.nodes.data(), nb, hipMemcpyHostToDevice, s));
     PM_HIP(hipMemcpyAsync(b->d_tris, h.tris.data(), tb, hipMemcpyHostToDevice, s));
-    // host vectors are freed by the caller: build_wide waits for the copies
-    return build_wide(b, s);
+    // host vectors are freed by the caller: finish() waits for the copies
+    WideBuild wide;
+    const int rc = wide.launch(b, s);
+    return rc ? rc : wide.finish(b, s);
 }
 
 void free_bvh(pm_bvh *b) {
     if (b->d_nodes) (void)hipFree(b->d_nodes);
     if (b->d_wide) (void)hipFree(b->d_wide);
     if (b->d_tris) (void)hipFree(b->d_tris);
-    if (b->d_next) (void)hipFree(b->d_next);
     if (b->d_perm) (void)hipFree(b->d_perm);
     if (b->d_order) (void)hipFree(b->d_order);
     for (int k = 0; k < PM_MAX_TRACE_BATCHES; ++k) {
