@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <mutex>
 #include <system_error>
 #include <thread>
 #include <vector>
@@ -27,19 +28,19 @@ using namespace pmd;
     __shared__ float4 photon_buf[kBlock / 64][kSinkWords]; \
     const PhotonSink sink{photon_buf[threadIdx.x >> 6], 0u}
 
-__global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_eye(SppmDev d, uint32_t k, int32_t accumulate_D) {
+__global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_eye(SppmDev d, uint32_t k, int32_t emission) {
     int64_t p = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
     PM_STACK();
-    eye_elem(d, k, p, p < d.P, accumulate_D != 0, stk);
+    eye_elem(d, k, p, p < d.P, emission != 0, stk);
 }
 
 // The statistics variants (PM_PROFILE_COUNT): the same work, plus counts of
 // paths, rays, box and triangle tests, and of the range query's buckets and
 // photons, added to d.stats once per wavefront.
-__global__ __launch_bounds__(kBlock) void k_eye_stats(SppmDev d, uint32_t k, int32_t accumulate_D) {
+__global__ __launch_bounds__(kBlock) void k_eye_stats(SppmDev d, uint32_t k, int32_t emission) {
     int64_t p = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
     LaneStats ls;
-    eye_elem<true>(d, k, p, p < d.P, accumulate_D != 0, nullptr, &ls);
+    eye_elem<true>(d, k, p, p < d.P, emission != 0, nullptr, &ls);
     wave_stats_flush(d.stats + kStatEyePaths, ls);
 }
 
@@ -534,26 +535,85 @@ inline H3 hnorm(H3 v) {
 
 namespace pm {
 
+// Stream sets of released handles, kept for the next ones (at most kPoolSets).
+//
+// The runtime maps streams onto four hardware queues (its default), a new
+// stream onto the queue with the fewest, and streams that share a queue run one
+// after another.  The four streams of a set must lie on four queues: with the
+// main stream on a photon pass's queue 8 iterations at 1280x720 take 10.5 ms
+// instead of 9.0, and the caller's stream in place of the main one shares a
+// queue with a photon pass in every third handle (10.9).  While one of the queues
+// is already used by the default stream, the fourth stream of a fresh process
+// would not get that queue but one of its own set's, so three more streams are
+// created first, which even out the queues, and released afterwards.  That costs
+// 300 us a set, so sets are kept: a set is used by one handle at a time, and only
+// a set with no work and no capture under way is kept.
+constexpr int kPoolSets = 4;
+static std::mutex g_pool_mu;
+static struct {
+    int device;
+    PassStreams set;
+} g_pool[kPoolSets];
+static int g_pool_n = 0;
+
+static void destroy_streams(PassStreams &p) {
+    for (hipStream_t *q : {&p.pass[0], &p.pass[1], &p.pass[2], &p.main}) {
+        if (*q) (void)hipStreamDestroy(*q);
+        *q = nullptr;
+    }
+}
+
+// A set of streams of the current device.
+static hipError_t take_streams(int device, PassStreams &out) {
+    {
+        std::lock_guard<std::mutex> lock(g_pool_mu);
+        for (int i = g_pool_n - 1; i >= 0; --i)
+            if (g_pool[i].device == device) {
+                out = g_pool[i].set;
+                g_pool[i] = g_pool[--g_pool_n];
+                return hipSuccess;
+            }
+    }
+    hipStream_t even[3] = {};
+    hipError_t e = hipSuccess;
+    for (hipStream_t *q : {&even[0], &even[1], &even[2], &out.pass[0], &out.pass[1], &out.pass[2], &out.main})
+        if (e == hipSuccess) e = hipStreamCreateWithFlags(q, hipStreamNonBlocking);
+    for (hipStream_t q : even)
+        if (q) (void)hipStreamDestroy(q);
+    return e;
+}
+
+// Called once all work on the set's streams has ended.
+static void give_streams(int device, PassStreams &p) {
+    bool keep = true;
+    for (hipStream_t q : {p.pass[0], p.pass[1], p.pass[2], p.main}) {
+        hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+        keep = keep && q && hipStreamIsCapturing(q, &c) == hipSuccess && c == hipStreamCaptureStatusNone;
+    }
+    if (keep) {
+        std::lock_guard<std::mutex> lock(g_pool_mu);
+        if (g_pool_n < kPoolSets) {
+            g_pool[g_pool_n].device = device;
+            g_pool[g_pool_n++].set = p;
+            p = PassStreams{};
+            return;
+        }
+    }
+    destroy_streams(p);
+}
+
 void sppm_free(pm_sppm *s) {
     // kernels of this handle may still be in flight on the caller's stream
     (void)hipDeviceSynchronize();
     if (s->arena) (void)hipFree(s->arena);
     for (hipEvent_t e : s->prof_ev)
         if (e) (void)hipEventDestroy(e);
-    for (int i = 0; i < 2; ++i) {
-        if (s->ev_ph[i]) (void)hipEventDestroy(s->ev_ph[i]);
-        if (s->ev_scat[i]) (void)hipEventDestroy(s->ev_scat[i]);
-    }
-    if (s->phs) (void)hipStreamDestroy(s->phs);
-    for (int i = 0; i < 2; ++i) {
-        if (s->ev_head[i]) (void)hipEventDestroy(s->ev_head[i]);
-        if (s->ev_eye[i]) (void)hipEventDestroy(s->ev_eye[i]);
-        if (s->ev_upd[i]) (void)hipEventDestroy(s->ev_upd[i]);
-    }
-    if (s->tails) (void)hipStreamDestroy(s->tails);
-    if (s->ev_fork) (void)hipEventDestroy(s->ev_fork);
-    if (s->ev_join) (void)hipEventDestroy(s->ev_join);
-    if (s->side) (void)hipStreamDestroy(s->side);
+    for (uint32_t i = 0; i < kRing; ++i)
+        for (hipEvent_t e : {s->ev_ph[i], s->ev_scat[i], s->ev_eye[i], s->ev_upd[i]})
+            if (e) (void)hipEventDestroy(e);
+    give_streams(s->device, s->streams);
+    for (hipEvent_t e : {s->ev_fork, s->ev_join})
+        if (e) (void)hipEventDestroy(e);
     if (s->own_bvh && s->bvh) {
         free_bvh(s->bvh);
         delete s->bvh;
@@ -618,13 +678,22 @@ int sppm_validate(const pm_scene_desc *d, const pm_sppm_params *p) {
 }
 
 // A default photon pass of at most this many paths for each wave the device
-// holds (4,096) runs in one launch that spreads them evenly over the waves
-// (k_photon), the passes of even and odd iterations on two streams.  It ends
-// with its longest path either way, but the two launches of full waves came one
-// after another for every iteration.  Calls, two launches and one (ms): 8
-// iterations of 100,003 paths 6.6 and 4.6, 4 of 2^18 paths 2.4 and 2.0.  Beyond
-// 64 paths a wave the regenerating launch fills its lanes better.
+// holds (4,096) runs in one launch that spreads them evenly over half of the
+// waves (k_photon).  It ends with its longest path either way, but the two
+// launches of full waves came one after another for every iteration.  Calls, two
+// launches and one (ms): 8 iterations of 100,003 paths 3.6 and 3.1, 4 of 2^18
+// paths 1.9 either way.  Beyond 64 paths a wave the regenerating launch fills its
+// lanes better.
 constexpr uint32_t kThinPaths = 64;
+
+// The photon passes of a pipelined handle do not take the whole device: a wave
+// of theirs keeps its slot (and its LDS) for most of a pass, and two passes, an
+// eye pass and a range query are under way at once.  With all slots taken the
+// eye pass, whose waves mostly wait, became the longest stage: 1.9 ms instead of
+// 0.4.  1280x720, 2^20 photons, ms an iteration in calls of 8: all waves for
+// either launch 1.20, half for the first and a quarter for the second 1.09
+// (3/4 and 1/4 1.10, 3/8 and 1/4 1.10, 1/2 and 1/8 1.19).
+constexpr uint32_t kHeadShare = 2, kTailShare = 4;
 
 // The photon schedule a handle runs: the default is the two-phase pass on
 // single-scene handles and regeneration for a batch member (whose photon
@@ -754,6 +823,7 @@ int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t 
     {
         int dev = 0, cus = 0, per_cu = 0;
         PM_HIPF(hipGetDevice(&dev));
+        s->device = dev;
         PM_HIPF(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
         PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_regen, kBlock, 0));
         s->regen_grid = (uint32_t)std::max(1, cus * std::max(1, per_cu));
@@ -772,93 +842,93 @@ int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t 
         PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_tail_rec, kBlock, 0));
         s->tail_grid_rec = (uint32_t)std::max(1, cus * std::max(1, per_cu));
     }
-    {
-        const int64_t waves = (int64_t)s->head_grid * (kBlock / 64);
-        auto spread = [&](int64_t n) {
-            return (uint32_t)std::max<int64_t>((n + waves - 1) / waves, (int64_t)kMinPathsPerWave);
-        };
-        if (own_grid && p->photon_kernel == PM_PHOTON_AUTO && !(p->profile & PM_PROFILE_COUNT) &&
-            spread(p->n_photons) <= kThinPaths)
-            s->thin = spread(p->n_photons);
-    }
     const int32_t photon_kernel = photon_kernel_of(p, own_grid);
     const bool pipelined = own_grid && !(p->profile & PM_PROFILE_TIME);
-    Arena arena;
-    arena.add(s->mat_type, sizeof(int32_t) * nm);
-    arena.add(s->mat_f, sizeof(float) * 4 * nm);
-    arena.add(s->emit_pos, sizeof(uint32_t) * std::max<size_t>(1, epos.size()));
-    arena.add(s->emit_cdf, sizeof(double) * std::max<size_t>(1, ecdf.size()));
-    arena.add(s->N, sizeof(double) * s->P);
-    arena.add(s->R2, sizeof(double) * s->P);
-    arena.add(s->tau, sizeof(double) * s->P);
-    arena.add(s->D, sizeof(double) * s->P);
-    arena.add(s->hp_pos, sizeof(float4) * s->P);
-    arena.add(s->hp_nrm, sizeof(float4) * s->P);
-    arena.add(s->store, sizeof(float4) * 2 * (size_t)cap64);
-    arena.add(s->counters, sizeof(uint32_t) * 8);
-    arena.add(s->r2max, sizeof(unsigned long long) * 2);  // one per iteration parity
-    if (pipelined) {
-        // a second photon store and a photon stream: consecutive iterations overlap
-        arena.add(s->store2, sizeof(float4) * 2 * (size_t)cap64);
-        PM_HIPF(hipStreamCreateWithFlags(&s->phs, hipStreamNonBlocking));
-        for (int i = 0; i < 2; ++i) {
-            PM_HIPF(hipEventCreateWithFlags(&s->ev_ph[i], hipEventDisableTiming));
-            PM_HIPF(hipEventCreateWithFlags(&s->ev_scat[i], hipEventDisableTiming));
-            PM_HIPF(hipEventCreateWithFlags(&s->ev_eye[i], hipEventDisableTiming));
-            PM_HIPF(hipEventCreateWithFlags(&s->ev_upd[i], hipEventDisableTiming));
-        }
-        arena.add(s->hp_pos2, sizeof(float4) * s->P);
-        arena.add(s->hp_nrm2, sizeof(float4) * s->P);
-        if (photon_kernel == PM_PHOTON_TWO_PHASE) {
-            PM_HIPF(hipStreamCreateWithFlags(&s->tails, hipStreamNonBlocking));
-            for (int i = 0; i < 2; ++i) PM_HIPF(hipEventCreateWithFlags(&s->ev_head[i], hipEventDisableTiming));
-        }
+    {
+        const int64_t waves = (int64_t)s->head_grid * (kBlock / 64), np = p->n_photons;
+        if (own_grid && p->photon_kernel == PM_PHOTON_AUTO && !(p->profile & PM_PROFILE_COUNT) &&
+            np <= waves * kThinPaths)
+            s->thin = (uint32_t)std::min<int64_t>(std::max<int64_t>((2 * np + waves - 1) / waves, kMinPathsPerWave),
+                                                  kThinPaths);
+        if (pipelined)
+            for (uint32_t *head : {&s->head_grid, &s->head_grid_rec}) *head = std::max(1u, *head / kHeadShare);
+        if (pipelined)
+            for (uint32_t *tail : {&s->tail_grid, &s->tail_grid_rec}) *tail = std::max(1u, *tail / kTailShare);
     }
+    // a stream per slot (two where the photon passes share one): see photon_queue
+    const uint32_t slots = !pipelined ? 1u : (photon_kernel == PM_PHOTON_TWO_PHASE ? kRing : 2u);
     if (own_grid) {
-        PM_HIPF(hipStreamCreateWithFlags(&s->side, hipStreamNonBlocking));
+        for (uint32_t i = 0; i < std::max(slots, 2u); ++i) {
+            for (hipEvent_t *e : {&s->ev_ph[i], &s->ev_scat[i], &s->ev_eye[i], &s->ev_upd[i]})
+                PM_HIPF(hipEventCreateWithFlags(e, hipEventDisableTiming));
+        }
+        PM_HIPF(take_streams(s->device, s->streams));
         PM_HIPF(hipEventCreateWithFlags(&s->ev_fork, hipEventDisableTiming));
         PM_HIPF(hipEventCreateWithFlags(&s->ev_join, hipEventDisableTiming));
-        arena.add(s->cell_count, sizeof(uint32_t) * T);
-        if (p->gather_mode == PM_GATHER_STOCHASTIC) {
-            arena.add(s->sh_key, sizeof(unsigned long long) * T);
-            arena.add(s->sh_surv, sizeof(uint32_t) * T);
-        } else {
-            arena.add(s->sorted, sizeof(float4) * 2 * (size_t)cap64);
-            arena.add(s->cell_start, sizeof(uint32_t) * (T + 1));
-            arena.add(s->cell_fill, sizeof(uint32_t) * T);
-            arena.add(s->bsum, sizeof(uint32_t) * (nb + 1));
-        }
     }
-    arena.add(s->M, sizeof(uint32_t) * s->P);
-    arena.add(s->Phi, sizeof(unsigned long long) * s->P);
-    if (p->gather_mode == PM_GATHER_EXACT) arena.add(s->key_rank, sizeof(uint2) * (size_t)cap64);
     // one slot per thread of a pass; the paper runs one thread per pixel
     const uint32_t pass_slots = p->pass_threads > 0 ? (uint32_t)p->pass_threads
                                                     : (uint32_t)std::min<int64_t>(s->P, int64_t(1) << 26);
-    if (p->photon_kernel == PM_PHOTON_PASSES) arena.add(s->slot_mem, (size_t)56 * pass_slots);
-    // two-phase pass, per store parity: a queue slot for every lane of the first
+    // two-phase pass, per slot: a queue slot for every lane of the first
     // launch (each parks at most one path), then the queue's count
     const uint32_t queue_slots =
         (uint32_t)std::min<int64_t>(p->n_photons, (int64_t)std::max(s->head_grid, s->head_grid_rec) * kBlock);
     const size_t queue_bytes = (size_t)56 * queue_slots + 256;
-    if (photon_kernel == PM_PHOTON_TWO_PHASE) arena.add(s->queue_mem, 2 * queue_bytes);
-    if (p->profile & PM_PROFILE_COUNT) arena.add(s->stats, sizeof(unsigned long long) * kStatCount);
     s->rec_iters = p->record_iterations;
-    if (s->rec_iters > 0) {
-        arena.add(s->R2_hist, sizeof(double) * (size_t)s->rec_iters * s->P);
-        arena.add(s->adj_tab, sizeof(long long) * (size_t)p->n_photons * p->max_photon_bounces);
-        arena.add(s->mat_tab, sizeof(uint16_t) * (size_t)p->n_photons * p->max_photon_bounces);
-        arena.add(s->grad_mat, sizeof(double) * (nm + 1));
-        arena.add(s->adj_wide, sizeof(unsigned long long) * 2 * nm);
-        arena.add(s->adj_max, sizeof(unsigned long long) * 4);
-        if (pipelined) {  // the adjoint overlaps consecutive iterations like the forward
-            arena.add(s->adj_tab2, sizeof(long long) * (size_t)p->n_photons * p->max_photon_bounces);
-            arena.add(s->mat_tab2, sizeof(uint16_t) * (size_t)p->n_photons * p->max_photon_bounces);
+    // a handle that does not fit with all slots makes do with two
+    for (s->ring = slots;; s->ring = 2u) {
+        Arena arena;
+        arena.add(s->mat_type, sizeof(int32_t) * nm);
+        arena.add(s->mat_f, sizeof(float) * 4 * nm);
+        arena.add(s->emit_pos, sizeof(uint32_t) * std::max<size_t>(1, epos.size()));
+        arena.add(s->emit_cdf, sizeof(double) * std::max<size_t>(1, ecdf.size()));
+        arena.add(s->N, sizeof(double) * s->P);
+        arena.add(s->R2, sizeof(double) * s->P);
+        arena.add(s->tau, sizeof(double) * s->P);
+        arena.add(s->D, sizeof(double) * s->P);
+        for (uint32_t i = 0; i < s->ring; ++i) {
+            arena.add(s->hp_pos[i], sizeof(float4) * s->P);
+            arena.add(s->hp_nrm[i], sizeof(float4) * s->P);
+            arena.add(s->emit[i], sizeof(double) * s->P);
+            arena.add(s->store[i], sizeof(float4) * 2 * (size_t)cap64);
         }
-        arena.add(s->adj_scale, sizeof(double));
-        arena.add(s->le_part, sizeof(double) * blocks_for(s->P));
+        arena.add(s->counters, sizeof(uint32_t) * 4 * kRing);
+        arena.add(s->r2max, sizeof(unsigned long long) * kRing);
+        if (own_grid) {
+            arena.add(s->cell_count, sizeof(uint32_t) * T);
+            if (p->gather_mode == PM_GATHER_STOCHASTIC) {
+                arena.add(s->sh_key, sizeof(unsigned long long) * T);
+                arena.add(s->sh_surv, sizeof(uint32_t) * T);
+            } else {
+                arena.add(s->sorted, sizeof(float4) * 2 * (size_t)cap64);
+                arena.add(s->cell_start, sizeof(uint32_t) * (T + 1));
+                arena.add(s->cell_fill, sizeof(uint32_t) * T);
+                arena.add(s->bsum, sizeof(uint32_t) * (nb + 1));
+            }
+        }
+        arena.add(s->M, sizeof(uint32_t) * s->P);
+        arena.add(s->Phi, sizeof(unsigned long long) * s->P);
+        if (p->gather_mode == PM_GATHER_EXACT) arena.add(s->key_rank, sizeof(uint2) * (size_t)cap64);
+        if (p->photon_kernel == PM_PHOTON_PASSES) arena.add(s->slot_mem, (size_t)56 * pass_slots);
+        if (photon_kernel == PM_PHOTON_TWO_PHASE) arena.add(s->queue_mem, s->ring * queue_bytes);
+        if (p->profile & PM_PROFILE_COUNT) arena.add(s->stats, sizeof(unsigned long long) * kStatCount);
+        if (s->rec_iters > 0) {
+            arena.add(s->R2_hist, sizeof(double) * (size_t)s->rec_iters * s->P);
+            for (uint32_t i = 0; i < s->ring; ++i) {  // the adjoint overlaps iterations like the forward
+                arena.add(s->adj_tab[i], sizeof(long long) * (size_t)p->n_photons * p->max_photon_bounces);
+                arena.add(s->mat_tab[i], sizeof(uint16_t) * (size_t)p->n_photons * p->max_photon_bounces);
+            }
+            arena.add(s->grad_mat, sizeof(double) * (nm + 1));
+            arena.add(s->adj_wide, sizeof(unsigned long long) * 2 * nm);
+            arena.add(s->adj_max, sizeof(unsigned long long) * 2 * kRing);
+            arena.add(s->adj_scale, sizeof(double));
+            arena.add(s->le_part, sizeof(double) * blocks_for(s->P));
+        }
+        const hipError_t e = arena.allocate(&s->arena);
+        if (e == hipSuccess) break;
+        if (s->ring <= 2u) return fail(hip_fail(e, "hipMalloc"));
+        (void)hipGetLastError();
     }
-    PM_HIPF(arena.allocate(&s->arena));
 
     if (p->photon_kernel == PM_PHOTON_PASSES) {
         const uint32_t S = pass_slots;
@@ -873,7 +943,7 @@ int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t 
     }
     if (photon_kernel == PM_PHOTON_TWO_PHASE) {
         const uint32_t S = queue_slots;
-        for (int i = 0; i < 2; ++i) {
+        for (uint32_t i = 0; i < s->ring; ++i) {
             char *m = (char *)s->queue_mem + i * queue_bytes;
             PathQueue &q = s->queue[i];
             q.s.g = (int4 *)m;
@@ -915,12 +985,11 @@ int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t 
         PM_HIPF(hipMemcpyAsync(s->emit_pos, epos.data(), sizeof(uint32_t) * epos.size(), hipMemcpyHostToDevice, st));
         PM_HIPF(hipMemcpyAsync(s->emit_cdf, ecdf.data(), sizeof(double) * ecdf.size(), hipMemcpyHostToDevice, st));
     }
-    PM_HIPF(hipMemsetAsync(s->counters, 0, sizeof(uint32_t) * 8, st));
-    PM_HIPF(hipMemsetAsync(s->hp_nrm, 0xff, sizeof(float4) * s->P, st));
-    if (s->hp_nrm2) PM_HIPF(hipMemsetAsync(s->hp_nrm2, 0xff, sizeof(float4) * s->P, st));
+    PM_HIPF(hipMemsetAsync(s->counters, 0, sizeof(uint32_t) * 4 * kRing, st));
+    for (uint32_t i = 0; i < s->ring; ++i) PM_HIPF(hipMemsetAsync(s->hp_nrm[i], 0xff, sizeof(float4) * s->P, st));
     PM_HIPF(hipMemsetAsync(s->M, 0, sizeof(uint32_t) * s->P, st));
     PM_HIPF(hipMemsetAsync(s->Phi, 0, sizeof(unsigned long long) * s->P, st));
-    PM_HIPF(hipMemsetAsync(s->r2max, 0, sizeof(unsigned long long) * 2, st));
+    PM_HIPF(hipMemsetAsync(s->r2max, 0, sizeof(unsigned long long) * kRing, st));
 
     SceneDev &sc = s->dev.sc;
     sc.bvh = make_device_bvh(b);
@@ -973,13 +1042,14 @@ int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t 
     dv.gather_mode = p->gather_mode;
     dv.sh_key = s->sh_key;
     dv.sh_surv = s->sh_surv;
-    dv.hp_pos = s->hp_pos;
-    dv.hp_nrm = s->hp_nrm;
+    dv.hp_pos = s->hp_pos[0];
+    dv.hp_nrm = s->hp_nrm[0];
+    dv.emit = s->emit[0];
     dv.N = s->N;
     dv.R2 = s->R2;
     dv.tau = s->tau;
     dv.D = s->D;
-    dv.store = s->store;
+    dv.store = s->store[0];
     dv.key_rank = s->key_rank;
     dv.counters = s->counters;
     dv.r2max = s->r2max;
@@ -1013,26 +1083,68 @@ int sppm_reset(pm_sppm *s, hipStream_t st) {
     return PM_OK;
 }
 
-// Device view of iteration k: a pipelined handle alternates two photon stores
-// (each with its block of four counters), two hit-point buffers and two R_max
-// accumulators between consecutive iterations.
+// Device view of iteration k: its slot's photon store (with its block of four
+// counters), hit points, seen emission and R_max.
 static SppmDev iteration_view(const pm_sppm *s, uint32_t k) {
     SppmDev dk = s->dev;
-    const uint32_t par = s->store2 ? (k & 1u) : 0u;
-    dk.store = par ? s->store2 : s->store;
-    dk.counters = s->counters + 4 * par;
-    dk.r2max = s->r2max + par;
-    if (par && s->hp_pos2) {
-        dk.hp_pos = s->hp_pos2;
-        dk.hp_nrm = s->hp_nrm2;
-    }
+    const uint32_t i = k % s->ring;
+    dk.store = s->store[i];
+    dk.counters = s->counters + 4 * i;
+    dk.r2max = s->r2max + i;
+    dk.hp_pos = s->hp_pos[i];
+    dk.hp_nrm = s->hp_nrm[i];
+    dk.emit = s->emit[i];
     return dk;
 }
 
-// The photon pass of iteration k (its counters cleared first) on stream q;
-// the two-phase pass's second launch goes on stream tq (after the first).
-// The pass has ended once tq's work enqueued so far is done.
-static int enqueue_photon(pm_sppm *s, const SppmDev &dk, uint32_t k, bool count, hipStream_t q, hipStream_t tq) {
+// The streams of iteration k's photon and eye pass beside the main stream.  A
+// pipelined handle's iterations take them in turn, the eye pass of k on the one
+// that the photon pass of k + 1 takes after it: every stream then has the same
+// work, and a photon pass, whose last paths run long, overlaps the next two.
+// (With one stream for all eye passes and two for the photon passes the eye
+// passes' stream was the slowest.  The eye pass of k on the stream of k + 2: 0
+// to 3% faster or slower in calls of 8 iterations, 11% slower in 4 of the
+// stochastic gather at 640x360.)  Photon kernels whose passes share a workspace
+// run them on one stream.
+static hipStream_t photon_queue(const pm_sppm *s, uint32_t k) {
+    return s->streams.pass[s->dev.photon_kernel == PM_PHOTON_TWO_PHASE ? k % s->ring : 0u];
+}
+static hipStream_t eye_queue(const pm_sppm *s, uint32_t k) {
+    return s->streams.pass[s->dev.photon_kernel == PM_PHOTON_TWO_PHASE && s->ring > 1 ? (k + 1u) % s->ring : 1u];
+}
+// The stream of a pipelined call's grids, range queries and updates: the main
+// stream, or the caller's where the call is being recorded into a graph.  The
+// runtime keeps the streams of a recording in a tree below the one that began
+// it and walks that tree at the end: main and a pass stream, each waiting for the
+// other, would be each other's parent and the walk endless.
+static hipStream_t work_stream(const pm_sppm *s, hipStream_t caller) {
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (caller && hipStreamIsCapturing(caller, &c) == hipSuccess && c != hipStreamCaptureStatusNone) return caller;
+    return s->streams.main;
+}
+
+// Forks the work stream and those that the first iterations from k0 on use from
+// the caller's stream; a stream without work stays out of it (in a recording it
+// could not be joined).
+static hipError_t fork_streams(pm_sppm *s, uint32_t k0, uint32_t n_iter, hipStream_t work, hipStream_t st) {
+    hipError_t e = hipEventRecord(s->ev_fork, st);
+    for (hipStream_t q : {work, s->streams.pass[0], s->streams.pass[1], s->streams.pass[2]}) {
+        bool used = q == work && q != st;
+        for (uint32_t k = k0; k < k0 + std::min(n_iter, kRing); ++k)
+            used = used || q == photon_queue(s, k) || q == eye_queue(s, k);
+        if (used && e == hipSuccess) e = hipStreamWaitEvent(q, s->ev_fork, 0);
+    }
+    return e;
+}
+// The work stream has waited for the others.
+static hipError_t join_streams(pm_sppm *s, hipStream_t work, hipStream_t st) {
+    if (work == st) return hipSuccess;
+    hipError_t e = hipEventRecord(s->ev_join, work);
+    return e == hipSuccess ? hipStreamWaitEvent(st, s->ev_join, 0) : e;
+}
+
+// The photon pass of iteration k (its counters cleared first) on stream q.
+static int enqueue_photon(pm_sppm *s, const SppmDev &dk, uint32_t k, bool count, hipStream_t q) {
     const uint32_t np = (uint32_t)s->prm.n_photons;
     hipLaunchKernelGGL(k_photon_begin, dim3(1), dim3(64), 0, q, dk, s->thin ? np : 0u);
     if (s->thin) {
@@ -1042,20 +1154,16 @@ static int enqueue_photon(pm_sppm *s, const SppmDev &dk, uint32_t k, bool count,
         return PM_OK;
     }
     if (dk.photon_kernel == PM_PHOTON_TWO_PHASE) {
-        const PathQueue &pq = s->queue[s->store2 ? (k & 1u) : 0u];
+        const PathQueue &pq = s->queue[k % s->ring];
         hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, q, pq.cnt, 1u, 0u);
         if (count)
             hipLaunchKernelGGL(k_photon_head<true>, dim3(s->head_grid), dim3(kBlock), 0, q, dk, k, pq);
         else
             hipLaunchKernelGGL(k_photon_head<false>, dim3(s->head_grid), dim3(kBlock), 0, q, dk, k, pq);
-        if (tq != q) {
-            PM_HIP(hipEventRecord(s->ev_head[k & 1u], q));
-            PM_HIP(hipStreamWaitEvent(tq, s->ev_head[k & 1u], 0));
-        }
         if (count)
-            hipLaunchKernelGGL(k_photon_tail<true>, dim3(s->tail_grid), dim3(kBlock), 0, tq, dk, pq);
+            hipLaunchKernelGGL(k_photon_tail<true>, dim3(s->tail_grid), dim3(kBlock), 0, q, dk, pq);
         else
-            hipLaunchKernelGGL(k_photon_tail<false>, dim3(s->tail_grid), dim3(kBlock), 0, tq, dk, pq);
+            hipLaunchKernelGGL(k_photon_tail<false>, dim3(s->tail_grid), dim3(kBlock), 0, q, dk, pq);
     } else if (dk.photon_kernel == PM_PHOTON_RAY_REGEN) {
         if (count)
             hipLaunchKernelGGL(k_photon_stream_stats, dim3(s->stream_grid), dim3(kBlock), 0, q, dk, k);
@@ -1087,94 +1195,90 @@ static int enqueue_photon(pm_sppm *s, const SppmDev &dk, uint32_t k, bool count,
     return PM_OK;
 }
 
-// One call runs n_iter iterations.  Per iteration k: the eye pass and R_max
-// on the side stream, the photon pass, then on the caller's stream the hashed
-// grid, the range query and the update.  A pipelined handle (two photon
-// stores) runs its photon passes on a third stream, one after another: the
-// pass of iteration k + 1 needs nothing of iteration k except a free store,
-// so it overlaps iteration k's grid, range query and update and keeps the
-// device full while the photon pass drains.  Events order the rest: the
-// photon pass of k + 1 waits for the scatter of k - 1 (the last reader of its
-// store), the eye pass of k for the update of k - 1 (it overwrites the hit
-// points and R_max that k - 1 read), and the grid of k for the eye pass and
-// photon pass of k.  At the end of the call the caller's stream has waited
+// One call runs n_iter iterations.  Per iteration k: the eye pass and R_max,
+// the photon pass, then the hashed grid, the range query and the update.  A
+// pipelined handle has the last three on its main stream and the eye and photon
+// passes of its iterations on three more (see photon_queue): they need nothing
+// of the iterations before except a free slot, so up to `ring` of them overlap
+// the grid, range query and update of k and each other, and the device stays
+// full while the last paths of a pass run.  Events order the rest: the photon
+// pass of k waits for the last reader of its slot's store (the scatter of
+// k - ring, or its stochastic gather), the eye pass for the update of k - ring
+// (it overwrites the hit points that k - ring read), and the grid of k for the
+// eye pass and photon pass of k.  With two slots, and the second launches of all
+// passes on one stream, the next pass waited out a whole photon pass: 8
+// iterations at 1280x720 with 2^20 photons went from 10.6 to 8.8 ms, 4 of the
+// stochastic gather at 640x360 with 2^18 from 2.2 to 1.8, with the shares of the
+// device at kHeadShare.  At the end of the call the caller's stream has waited
 // for every stream.  Results are those of the serial order.
-int sppm_iterate(pm_sppm *s, int32_t n_iter, hipStream_t st) {
+int sppm_iterate(pm_sppm *s, int32_t n_iter, hipStream_t caller) {
     if (!s || n_iter < 0) return set_error("invalid handle or iteration count"), PM_ERR_ARG;
     if (!s->cell_count) return set_error("handle belongs to a batch: iterate the batch"), PM_ERR_STATE;
     if (n_iter == 0) return PM_OK;
     const uint32_t T = 1u << s->table_bits;
     const uint32_t ph_blocks = std::min<uint32_t>(blocks_for(s->cap), 256u * 64u);
     const bool count = (s->prm.profile & PM_PROFILE_COUNT) != 0, timed = (s->prm.profile & PM_PROFILE_TIME) != 0;
-    const bool pipe = s->store2 != nullptr;
+    const bool pipe = s->ring > 1;
     hipEvent_t *ev = s->prof_ev;
     const uint32_t k0 = (uint32_t)s->K;
     int rc;
-    // the two-phase pass's second launch runs on its own stream, so that the
-    // next pass's first launch can start beside it
-    hipStream_t tq = s->tails ? s->tails : s->phs;
-    // a pass in one launch of few paths a wave: the streams of the two
-    // launches take the passes of even and odd iterations
-    auto head_stream = [&](uint32_t kk) { return s->thin && (kk & 1u) ? tq : s->phs; };
-    auto tail_stream = [&](uint32_t kk) { return s->thin ? head_stream(kk) : tq; };
     auto eye_pass = [&](const SppmDev &dv, uint32_t kk, hipStream_t q) {
         if (count)
             hipLaunchKernelGGL(k_eye_stats, dim3(blocks_for(s->P)), dim3(kBlock), 0, q, dv, kk, 1);
         else
             hipLaunchKernelGGL(k_eye, dim3(blocks_for(s->P)), dim3(kBlock), 0, q, dv, kk, 1);
     };
-    if (pipe) {
-        // photon pass and eye pass of the first iteration, each on its stream
-        PM_HIP(hipEventRecord(s->ev_fork, st));
-        PM_HIP(hipStreamWaitEvent(s->phs, s->ev_fork, 0));
-        if (s->thin) PM_HIP(hipStreamWaitEvent(tq, s->ev_fork, 0));
-        PM_HIP(hipStreamWaitEvent(s->side, s->ev_fork, 0));
-        if ((rc = enqueue_photon(s, iteration_view(s, k0), k0, count, head_stream(k0), tail_stream(k0)))) return rc;
-        PM_HIP(hipEventRecord(s->ev_ph[k0 & 1u], tail_stream(k0)));
-        eye_pass(iteration_view(s, k0), k0, s->side);
-        PM_HIP(hipEventRecord(s->ev_eye[k0 & 1u], s->side));
-    }
+    // photon and eye pass of iteration k, once their slot's readers of ring
+    // iterations ago (the first `ring` of a call follow all earlier work) are done
+    auto ahead = [&](uint32_t kk) -> int {
+        const uint32_t i = kk % s->ring;
+        hipStream_t q = photon_queue(s, kk), eq = eye_queue(s, kk);
+        if (kk >= k0 + s->ring) {
+            PM_HIP(hipStreamWaitEvent(q, s->ev_scat[i], 0));
+            PM_HIP(hipStreamWaitEvent(eq, s->ev_upd[i], 0));
+        }
+        if (int e = enqueue_photon(s, iteration_view(s, kk), kk, count, q)) return e;
+        PM_HIP(hipEventRecord(s->ev_ph[i], q));
+        eye_pass(iteration_view(s, kk), kk, eq);
+        PM_HIP(hipEventRecord(s->ev_eye[i], eq));
+        return PM_OK;
+    };
+    uint32_t sent = k0;  // iterations whose photon and eye passes are enqueued
+    hipStream_t st = pipe ? work_stream(s, caller) : caller;
+    if (pipe) PM_HIP(fork_streams(s, k0, (uint32_t)n_iter, st, caller));
     for (int32_t it = 0; it < n_iter; ++it) {
         const uint32_t k = k0 + (uint32_t)it;
         const SppmDev dk = iteration_view(s, k);
-        if (pipe && it + 1 < n_iter) {
-            // the next photon pass refills the store (and queue) that the scatter of k - 1 read
-            hipStream_t hq = head_stream(k + 1u);
-            if (it >= 1) PM_HIP(hipStreamWaitEvent(hq, s->ev_scat[(k + 1u) & 1u], 0));
-            if ((rc = enqueue_photon(s, iteration_view(s, k + 1u), k + 1u, count, hq, tail_stream(k + 1u)))) return rc;
-            PM_HIP(hipEventRecord(s->ev_ph[(k + 1u) & 1u], tail_stream(k + 1u)));
-            // the next eye pass refills the hit points that the update of k - 1 read
-            if (it >= 1) PM_HIP(hipStreamWaitEvent(s->side, s->ev_upd[(k + 1u) & 1u], 0));
-            eye_pass(iteration_view(s, k + 1u), k + 1u, s->side);
-            PM_HIP(hipEventRecord(s->ev_eye[(k + 1u) & 1u], s->side));
-        }
+        for (; pipe && sent < k0 + (uint32_t)n_iter && sent < k + s->ring; ++sent)
+            if ((rc = ahead(sent))) return rc;
         if (timed) PM_HIP(hipEventRecord(ev[0], st));
         if (pipe) {
             // R_max over the radii after the update of k - 1 and the hit points of k
-            PM_HIP(hipStreamWaitEvent(st, s->ev_eye[k & 1u], 0));
+            PM_HIP(hipStreamWaitEvent(st, s->ev_eye[k % s->ring], 0));
             hipLaunchKernelGGL(k_rmax_clear, dim3(1), dim3(64), 0, st, dk);
             hipLaunchKernelGGL(k_rmax, dim3(std::min(blocks_for(s->P), kRmaxBlocks)), dim3(kBlock), 0, st, dk,
                                (const double *)s->R2);
         } else {
-            // eye pass and R_max on the side stream, beside the photon pass:
+            // eye pass and R_max on a second stream, beside the photon pass:
             // they share no data, and the eye pass's long specular paths would
             // otherwise leave the device idle at its end
+            hipStream_t side = s->streams.pass[1];
             PM_HIP(hipEventRecord(s->ev_fork, st));
-            PM_HIP(hipStreamWaitEvent(s->side, s->ev_fork, 0));
-            if (timed) PM_HIP(hipEventRecord(ev[1], s->side));
-            hipLaunchKernelGGL(k_rmax_clear, dim3(1), dim3(64), 0, s->side, dk);
-            eye_pass(dk, k, s->side);
-            hipLaunchKernelGGL(k_rmax, dim3(std::min(blocks_for(s->P), kRmaxBlocks)), dim3(kBlock), 0, s->side, dk,
+            PM_HIP(hipStreamWaitEvent(side, s->ev_fork, 0));
+            if (timed) PM_HIP(hipEventRecord(ev[1], side));
+            hipLaunchKernelGGL(k_rmax_clear, dim3(1), dim3(64), 0, side, dk);
+            eye_pass(dk, k, side);
+            hipLaunchKernelGGL(k_rmax, dim3(std::min(blocks_for(s->P), kRmaxBlocks)), dim3(kBlock), 0, side, dk,
                                (const double *)s->R2);
-            if (timed) PM_HIP(hipEventRecord(ev[2], s->side));
-            PM_HIP(hipEventRecord(s->ev_join, s->side));
+            if (timed) PM_HIP(hipEventRecord(ev[2], side));
+            PM_HIP(hipEventRecord(s->ev_join, side));
             if (timed) PM_HIP(hipEventRecord(ev[3], st));
-            if ((rc = enqueue_photon(s, dk, k, count, st, st))) return rc;
+            if ((rc = enqueue_photon(s, dk, k, count, st))) return rc;
             if (timed) PM_HIP(hipEventRecord(ev[4], st));
         }
         hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(T)), dim3(kBlock), 0, st, s->cell_count, T, 0u);
         if (!pipe) PM_HIP(hipStreamWaitEvent(st, s->ev_join, 0));
-        if (pipe) PM_HIP(hipStreamWaitEvent(st, s->ev_ph[k & 1u], 0));
+        if (pipe) PM_HIP(hipStreamWaitEvent(st, s->ev_ph[k % s->ring], 0));
         if (timed) PM_HIP(hipEventRecord(ev[5], st));
         if (dk.gather_mode == PM_GATHER_STOCHASTIC) {
             hipLaunchKernelGGL(k_sh_clear, dim3(std::min<uint32_t>(blocks_for(T), 4096u)), dim3(kBlock), 0, st, dk, T);
@@ -1184,13 +1288,13 @@ int sppm_iterate(pm_sppm *s, int32_t n_iter, hipStream_t st) {
             hipLaunchKernelGGL(k_sh_gather, dim3(blocks_for(s->P)), dim3(kBlock), 0, st, dk,
                                (const uint32_t *)s->cell_count);
             // this gather reads the photon store itself: only now may the pass of k + 2 refill it
-            if (pipe) PM_HIP(hipEventRecord(s->ev_scat[k & 1u], st));
+            if (pipe) PM_HIP(hipEventRecord(s->ev_scat[k % s->ring], st));
         } else {
             hipLaunchKernelGGL(k_count, dim3(ph_blocks), dim3(kBlock), 0, st, dk, s->cell_count);
             launch_bucket_scan(s->cell_count, s->cell_start, s->cell_fill, s->bsum, T, st);
             hipLaunchKernelGGL(k_scatter, dim3(ph_blocks), dim3(kBlock), 0, st, dk, (const uint32_t *)s->cell_start,
                                s->sorted);
-            if (pipe) PM_HIP(hipEventRecord(s->ev_scat[k & 1u], st));
+            if (pipe) PM_HIP(hipEventRecord(s->ev_scat[k % s->ring], st));
             if (timed) PM_HIP(hipEventRecord(ev[6], st));
             const int hits = hits_per_wave(s->P);
             auto gather = count        ? k_gather<64, true>
@@ -1203,7 +1307,7 @@ int sppm_iterate(pm_sppm *s, int32_t n_iter, hipStream_t st) {
         if (timed) PM_HIP(hipEventRecord(ev[7], st));
         double *hist = (int32_t)k < s->rec_iters ? s->R2_hist + (size_t)k * s->P : nullptr;
         hipLaunchKernelGGL(k_update, dim3(blocks_for(s->P)), dim3(kBlock), 0, st, dk, hist);
-        if (pipe) PM_HIP(hipEventRecord(s->ev_upd[k & 1u], st));
+        if (pipe) PM_HIP(hipEventRecord(s->ev_upd[k % s->ring], st));
         PM_HIP(hipGetLastError());
         if (timed) {  // wait for the iteration and add its stage times
             PM_HIP(hipEventRecord(ev[8], st));
@@ -1221,6 +1325,7 @@ int sppm_iterate(pm_sppm *s, int32_t n_iter, hipStream_t st) {
         if (count) s->prof_counted_iters++;
         s->K++;
     }
+    if (pipe) PM_HIP(join_streams(s, st, caller));
     return PM_OK;
 }
 
@@ -1277,10 +1382,10 @@ int sppm_resolve(pm_sppm *s, float *image, hipStream_t st) {
 
 int sppm_status(pm_sppm *s, hipStream_t st) {
     if (!s) return set_error("NULL handle"), PM_ERR_ARG;
-    uint32_t c[8];
+    uint32_t c[4 * kRing];
     PM_HIP(hipMemcpyAsync(c, s->counters, sizeof(c), hipMemcpyDeviceToHost, st));
     PM_HIP(hipStreamSynchronize(st));
-    const uint32_t flags = c[1] | c[5];  // the sticky flags of both photon stores' counter blocks
+    const uint32_t flags = c[1] | c[5] | c[9];  // the sticky flags of all slots
     if (flags & 1u) return set_error("photon store overflow: raise store_factor"), PM_ERR_OVERFLOW;
     if (flags & 2u)
         return set_error("flux fixed-point overflow (a term or a pixel's sum passed 2^64): lower fixed_shift"),
@@ -1292,91 +1397,80 @@ int sppm_status(pm_sppm *s, hipStream_t st) {
 // forward iteration: the replayed photon pass of k + 1 (with its flux
 // maximum) runs on the photon stream beside the grid, gather and path sums of
 // k, into the other photon store, (path, bounce) tables and maxima; the
-// replayed eye pass of k, R_max and the |G| wk maximum run on the side stream
+// replayed eye pass of k, R_max and the |G| wk maximum run on its eye stream
 // once iteration k - 1 is done with the hit points.  Every sum is an integer
 // sum, so the gradient equals the serial schedule's bit for bit.
-static int adjoint_overlapped(pm_sppm *s, const float *g, hipStream_t st) {
+static int adjoint_overlapped(pm_sppm *s, const float *g, hipStream_t caller) {
+    hipStream_t st = work_stream(s, caller);
     const uint32_t T = 1u << s->table_bits;
     const uint32_t np = (uint32_t)s->prm.n_photons;
     const int32_t mb = s->prm.max_photon_bounces;
     const uint32_t ph_blocks = std::min<uint32_t>(blocks_for(s->cap), 256u * 64u);
     const uint32_t K = (uint32_t)s->K;
     const double Kd = (double)s->K;
-    auto mat_of = [&](uint32_t k) { return (k & 1u) ? s->mat_tab2 : s->mat_tab; };
-    auto tab_of = [&](uint32_t k) { return (k & 1u) ? s->adj_tab2 : s->adj_tab; };
-    auto max_of = [&](uint32_t k) { return s->adj_max + 2 * (k & 1u); };
-    // the replayed photon pass: on the photon stream, or (two-phase handles)
-    // its first launch there and the second on the tail stream, beside the
-    // first launch of the next replay; the flux maximum follows the pass
-    const bool two = s->dev.photon_kernel == PM_PHOTON_TWO_PHASE && s->tails;
-    hipStream_t tails = two ? s->tails : s->phs;
+    auto mat_of = [&](uint32_t k) { return s->mat_tab[k % s->ring]; };
+    auto tab_of = [&](uint32_t k) { return s->adj_tab[k % s->ring]; };
+    auto max_of = [&](uint32_t k) { return s->adj_max + 2 * (k % s->ring); };
+    // the replayed photon pass on its iteration's photon stream; the flux maximum follows it
     auto replay = [&](uint32_t k) -> int {
         const SppmDev dk = iteration_view(s, k);
-        hipStream_t hq = s->thin && (k & 1u) ? s->tails : s->phs, tq = s->thin ? hq : tails;
-        hipLaunchKernelGGL(k_photon_begin, dim3(1), dim3(64), 0, hq, dk, s->thin ? np : 0u);
-        hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, hq, (uint32_t *)(max_of(k) + 1), 2u, 0u);
+        hipStream_t q = photon_queue(s, k);
+        if (k >= s->ring) PM_HIP(hipStreamWaitEvent(q, s->ev_scat[k % s->ring], 0));
+        hipLaunchKernelGGL(k_photon_begin, dim3(1), dim3(64), 0, q, dk, s->thin ? np : 0u);
+        hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, q, (uint32_t *)(max_of(k) + 1), 2u, 0u);
         if (s->thin) {
-            hipLaunchKernelGGL(k_photon<true>, dim3(blocks_for_waves(np, s->thin)), dim3(kBlock), 0, hq, dk, k, s->thin,
+            hipLaunchKernelGGL(k_photon<true>, dim3(blocks_for_waves(np, s->thin)), dim3(kBlock), 0, q, dk, k, s->thin,
                                mat_of(k), tab_of(k));
-        } else if (two) {
-            const PathQueue &pq = s->queue[k & 1u];
-            hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s->phs, pq.cnt, 1u, 0u);
-            hipLaunchKernelGGL(k_photon_head_rec, dim3(s->head_grid_rec), dim3(kBlock), 0, s->phs, dk, k, pq,
+        } else if (s->dev.photon_kernel == PM_PHOTON_TWO_PHASE) {
+            const PathQueue &pq = s->queue[k % s->ring];
+            hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, q, pq.cnt, 1u, 0u);
+            hipLaunchKernelGGL(k_photon_head_rec, dim3(s->head_grid_rec), dim3(kBlock), 0, q, dk, k, pq,
                                mat_of(k), tab_of(k));
-            PM_HIP(hipEventRecord(s->ev_head[k & 1u], s->phs));
-            PM_HIP(hipStreamWaitEvent(tq, s->ev_head[k & 1u], 0));
-            hipLaunchKernelGGL(k_photon_tail_rec, dim3(s->tail_grid_rec), dim3(kBlock), 0, tq, dk, pq, mat_of(k),
+            hipLaunchKernelGGL(k_photon_tail_rec, dim3(s->tail_grid_rec), dim3(kBlock), 0, q, dk, pq, mat_of(k),
                                tab_of(k));
         } else {
-            hipLaunchKernelGGL(k_photon_regen_rec, dim3(s->regen_grid_rec), dim3(kBlock), 0, s->phs, dk, k,
+            hipLaunchKernelGGL(k_photon_regen_rec, dim3(s->regen_grid_rec), dim3(kBlock), 0, q, dk, k,
                                mat_of(k), tab_of(k));
         }
-        hipLaunchKernelGGL(k_adj_phimax, dim3(std::min<uint32_t>(ph_blocks, kAdjMaxBlocks)), dim3(kBlock), 0, tq, dk,
+        hipLaunchKernelGGL(k_adj_phimax, dim3(std::min<uint32_t>(ph_blocks, kAdjMaxBlocks)), dim3(kBlock), 0, q, dk,
                            max_of(k));
         PM_HIP(hipGetLastError());
-        PM_HIP(hipEventRecord(s->ev_ph[k & 1u], tq));
+        PM_HIP(hipEventRecord(s->ev_ph[k % s->ring], q));
         return PM_OK;
     };
     // the replayed eye pass, R_max (over the recorded radii) and max |G| wk of
-    // iteration k, on the side stream, into the hit-point buffer, R_max
-    // accumulator and maxima of k's parity
+    // iteration k, on its eye stream, into the hit-point buffer, R_max
+    // accumulator and maxima of k's slot
     auto eye_chain = [&](uint32_t k) -> int {
         const SppmDev dk = iteration_view(s, k);
+        hipStream_t q = eye_queue(s, k);
         const double *R2k = s->R2_hist + (size_t)k * s->P;
-        hipLaunchKernelGGL(k_rmax_clear, dim3(1), dim3(64), 0, s->side, dk);
-        hipLaunchKernelGGL(k_eye, dim3(blocks_for(s->P)), dim3(kBlock), 0, s->side, dk, k, 0);
-        hipLaunchKernelGGL(k_rmax, dim3(std::min(blocks_for(s->P), kRmaxBlocks)), dim3(kBlock), 0, s->side, dk, R2k);
-        hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s->side, (uint32_t *)max_of(k), 2u, 0u);
+        if (k >= s->ring) PM_HIP(hipStreamWaitEvent(q, s->ev_upd[k % s->ring], 0));
+        hipLaunchKernelGGL(k_rmax_clear, dim3(1), dim3(64), 0, q, dk);
+        hipLaunchKernelGGL(k_eye, dim3(blocks_for(s->P)), dim3(kBlock), 0, q, dk, k, 0);
+        hipLaunchKernelGGL(k_rmax, dim3(std::min(blocks_for(s->P), kRmaxBlocks)), dim3(kBlock), 0, q, dk, R2k);
+        hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, q, (uint32_t *)max_of(k), 2u, 0u);
         hipLaunchKernelGGL(k_adj_gmax, dim3(std::min<uint32_t>(blocks_for(s->P), kAdjMaxBlocks)), dim3(kBlock), 0,
-                           s->side, dk, R2k, g, Kd, max_of(k));
+                           q, dk, R2k, g, Kd, max_of(k));
         PM_HIP(hipGetLastError());
-        PM_HIP(hipEventRecord(s->ev_eye[k & 1u], s->side));
+        PM_HIP(hipEventRecord(s->ev_eye[k % s->ring], q));
         return PM_OK;
     };
-    PM_HIP(hipEventRecord(s->ev_fork, st));
-    PM_HIP(hipStreamWaitEvent(s->phs, s->ev_fork, 0));
-    if (s->thin) PM_HIP(hipStreamWaitEvent(s->tails, s->ev_fork, 0));
-    PM_HIP(hipStreamWaitEvent(s->side, s->ev_fork, 0));
-    int rc = replay(0);
-    if (rc) return rc;
-    if ((rc = eye_chain(0))) return rc;
+    PM_HIP(fork_streams(s, 0u, K, st, caller));
+    uint32_t sent = 0;  // iterations whose replays are enqueued
     for (uint32_t k = 0; k < K; ++k) {
         const SppmDev dk = iteration_view(s, k);
         const double *R2k = s->R2_hist + (size_t)k * s->P;
-        if (k + 1 < K) {
-            // the replay of k + 1 reuses the store and tables that iteration k - 1 read
-            if (k >= 1)
-                PM_HIP(hipStreamWaitEvent(s->thin && (k + 1u) & 1u ? s->tails : s->phs, s->ev_scat[(k + 1u) & 1u], 0));
-            if ((rc = replay(k + 1))) return rc;
-            // and its eye pass the hit points, R_max and maxima that the range query of k - 1 read
-            if (k >= 1) PM_HIP(hipStreamWaitEvent(s->side, s->ev_upd[(k + 1u) & 1u], 0));
-            if ((rc = eye_chain(k + 1))) return rc;
+        // a replay reuses the slot (store, tables, hit points, maxima) that iteration k - ring read
+        for (; sent < K && sent < k + s->ring; ++sent) {
+            if (int rc = replay(sent)) return rc;
+            if (int rc = eye_chain(sent)) return rc;
         }
         hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(T)), dim3(kBlock), 0, st, s->cell_count, T, 0u);
         hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(4 * s->n_mat)), dim3(kBlock), 0, st, (uint32_t *)s->adj_wide,
                            (uint32_t)(4 * s->n_mat), 0u);
-        PM_HIP(hipStreamWaitEvent(st, s->ev_eye[k & 1u], 0));
-        PM_HIP(hipStreamWaitEvent(st, s->ev_ph[k & 1u], 0));
+        PM_HIP(hipStreamWaitEvent(st, s->ev_eye[k % s->ring], 0));
+        PM_HIP(hipStreamWaitEvent(st, s->ev_ph[k % s->ring], 0));
         hipLaunchKernelGGL(k_adj_scale, dim3(1), dim3(64), 0, st, (const unsigned long long *)max_of(k), s->adj_scale);
         hipLaunchKernelGGL(k_count, dim3(ph_blocks), dim3(kBlock), 0, st, dk, s->cell_count);
         launch_bucket_scan(s->cell_count, s->cell_start, s->cell_fill, s->bsum, T, st);
@@ -1385,14 +1479,15 @@ static int adjoint_overlapped(pm_sppm *s, const float *g, hipStream_t st) {
         hipLaunchKernelGGL(k_gather_adj, dim3(blocks_for(s->P)), dim3(kBlock), 0, st, dk, R2k,
                            (const uint32_t *)s->cell_start, (const float4 *)s->sorted, g, Kd,
                            (const double *)s->adj_scale, tab_of(k), s->n_mat, s->adj_wide);
-        PM_HIP(hipEventRecord(s->ev_upd[k & 1u], st));
+        PM_HIP(hipEventRecord(s->ev_upd[k % s->ring], st));
         hipLaunchKernelGGL(k_path_adj, dim3(blocks_for(np)), dim3(kBlock), 0, st, (const uint16_t *)mat_of(k),
                            (const long long *)tab_of(k), np, mb, s->n_mat, s->adj_wide);
-        PM_HIP(hipEventRecord(s->ev_scat[k & 1u], st));
+        PM_HIP(hipEventRecord(s->ev_scat[k % s->ring], st));
         hipLaunchKernelGGL(k_adj_fold, dim3(1), dim3(kMaxAdjMat), 0, st, (const unsigned long long *)s->adj_wide,
                            s->n_mat, (const double *)s->adj_scale, dk.sc.mat_rho, s->grad_mat);
         PM_HIP(hipGetLastError());
     }
+    PM_HIP(join_streams(s, st, caller));
     return PM_OK;
 }
 
@@ -1418,25 +1513,26 @@ int sppm_adjoint(pm_sppm *s, const float *g, const int32_t *pmat, int32_t n_par,
     for (int32_t i = 0; i < n_par; ++i) pms.m[i] = (uint8_t)pmat[i];
     hipLaunchKernelGGL(k_fill_f64, dim3(blocks_for(s->n_mat + 1)), dim3(kBlock), 0, st, s->grad_mat,
                        (int64_t)s->n_mat + 1);
-    if (s->adj_tab2) {
+    if (s->ring > 1) {
         int rc = adjoint_overlapped(s, g, st);
         if (rc) return rc;
     }
-    for (int32_t k = 0; k < (s->adj_tab2 ? 0 : s->K); ++k) {
+    for (int32_t k = 0; k < (s->ring > 1 ? 0 : s->K); ++k) {
         const double *R2k = s->R2_hist + (size_t)k * s->P;
         hipLaunchKernelGGL(k_begin, dim3(1), dim3(64), 0, st, d);
         hipLaunchKernelGGL(k_adj_begin, dim3(1), dim3(kBlock), 0, st, s->adj_max, s->adj_wide, s->n_mat);
         hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(T)), dim3(kBlock), 0, st, s->cell_count, T, 0u);
         // replayed eye pass, R_max and max |G| wk beside the replayed photon pass, as in the forward iteration
+        hipStream_t side = s->streams.pass[1];
         PM_HIP(hipEventRecord(s->ev_fork, st));
-        PM_HIP(hipStreamWaitEvent(s->side, s->ev_fork, 0));
-        hipLaunchKernelGGL(k_eye, dim3(blocks_for(s->P)), dim3(kBlock), 0, s->side, d, (uint32_t)k, 0);
-        hipLaunchKernelGGL(k_rmax, dim3(std::min(blocks_for(s->P), kRmaxBlocks)), dim3(kBlock), 0, s->side, d, R2k);
+        PM_HIP(hipStreamWaitEvent(side, s->ev_fork, 0));
+        hipLaunchKernelGGL(k_eye, dim3(blocks_for(s->P)), dim3(kBlock), 0, side, d, (uint32_t)k, 0);
+        hipLaunchKernelGGL(k_rmax, dim3(std::min(blocks_for(s->P), kRmaxBlocks)), dim3(kBlock), 0, side, d, R2k);
         hipLaunchKernelGGL(k_adj_gmax, dim3(std::min<uint32_t>(blocks_for(s->P), kAdjMaxBlocks)), dim3(kBlock), 0,
-                           s->side, d, R2k, g, K, s->adj_max);
-        PM_HIP(hipEventRecord(s->ev_join, s->side));
+                           side, d, R2k, g, K, s->adj_max);
+        PM_HIP(hipEventRecord(s->ev_join, side));
         hipLaunchKernelGGL(k_photon_regen_rec, dim3(s->regen_grid_rec), dim3(kBlock), 0, st, d, (uint32_t)k,
-                           s->mat_tab, s->adj_tab);
+                           s->mat_tab[0], s->adj_tab[0]);
         hipLaunchKernelGGL(k_adj_phimax, dim3(std::min<uint32_t>(ph_blocks, kAdjMaxBlocks)), dim3(kBlock), 0, st, d,
                            s->adj_max);
         PM_HIP(hipStreamWaitEvent(st, s->ev_join, 0));
@@ -1448,9 +1544,9 @@ int sppm_adjoint(pm_sppm *s, const float *g, const int32_t *pmat, int32_t n_par,
                            s->sorted);
         hipLaunchKernelGGL(k_gather_adj, dim3(blocks_for(s->P)), dim3(kBlock), 0, st, d, R2k,
                            (const uint32_t *)s->cell_start, (const float4 *)s->sorted, g, K,
-                           (const double *)s->adj_scale, s->adj_tab, s->n_mat, s->adj_wide);
-        hipLaunchKernelGGL(k_path_adj, dim3(blocks_for(np)), dim3(kBlock), 0, st, (const uint16_t *)s->mat_tab,
-                           (const long long *)s->adj_tab, np, mb, s->n_mat, s->adj_wide);
+                           (const double *)s->adj_scale, s->adj_tab[0], s->n_mat, s->adj_wide);
+        hipLaunchKernelGGL(k_path_adj, dim3(blocks_for(np)), dim3(kBlock), 0, st, (const uint16_t *)s->mat_tab[0],
+                           (const long long *)s->adj_tab[0], np, mb, s->n_mat, s->adj_wide);
         hipLaunchKernelGGL(k_adj_fold, dim3(1), dim3(kMaxAdjMat), 0, st, (const unsigned long long *)s->adj_wide,
                            s->n_mat, (const double *)s->adj_scale, d.sc.mat_rho, s->grad_mat);
         PM_HIP(hipGetLastError());
@@ -1533,9 +1629,9 @@ int sppm_save(pm_sppm *s, void *buf, uint64_t *size, hipStream_t st) {
         *size = need;
         return set_error("checkpoint buffer too small (the required size is returned in *size)"), PM_ERR_ARG;
     }
-    uint32_t c[8];
+    uint32_t c[4 * kRing];
     PM_HIP(hipMemcpyAsync(c, s->counters, sizeof(c), hipMemcpyDeviceToHost, st));
-    c[1] |= c[5];
+    c[1] |= c[5] | c[9];
     CheckpointHeader h{};
     memcpy(h.magic, "PMSPPMCK", 8);
     h.version = kCheckpointVersion;
@@ -1607,12 +1703,12 @@ int sppm_views(pm_sppm *s, pm_sppm_views *v) {
     v->R2 = s->R2;
     v->tau = s->tau;
     v->D = s->D;
-    // the last iteration's hit points, photon store and counters (a pipelined handle alternates two of each)
-    const uint32_t par = (s->store2 && s->K > 0) ? (uint32_t)((s->K - 1) & 1) : 0u;
-    v->hp_pos = (float *)(par ? s->hp_pos2 : s->hp_pos);
-    v->hp_nrm = (float *)(par ? s->hp_nrm2 : s->hp_nrm);
-    v->photons = (float *)(par ? s->store2 : s->store);
-    v->photon_count = s->counters + 4 * par;
+    // the last iteration's hit points, photon store and counters
+    const uint32_t i = s->K > 0 ? (uint32_t)(s->K - 1) % s->ring : 0u;
+    v->hp_pos = (float *)s->hp_pos[i];
+    v->hp_nrm = (float *)s->hp_nrm[i];
+    v->photons = (float *)s->store[i];
+    v->photon_count = s->counters + 4 * i;
     v->gather_M = s->M;
     v->gather_Phi = (uint64_t *)s->Phi;
     return PM_OK;

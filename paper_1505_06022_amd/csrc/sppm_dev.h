@@ -52,6 +52,7 @@ struct SppmDev {
     double *N, *R2, *tau, *D;
     float4 *store;            // [cap][2]: (x, phi), (w, path << 5 | bounce)
     uint2 *key_rank;          // [cap] exact gather: each stored photon's bucket and its rank in the bucket
+    double *emit;             // [P] emission seen directly by this iteration's eye paths
     uint32_t *counters;       // [0] photons stored, [1] sticky flags (1: store overflow, 2: flux overflow), [2] next path
     unsigned long long *r2max;
     uint32_t *M;
@@ -130,11 +131,12 @@ __device__ __forceinline__ int32_t wave_closest_hit(const SppmDev &d, uint32_t *
 // ---------------------------------------------------------------------------
 // Eye pass: a jittered pinhole ray followed through mirror and glass to the
 // first diffuse (rho > 0) surface, which becomes the pixel's hit point;
-// directly seen emission is accumulated into D (skipped when replaying).
+// directly seen emission goes to d.emit for the update to add to D (skipped when
+// replaying): eye passes of several iterations may run at once.
 // Called by all lanes of a wave; active: this lane has pixel p.
 // ---------------------------------------------------------------------------
 template <bool kStats = false>
-__device__ __forceinline__ void eye_elem(const SppmDev &d, uint32_t k, int64_t p, bool active, bool accumulate_D,
+__device__ __forceinline__ void eye_elem(const SppmDev &d, uint32_t k, int64_t p, bool active, bool emission,
                                          uint32_t *stk, LaneStats *ls = nullptr) {
     const SceneDev &sc = d.sc;
     Rng g{1, 1, 1, 1};
@@ -194,7 +196,7 @@ __device__ __forceinline__ void eye_elem(const SppmDev &d, uint32_t k, int64_t p
     if (!active) return;
     d.hp_pos[p] = pos;
     d.hp_nrm[p] = nrm;
-    if (accumulate_D) d.D[p] += dadd;
+    if (emission) d.emit[p] = dadd;
     if (kStats) {
         ls->paths++;
         ls->boxes += st.boxes;
@@ -1291,6 +1293,7 @@ __device__ __forceinline__ void gather_wave(const SppmDev &d, const Grid &gr, in
 // (optional) receives the radius used in this iteration.
 __device__ __forceinline__ void update_elem(const SppmDev &d, int64_t p, double *__restrict__ hist) {
     if (hist) hist[p] = d.R2[p];
+    d.D[p] += d.emit[p];
     uint32_t Mi = d.M[p];
     if (__float_as_int(d.hp_nrm[p].w) < 0 || Mi == 0) return;
     double m = (double)Mi;

@@ -8,6 +8,14 @@
 #include "runtime.h"
 #include "sppm_dev.h"
 
+// Iterations of a pipelined handle that may be under way at once.
+constexpr uint32_t kRing = 3;
+
+// The streams of a handle.
+struct PassStreams {
+    hipStream_t pass[kRing] = {}, main = nullptr;
+};
+
 struct pm_sppm {
     pm_sppm_params prm{};
     pm_bvh *bvh = nullptr;
@@ -34,27 +42,26 @@ struct pm_sppm {
     uint32_t *emit_pos = nullptr;
     double *emit_cdf = nullptr;
     double *N = nullptr, *R2 = nullptr, *tau = nullptr, *D = nullptr;
-    float4 *hp_pos = nullptr, *hp_nrm = nullptr;
-    float4 *store = nullptr, *sorted = nullptr;
-    // pipelined handles: a second photon store, the stream the photon passes
-    // run on, and events per store (photon pass done, scatter done)
-    float4 *store2 = nullptr;
-    hipStream_t phs = nullptr;
-    hipEvent_t ev_ph[2] = {}, ev_scat[2] = {};
-    // two-phase photon pass (PM_PHOTON_TWO_PHASE): a queue per store parity
-    // for the paths set aside by the first launch; on a pipelined handle the
-    // second launch runs on its own stream after the first (event ev_head)
+    // what iteration k writes before its grid is built lies in slot k % ring of
+    // ring slots (1: an iteration at a time): hit points, emission, photon store, its block
+    // of counters, R_max, the paths set aside and the adjoint's tables
+    uint32_t ring = 1;
+    float4 *hp_pos[kRing] = {}, *hp_nrm[kRing] = {};
+    double *emit[kRing] = {};
+    float4 *store[kRing] = {}, *sorted = nullptr;
+    // streams beside the caller's (default priority), forked from and joined to
+    // it by events: see photon_queue and eye_queue; events per slot: photon pass
+    // done, eye pass done, photon store read, hit points read
+    PassStreams streams;
+    int device = 0;
+    hipEvent_t ev_ph[kRing] = {}, ev_eye[kRing] = {}, ev_scat[kRing] = {}, ev_upd[kRing] = {};
+    hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+    // two-phase photon pass (PM_PHOTON_TWO_PHASE): queues for the paths set
+    // aside by the first launch
     void *queue_mem = nullptr;
-    // a second hit-point buffer (pipelined handles): the eye pass of k + 1
-    // writes it while the range query and update of k read the first; events
-    // per buffer: eye pass done, update done
-    float4 *hp_pos2 = nullptr, *hp_nrm2 = nullptr;
-    hipEvent_t ev_eye[2] = {}, ev_upd[2] = {};
-    pmd::PathQueue queue[2] = {};
-    hipStream_t tails = nullptr;
-    hipEvent_t ev_head[2] = {};
+    pmd::PathQueue queue[kRing] = {};
     uint2 *key_rank = nullptr;  // exact gather: [cap] bucket and rank of each stored photon
-    uint32_t *counters = nullptr;  // [8]: per photon store [0] photons stored, [1] sticky flags, [2] next path, [3] pass leftovers
+    uint32_t *counters = nullptr;  // [kRing][4]: per photon store [0] photons stored, [1] sticky flags, [2] next path, [3] pass leftovers
     unsigned long long *r2max = nullptr;
     // bucket arrays (absent for a batch member, which uses the batch's)
     uint32_t *cell_count = nullptr, *cell_start = nullptr, *cell_fill = nullptr, *bsum = nullptr;
@@ -66,22 +73,15 @@ struct pm_sppm {
     std::vector<float> rho_host;  // albedos (validation of adjoint parameters)
     double le_single = 0.0;  // Le of the single emitting material, 0 if not exactly one
     double *R2_hist = nullptr;    // [rec_iters][P] radius used in each iteration
-    long long *adj_tab = nullptr;  // [n_photons][max_bounces] photon sensitivities (fixed point, see adj_*)
-    uint16_t *mat_tab = nullptr;   // [n_photons][max_bounces] stored-photon materials
-    // second copies for odd iterations when the adjoint overlaps iterations (with store2)
-    long long *adj_tab2 = nullptr;
-    uint16_t *mat_tab2 = nullptr;
+    long long *adj_tab[kRing] = {};  // [n_photons][max_bounces] photon sensitivities (fixed point, see adj_*)
+    uint16_t *mat_tab[kRing] = {};   // [n_photons][max_bounces] stored-photon materials
     double *grad_mat = nullptr;    // [n_mat + 1]; last entry: sum g L
     unsigned long long *adj_wide = nullptr;  // [2][n_mat] per-material integer sums of one iteration (lo | hi)
-    unsigned long long *adj_max = nullptr;   // [2][2] per iteration parity: max |G| wk over hit points, max
+    unsigned long long *adj_max = nullptr;   // [kRing][2] per slot: max |G| wk over hit points, max
                                              // flux over photons (double bits)
     double *adj_scale = nullptr;             // [1] fixed-point scale of the current iteration
     double *le_part = nullptr;               // [blocks over pixels] partial sums of g L
     uint64_t scene_hash = 0;      // fingerprint of the scene description (checkpoint matching)
-    // the eye pass runs beside the photon pass on a second stream (default
-    // priority), forked from and joined back to the caller's stream by events
-    hipStream_t side = nullptr;
-    hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     unsigned long long *sh_key = nullptr;  // stochastic hashing (gather_mode 1): [T] keys
     uint32_t *sh_surv = nullptr;           // and [T] survivors
     // one-bounce-per-pass photon schedule (PM_PHOTON_PASSES): path slots and
