@@ -396,6 +396,14 @@ __global__ void k_adj_scale(const unsigned long long *__restrict__ adj_max, doub
     }
 }
 
+// The adjoint's range query, bound by its chain of reads and by the additions
+// to the photons' table entries.  On small images it is split over lanes and
+// waves like the forward one (gather_wave): a hit point whose buckets hold many
+// photons is scanned by its whole wave, 320x180 with 2^16 photons 187 -> 114 us
+// an iteration.  With 64 hit points a wave every lane scans its own: at 1280x720
+// with 2^20 photons the whole-wave scans, 23 more registers and the additions
+// of a wave to few entries at once made it 908 us instead of 701.
+template <int kHits>
 __global__ __launch_bounds__(kBlock) void k_gather_adj(SppmDev d, const double *__restrict__ R2k,
                                                        const uint32_t *__restrict__ start,
                                                        const float4 *__restrict__ sorted, const float *__restrict__ g,
@@ -405,27 +413,63 @@ __global__ __launch_bounds__(kBlock) void k_gather_adj(SppmDev d, const double *
     __shared__ WideLds lds;
     wide_clear(lds, n_mat);
     const double scale = *scale_p;
-    int64_t p = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
-    float4 hn = p < d.P ? d.hp_nrm[p] : make_float4(0.0f, 0.0f, 0.0f, __int_as_float(-1));
-    if (__float_as_int(hn.w) >= 0 && g[p] != 0.0f && scale > 0.0) {
-        float4 hx = d.hp_pos[p];
-        double r2 = R2k[p];
-        double G = adj_G(g, p, r2, K);
-        Grid gr = make_grid(d);
-        double wk = (double)hx.w;
+    const uint32_t lane = threadIdx.x & 63u;
+    const int64_t p = wave_index() * kHits + lane;
+    const bool in = p < d.P && lane < (uint32_t)kHits;
+    const float4 hn = in ? d.hp_nrm[p] : make_float4(0.0f, 0.0f, 0.0f, __int_as_float(-1));
+    const bool valid = __float_as_int(hn.w) >= 0 && g[p] != 0.0f && scale > 0.0;
+    const Grid gr = make_grid(d);
+    const int32_t mb = d.max_bounces;
+    float4 hx = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    double r2 = 0.0, G = 0.0;
+    DiscCells dc{};
+    uint32_t load = 0u;
+    if (valid) {
+        hx = d.hp_pos[p];
+        r2 = R2k[p];
+        G = adj_G(g, p, r2, K);
+        dc = disc_cells(gr, hx, r2);
+        if (kHits < 64) load = disc_load(d, gr, dc, start);
+    }
+    // one photon's term of a hit point: to the photon's entry, and returned
+    auto term = [&](double Gp, double wk, const float4 &a, const float4 &b) {
+        const double cc = wk * (double)a.w;
+        const long long q = __double2ll_rn((Gp * cc) * scale);
+        const uint32_t meta = __float_as_uint(b.w);
+        if (q) atomicAdd((unsigned long long *)&adj_tab[(size_t)(meta >> 5) * mb + (meta & 31u)], (unsigned long long)q);
+        return q;
+    };
+    const bool coop = kHits < 64 && load >= coop_min(kHits);
+    if (valid && !coop) {
+        const double wk = (double)hx.w;
         i128 own = 0;
-        const int32_t mb = d.max_bounces;
-        for_each_photon_in_disc(d, gr, hx, hn, r2, start, sorted, [&](const float4 &a, const float4 &b) {
-            double cc = wk * (double)a.w;
-            long long q = __double2ll_rn((G * cc) * scale);
-            uint32_t meta = __float_as_uint(b.w);
-            if (q) atomicAdd((unsigned long long *)&adj_tab[(size_t)(meta >> 5) * mb + (meta & 31u)],
-                             (unsigned long long)q);
-            own += q;
-        });
+        auto add = [&](const float4 &a, const float4 &b) { own += term(G, wk, a, b); };
+        for (uint32_t m = dc.uniq; m != 0u; m &= m - 1u)
+            photons_of_bucket(d, disc_cell_bucket(gr, dc.c0, __builtin_ctz(m)), hx, hn, r2, start, sorted, add);
         if (own != 0) wide_add(&lds.lo[__float_as_uint(hn.w)], &lds.hi[__float_as_uint(hn.w)], own);
     }
+    for (uint64_t todo = kHits < 64 ? __ballot(coop) : 0ull; todo != 0ull; todo &= todo - 1ull) {
+        const int L = __ffsll((unsigned long long)todo) - 1;
+        const double wk = (double)readlane_f(hx.w, L), Gp = readlane_d(G, L);
+        i128 own = 0;
+        wave_scan(d, gr, L, hx, hn, r2, dc, start, sorted,
+                  [&](const float4 &a, const float4 &b) { own += term(Gp, wk, a, b); });
+        // the lanes' sums, in the two parts that wide_add adds
+        unsigned long long lo = (unsigned long long)(uint32_t)(uint64_t)own, hi = (unsigned long long)(long long)(own >> 32);
+        for (int off = 32; off > 0; off >>= 1) {
+            lo += __shfl_xor(lo, off);
+            hi += __shfl_xor(hi, off);
+        }
+        if ((int)lane == L && (lo | hi) != 0ull) {
+            atomicAdd(&lds.lo[__float_as_uint(hn.w)], lo);
+            atomicAdd(&lds.hi[__float_as_uint(hn.w)], hi);
+        }
+    }
     wide_flush(lds, n_mat, wide);
+}
+
+inline auto gather_adj_of(int hits) {
+    return hits == 64 ? k_gather_adj<64> : (hits == 16 ? k_gather_adj<16> : k_gather_adj<4>);
 }
 
 __global__ __launch_bounds__(kBlock) void k_path_adj(const uint16_t *__restrict__ mat_tab,
@@ -1410,6 +1454,7 @@ static int adjoint_overlapped(pm_sppm *s, const float *g, hipStream_t caller) {
     const double Kd = (double)s->K;
     auto mat_of = [&](uint32_t k) { return s->mat_tab[k % s->ring]; };
     auto tab_of = [&](uint32_t k) { return s->adj_tab[k % s->ring]; };
+    const int hits = hits_per_wave(s->P);
     auto max_of = [&](uint32_t k) { return s->adj_max + 2 * (k % s->ring); };
     // the replayed photon pass on its iteration's photon stream; the flux maximum follows it
     auto replay = [&](uint32_t k) -> int {
@@ -1476,7 +1521,7 @@ static int adjoint_overlapped(pm_sppm *s, const float *g, hipStream_t caller) {
         launch_bucket_scan(s->cell_count, s->cell_start, s->cell_fill, s->bsum, T, st);
         hipLaunchKernelGGL(k_scatter, dim3(ph_blocks), dim3(kBlock), 0, st, dk, (const uint32_t *)s->cell_start,
                            s->sorted);
-        hipLaunchKernelGGL(k_gather_adj, dim3(blocks_for(s->P)), dim3(kBlock), 0, st, dk, R2k,
+        hipLaunchKernelGGL(gather_adj_of(hits), dim3(blocks_for(s->P * (64 / hits))), dim3(kBlock), 0, st, dk, R2k,
                            (const uint32_t *)s->cell_start, (const float4 *)s->sorted, g, Kd,
                            (const double *)s->adj_scale, tab_of(k), s->n_mat, s->adj_wide);
         PM_HIP(hipEventRecord(s->ev_upd[k % s->ring], st));
@@ -1509,6 +1554,7 @@ int sppm_adjoint(pm_sppm *s, const float *g, const int32_t *pmat, int32_t n_par,
     const uint32_t ph_blocks = std::min<uint32_t>(blocks_for(s->cap), 256u * 64u);
     const double K = (double)s->K;
     const SppmDev &d = s->dev;
+    const int hits = hits_per_wave(s->P);
     ParamMats pms;
     for (int32_t i = 0; i < n_par; ++i) pms.m[i] = (uint8_t)pmat[i];
     hipLaunchKernelGGL(k_fill_f64, dim3(blocks_for(s->n_mat + 1)), dim3(kBlock), 0, st, s->grad_mat,
@@ -1542,7 +1588,7 @@ int sppm_adjoint(pm_sppm *s, const float *g, const int32_t *pmat, int32_t n_par,
         launch_bucket_scan(s->cell_count, s->cell_start, s->cell_fill, s->bsum, T, st);
         hipLaunchKernelGGL(k_scatter, dim3(ph_blocks), dim3(kBlock), 0, st, d, (const uint32_t *)s->cell_start,
                            s->sorted);
-        hipLaunchKernelGGL(k_gather_adj, dim3(blocks_for(s->P)), dim3(kBlock), 0, st, d, R2k,
+        hipLaunchKernelGGL(gather_adj_of(hits), dim3(blocks_for(s->P * (64 / hits))), dim3(kBlock), 0, st, d, R2k,
                            (const uint32_t *)s->cell_start, (const float4 *)s->sorted, g, K,
                            (const double *)s->adj_scale, s->adj_tab[0], s->n_mat, s->adj_wide);
         hipLaunchKernelGGL(k_path_adj, dim3(blocks_for(np)), dim3(kBlock), 0, st, (const uint16_t *)s->mat_tab[0],

@@ -1001,17 +1001,6 @@ __device__ __forceinline__ DiscCells disc_cells(const Grid &gr, float4 hx, doubl
     return dc;
 }
 
-// Visit every photon inside a hit point's disc that arrived from the eye's
-// side, through the distinct buckets of the cells its disc can reach.
-template <typename F>
-__device__ __forceinline__ void for_each_photon_in_disc(const SppmDev &d, const Grid &gr, float4 hx, float4 hn, double r2,
-                                                       const uint32_t *__restrict__ start,
-                                                       const float4 *__restrict__ sorted, F &&f) {
-    const DiscCells dc = disc_cells(gr, hx, r2);
-    for (uint32_t m = dc.uniq; m != 0u; m &= m - 1u)
-        photons_of_bucket(d, disc_cell_bucket(gr, dc.c0, __builtin_ctz(m)), hx, hn, r2, start, sorted, f);
-}
-
 // Adds n fixed-point flux terms rint(v) to F; `bad` is set when a term or the
 // sum leaves the range of u64 (the sum itself stays the sum modulo 2^64).
 __device__ __forceinline__ void flux_add(unsigned long long &F, double v, uint32_t n, bool &bad) {
