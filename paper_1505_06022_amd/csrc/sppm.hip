@@ -776,40 +776,82 @@ class Arena {
     size_t size_ = 0;
 };
 
-// scene_fingerprint is one serial chain of multiplications (2.1 ms for 250,000
-// triangles, against 0.3 ms for the rest of a handle), so large scenes have it
-// on a thread beside the allocations and uploads: create 2.9 -> 2.2 ms.  Below
-// kHashThread triangles it takes no longer than starting a thread (about 50 us).
-// get() waits for it: the description is not read after the call returns.
-class FingerprintTask {
+// 64-bit fingerprint of everything in a scene description that the render reads
+// (FNV-1a over 32-bit words).  The triangles' words are one serial chain of
+// multiplications, 8.4 us for 1,000 triangles on the host.  From kHashThread
+// triangles on a thread runs it beside the creation of the handle (0.3 ms without
+// it); from kDeviceHash on the device does, in less time than the chain takes
+// there: creating the handle of 250,000 triangles went from 2.16 ms (with the
+// thread) to 0.8, while for 13,600 the device takes longer (0.41 ms instead of
+// 0.25).  The description is not read after finish().
+class SceneFingerprint {
   public:
-    static constexpr int64_t kHashThread = 8192;
-    explicit FingerprintTask(const pm_scene_desc *d) : d_(d) {
-        if (d->n_tri < kHashThread) return;
-        try {
-            thread_ = std::thread([this] { hash_ = scene_fingerprint(d_); });
-        } catch (const std::system_error &) {  // no thread to be had: get() computes it
-        }
-    }
-    ~FingerprintTask() {
+    static constexpr int64_t kHashThread = 8192, kDeviceHash = 1 << 15;
+    ~SceneFingerprint() {
         if (thread_.joinable()) thread_.join();
     }
-    uint64_t get() {
-        if (!thread_.joinable()) return scene_fingerprint(d_);
-        thread_.join();
-        return hash_;
+    int launch(const pm_scene_desc *d, hipStream_t st) {
+        d_ = d;
+        add(&d->n_tri, sizeof(d->n_tri));
+        const size_t nt = (size_t)d->n_tri;
+        device_ = d->n_tri >= kDeviceHash && d->n_tri < (int64_t(1) << 28);
+        if (device_) return hash_.launch(h_, d->tri_verts, 9 * nt, d->tri_mat, nt, st);
+        if (d->n_tri >= kHashThread) try {
+                thread_ = std::thread([this] { triangles(); });
+            } catch (const std::system_error &) {  // no thread to be had: finish() does it
+            }
+        return PM_OK;
+    }
+    int finish(uint64_t &out, hipStream_t st) {
+        if (device_) {
+            if (int rc = hash_.finish(h_, st)) return rc;
+        } else if (thread_.joinable()) {
+            thread_.join();
+        } else {
+            triangles();
+        }
+        const size_t nm = (size_t)d_->n_mat;
+        add(&d_->n_mat, sizeof(d_->n_mat));
+        add(d_->mat_type, sizeof(int32_t) * nm);
+        add(d_->mat_rho, sizeof(float) * nm);
+        add(d_->mat_q, sizeof(float) * nm);
+        add(d_->mat_Le, sizeof(float) * nm);
+        add(d_->mat_ior, sizeof(float) * nm);
+        add(d_->cam_pos, sizeof(d_->cam_pos));
+        add(d_->cam_look, sizeof(d_->cam_look));
+        add(d_->cam_up, sizeof(d_->cam_up));
+        add(&d_->tan_half_fov, sizeof(d_->tan_half_fov));
+        add(&d_->width, sizeof(d_->width));
+        add(&d_->height, sizeof(d_->height));
+        out = h_;
+        return PM_OK;
     }
 
   private:
-    const pm_scene_desc *d_;
-    uint64_t hash_ = 0;
+    void triangles() {
+        add(d_->tri_verts, sizeof(float) * 9 * (size_t)d_->n_tri);
+        add(d_->tri_mat, sizeof(uint32_t) * (size_t)d_->n_tri);
+    }
+    void add(const void *p, size_t bytes) {  // whole words
+        const uint8_t *b = (const uint8_t *)p;
+        for (size_t i = 0; i + 4 <= bytes; i += 4) {
+            uint32_t w;
+            memcpy(&w, b + i, 4);
+            h_ = (h_ ^ w) * kHashPrime;
+        }
+    }
+    const pm_scene_desc *d_ = nullptr;
+    uint64_t h_ = 0xcbf29ce484222325ull;
+    bool device_ = false;
+    DeviceHash hash_;
     std::thread thread_;
 };
 
 int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t st, bool own_grid, pm_sppm **out) {
     int rc = sppm_validate(d, p);
     if (rc) return rc;
-    FingerprintTask fingerprint(d);
+    SceneFingerprint fingerprint;
+    if ((rc = fingerprint.launch(d, st))) return rc;
     pm_sppm *s = new pm_sppm();
     s->prm = *p;
     auto fail = [&](int code) {
@@ -1102,9 +1144,9 @@ int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t 
     dv.stats = s->stats;
     hipLaunchKernelGGL(k_init_state, dim3(blocks_for(s->P)), dim3(kBlock), 0, st, dv, p->r0 * p->r0);
     PM_HIPF(hipGetLastError());
+    if ((rc = fingerprint.finish(s->scene_hash, st))) return fail(rc);
     // host staging vectors go out of scope: finish the copies first
     PM_HIPF(hipStreamSynchronize(st));
-    s->scene_hash = fingerprint.get();
 #undef PM_HIPF
     *out = s;
     return PM_OK;
@@ -1608,19 +1650,6 @@ int sppm_adjoint(pm_sppm *s, const float *g, const int32_t *pmat, int32_t n_par,
 
 namespace {
 
-struct HashWords {  // FNV-1a over 32-bit words
-    uint64_t h = 0xcbf29ce484222325ull;
-    void add(const void *p, size_t bytes) {
-        const uint8_t *b = (const uint8_t *)p;
-        for (size_t i = 0; i + 4 <= bytes; i += 4) {
-            uint32_t w;
-            memcpy(&w, b + i, 4);
-            h = (h ^ w) * 0x100000001b3ull;
-        }
-        for (size_t i = bytes & ~(size_t)3; i < bytes; ++i) h = (h ^ b[i]) * 0x100000001b3ull;
-    }
-};
-
 // Checkpoint layout: this header, then N, R2, tau, D (f64 [P] each), then
 // n_hist recorded radii (f64 [n_hist][P]).
 struct CheckpointHeader {
@@ -1641,26 +1670,6 @@ uint64_t checkpoint_bytes(const pm_sppm *s, int32_t n_hist) {
 }
 
 }  // namespace
-
-uint64_t scene_fingerprint(const pm_scene_desc *d) {
-    HashWords h;
-    h.add(&d->n_tri, sizeof(d->n_tri));
-    h.add(d->tri_verts, sizeof(float) * 9 * (size_t)d->n_tri);
-    h.add(d->tri_mat, sizeof(uint32_t) * (size_t)d->n_tri);
-    h.add(&d->n_mat, sizeof(d->n_mat));
-    h.add(d->mat_type, sizeof(int32_t) * (size_t)d->n_mat);
-    h.add(d->mat_rho, sizeof(float) * (size_t)d->n_mat);
-    h.add(d->mat_q, sizeof(float) * (size_t)d->n_mat);
-    h.add(d->mat_Le, sizeof(float) * (size_t)d->n_mat);
-    h.add(d->mat_ior, sizeof(float) * (size_t)d->n_mat);
-    h.add(d->cam_pos, sizeof(d->cam_pos));
-    h.add(d->cam_look, sizeof(d->cam_look));
-    h.add(d->cam_up, sizeof(d->cam_up));
-    h.add(&d->tan_half_fov, sizeof(d->tan_half_fov));
-    h.add(&d->width, sizeof(d->width));
-    h.add(&d->height, sizeof(d->height));
-    return h.h;
-}
 
 int sppm_save(pm_sppm *s, void *buf, uint64_t *size, hipStream_t st) {
     if (!s || !size) return set_error("NULL handle or size pointer"), PM_ERR_ARG;

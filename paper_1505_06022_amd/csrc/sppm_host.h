@@ -105,7 +105,24 @@ int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t 
 void sppm_free(pm_sppm *s);
 // Back to the initial state (N = 0, R^2 = r0^2, tau = 0, D = 0, K = 0).
 int sppm_reset(pm_sppm *s, hipStream_t st);
-// 64-bit fingerprint of everything in a scene description that the render reads.
-uint64_t scene_fingerprint(const pm_scene_desc *d);
+
+constexpr uint64_t kHashPrime = 0x100000001b3ull;
+
+// The hash h = (h ^ w) kHashPrime over the words a[0 .. words_a), b[0 .. words_b)
+// (at least one, below 2^32 together) from the state h: launch() uploads them and
+// enqueues the work on st, finish() waits for it and gives the final state.
+class DeviceHash {
+  public:
+    DeviceHash() = default;
+    DeviceHash(const DeviceHash &) = delete;
+    ~DeviceHash();
+    int launch(uint64_t h, const void *a, size_t words_a, const void *b, size_t words_b, hipStream_t st);
+    int finish(uint64_t &h, hipStream_t st);
+
+  private:
+    void *mem_ = nullptr;
+    uint64_t h_ = 0;
+    uint32_t n_ = 0, seg_ = 0, n_seg_ = 0;
+};
 
 }  // namespace pm
