@@ -94,8 +94,10 @@ __device__ __forceinline__ int ray_set(const SppmDev &d, V3 dir) {
 
 // Words of a wave's stack in LDS for the wide walk.
 constexpr int kStackWords = 64 * kWideStack;
-// The wide walk's threshold for held leaf tests in the SPPM passes.
-constexpr uint32_t kSppmLate = 24;
+// The wide walk's threshold for held leaf tests in the SPPM passes (8 iterations
+// at 1280x720 with 2^20 photons, a refill of 16 lanes: 8.66 ms with 8, 8.50 with
+// 12, 8.46 with 16, 8.7 with 24).
+constexpr uint32_t kSppmLate = 16;
 // Wavefronts per SIMD that the kernels with a path and a walk ask for: at most
 // 128 registers.  At 5 (96 registers) up to 27 of them spill: 7.2 against 6.3
 // ms for a 333x187 render, 9.6 and 9.7 for 8 iterations at 1280x720; at 6
