@@ -4,12 +4,11 @@ Default workload (the traversal-only configuration): 2^20 random triangles
 (centroids uniform in the unit cube, lognormal(-5, 0.5) vertex offsets),
 SAH-binned BVH (32 bins, <= 4 triangles per leaf), 1920x1080 coherent pinhole
 rays plus 2^21 incoherent rays.  One step = closest-hit traversal of all
-4,170,752 rays: two trace calls, inputs resident in HBM.  The camera batch is
-traced as packets, one wavefront per 8x8 pixel tile (--coherent), the
-incoherent batch after bucketing by (origin cell, link set) with postponed
-leaf tests (--incoherent); every
+4,170,752 rays, inputs resident in HBM.  The camera batch is traced in 8x8 pixel
+tiles, one per wavefront (--coherent), the incoherent batch after bucketing by
+(origin cell, link set) (--incoherent), both through the four-child nodes; every
 option listed in KERNEL_VARIANTS gives identical results and is also timed.
-The JSON line reports Mrays/s, the traversal's algorithmic-bytes roofline,
+The JSON line reports Mrays/s, the traversal's bytes against the memory roofline,
 the CPU oracle timed on the host, the SPPM iteration on the 250k-triangle
 procedural scene, the adjoint-to-forward time ratio and the batched renderer.
 
@@ -28,7 +27,7 @@ import numpy as np
 HBM_PEAK_GBS = 8000.0
 ROOT = os.path.dirname(os.path.abspath(__file__))
 TRACE_SOURCES = ["paper_1505_06022_amd/csrc/pm_device.h", "paper_1505_06022_amd/csrc/trace.hip",
-                 "paper_1505_06022_amd/csrc/bvh_build.cpp"]
+                 "paper_1505_06022_amd/csrc/wide.hip", "paper_1505_06022_amd/csrc/bvh_build.cpp"]
 
 
 # Traversal options compared by the bench (names usable with --coherent/--incoherent)
@@ -226,7 +225,8 @@ def traversal_bench(args, torch, api, scenes):
         c = cnt.to(torch.float64).sum(0).cpu().numpy()
         per_batch.append((c[0], c[1], len(r)))
     torch.cuda.synchronize()
-    # per ray: 32 B ray + 8 B result + 16 B per node visited + 48 B per triangle tested
+    # per ray: 32 B ray + 8 B result + 16 B per node visited + 48 B per triangle tested, as the stackless walk
+    # of the binary tree counts them (the four-child walk visits fewer nodes and does not count)
     alg_bytes = sum(40.0 * n + 16.0 * vn + 48.0 * vt for vn, vt, n in per_batch)
 
     # one step = one pm_trace_rays_multi call: the incoherent batch is bucketed, then one launch walks it
@@ -275,23 +275,23 @@ def traversal_bench(args, torch, api, scenes):
         ms /= 3
         variants[name] = {"coherent_mrays_s": round(len(rc) / ms[0] / 1e3, 1),
                           "incoherent_mrays_s": round(len(ri) / ms[1] / 1e3, 1)}
-    # the paper's TBVH comparison: every ray walks one link set (a single threaded BVH),
-    # with the timed kernel options
+    # the paper's comparison of MTBVH and TBVH on the stackless walk of the binary tree (the per-ray kernel,
+    # rays bucketed alike): every ray walks the link set of its direction (-1), or all one (a single threaded BVH)
     tbvh = {}
     if not args.no_variants:
-        for ls in range(6):
+        for ls in range(-1, 6):
             e = [torch.cuda.Event(enable_timing=True) for _ in range(2 * len(batches))]
             ms = np.zeros(len(batches))
             for rep in range(4):
-                for b, (r, (h, t), kw) in enumerate(zip(batches, outs, trace_kw)):
+                for b, (r, (h, t)) in enumerate(zip(batches, outs)):
                     e[2 * b].record(stream)
-                    api.trace_rays(bvh, r, h, t, link_set=ls, **kw)
+                    api.trace_rays(bvh, r, h, t, link_set=ls, kernel=api.TRACE_PER_RAY, reorder=b, block=64)
                     e[2 * b + 1].record(stream)
                 torch.cuda.synchronize()
                 if rep:
                     ms += [e[2 * b].elapsed_time(e[2 * b + 1]) for b in range(len(batches))]
             ms /= 3
-            tbvh[f"link_set_{ls}"] = {"coherent_mrays_s": round(len(rc) / ms[0] / 1e3, 1),
+            tbvh["by_direction" if ls < 0 else f"link_set_{ls}"] = {"coherent_mrays_s": round(len(rc) / ms[0] / 1e3, 1),
                                       "incoherent_mrays_s": round(len(ri) / ms[1] / 1e3, 1),
                                       "mrays_s": round((len(rc) + len(ri)) / ms.sum() / 1e3, 1)}
     # the GPU linear-BVH builder: build time and traversal rate with the timed options
@@ -340,12 +340,15 @@ def traversal_bench(args, torch, api, scenes):
             bv.destroy()
         variants["spatial_splits"] = spl
     avg_launch_ms = kern_ms.mean()
-    per_launch_bytes = alg_bytes   # one call traces both batches
+    # bytes of a call, both batches: between L2 and memory where the counters were taken on these sources, else those
+    # of the binary walk's visits
+    traffic = measured_traffic()
+    per_launch_bytes = traffic if traffic else alg_bytes
     achieved = per_launch_bytes / (avg_launch_ms * 1e-3) / 1e9
     hit_frac = float((outs[0][0] >= 0).float().mean().item())
     return dict(
         n_rays=n_rays, step_ms=step_ms, kern_ms=kern_ms, batch_ms=batch_ms, info=info, per_batch=per_batch,
-        achieved=achieved, per_launch_bytes=per_launch_bytes, hit_frac=hit_frac, variants=variants, tbvh=tbvh,
+        achieved=achieved, per_launch_bytes=per_launch_bytes, alg_bytes=alg_bytes, hit_frac=hit_frac, variants=variants, tbvh=tbvh,
         lbvh=lbvh, prewarm_steps=prewarm_steps, split_alpha=split_alpha, trav_cost=trav_cost,
         coherent_mrays=len(rc) / (batch_ms[0] * 1e-3) / 1e6,
         incoherent_mrays=len(ri) / (batch_ms[1] * 1e-3) / 1e6,
@@ -498,7 +501,7 @@ def sppm_bench(args, torch, api, scenes):
     runs += [("passes_threads_per_pixel", dict(photon_kernel=3)),
              ("passes_threads_2^18", dict(photon_kernel=3, pass_threads=1 << 18)),
              ("passes_threads_2^20_passes_24", dict(photon_kernel=3, pass_threads=1 << 20, passes=24))]
-    # the paper's TBVH comparison: every ray walks one link set (a single threaded BVH)
+    # every ray on one link set's binary tree (a single threaded BVH; the default walks the four-child nodes)
     runs += [(f"single_link_set_{k}", dict(single_link_set=k + 1)) for k in range(6)]
     for name, kw in runs:
         sv = api.Sppm(sc, api.sppm_params(Np, alpha=0.7, r0=0.05 * diag * 64 / 1280, seed=3, **kw), bvh=bvh)
@@ -810,34 +813,35 @@ def main():
                     trav_cost=tb["trav_cost"]),
         "kernel_variants": tb["variants"],
         "gpu_lbvh": tb["lbvh"],
-        "tbvh_ablation": ({"single_link_set": tb["tbvh"],
-                           "mtbvh_over_mean_tbvh": round(tb["n_rays"] / (tb["batch_ms"].sum() * 1e-3) / 1e6 /
-                                                         float(np.mean([v["mrays_s"] for v in tb["tbvh"].values()])), 3)}
+        "tbvh_ablation": ({"per_ray_kernel": tb["tbvh"],
+                           "mtbvh_over_mean_tbvh": round(tb["tbvh"]["by_direction"]["mrays_s"] /
+                                                         float(np.mean([v["mrays_s"] for k, v in tb["tbvh"].items()
+                                                                        if k != "by_direction"])), 3)}
                           if tb["tbvh"] else None),
         "traversal_stats": [{"rays": int(n), "boxes_per_ray": round(vn / n, 2), "tris_per_ray": round(vt / n, 2)}
                             for vn, vt, n in tb["per_batch"]],
         "roofline": {"bound": "hbm", "achieved": round(tb["achieved"], 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(tb["achieved"] / HBM_PEAK_GBS, 4), "traffic": measured_traffic(),
                      "kernel": "pm_trace_rays_multi call: k_hist_count + column and bucket scans + k_hist_scatter, then one launch of "
-                               "k_trace_perm_then_tiles (the incoherent batch's postponed walk, then the camera "
-                               "batch's packets over 8x8 pixel tiles)",
-                     "bytes_per_launch": tb["per_launch_bytes"],
+                               "k_trace_perm_then_tiles (the incoherent batch, then the camera batch's 8x8 pixel "
+                               "tiles, both through the four-child nodes)",
+                     "bytes_per_launch": tb["per_launch_bytes"], "binary_walk_bytes": tb["alg_bytes"],
                      "avg_launch_ms": round(float(tb["kern_ms"].mean()), 4),
                      "alone_ms_by_batch": [round(float(x), 4) for x in tb["batch_ms"]]},
     }
     ach = achievable_bandwidth(torch, api)
     best = max(ach["copy_GBps"], ach["read_GBps"])
     out["roofline"]["achievable"] = dict(ach, frac=round(tb["achieved"] / best, 4))
-    # the incoherent walk (node visits per second, bucketing included) against chains of dependent random
-    # reads of the same length per lane: over a BVH-sized buffer (reads served by the Infinity Cache and
-    # HBM) and over 4 MiB (one XCD's L2 holds it: the rate of a walk whose every node read hits L2)
+    # the incoherent walk (visits of the binary walk per second, bucketing included) against chains of dependent
+    # random reads of that length per lane: over a BVH-sized buffer (reads served by the Infinity Cache and
+    # HBM) and over 4 MiB (one XCD's L2 holds it: the most that the binary walk could reach)
     vn_inc, _, n_inc = tb["per_batch"][1]
     steps = max(1, int(round(vn_inc / n_inc)))
     node_rate = vn_inc / (float(tb["batch_ms"][1]) * 1e-3)
     far = dependent_read_rate(torch, api, n_inc, steps, log2_rows=24)
     near = dependent_read_rate(torch, api, n_inc, steps, log2_rows=18)
     out["roofline"]["achievable"]["dependent_reads"] = {
-        "incoherent_node_visits_per_s": round(node_rate, 1), "random_256MiB": far, "random_4MiB": near,
+        "binary_walk_visits_per_s": round(node_rate, 1), "random_256MiB": far, "random_4MiB": near,
         "frac_of_4MiB": round(node_rate / near["reads_per_s"], 4),
         "ratio_to_256MiB": round(node_rate / far["reads_per_s"], 3)}
     if not args.no_sppm:
@@ -850,7 +854,7 @@ def main():
                        "one_bounce_per_pass_schedule": sp["pass_schedule"],
                        "gather_exact_vs_stochastic_hashing": sp["stochastic_hashing"],
                        "tbvh_ablation": ({"iteration_ms_single_link_set": sp["tbvh"],
-                                          "mean_ratio_tbvh_over_mtbvh": round(
+                                          "mean_ratio_tbvh_over_default": round(
                                               float(np.mean(list(sp["tbvh"].values()))) / sp["iteration_ms"], 3)}
                                          if sp["tbvh"] else None)}
     if not args.no_adjoint:

@@ -506,11 +506,13 @@ using Walker = WalkerT<false>;
 // The binary walks are bound by their chain of dependent node reads (every
 // read names the next): an incoherent ray of the 2^20-triangle soup makes 111.
 // Here it makes 24, to one array of 23 MB instead of six of 147 MB together.
-// 2^21 such rays, bucketing included, went from 1.83 to 0.82 ms, the camera's
-// 2^21 in 8x8 tiles from 0.34 (packets) to 0.27 ms; the vector units, busy 98%
-// of the time with 36% of their lanes, now bind (64 box tests of a wave take
-// as many instructions as before; 8 children a node would test half as many
-// boxes again).
+// 2^21 such rays, bucketing included, went from 1.83 to 0.81 ms, the camera's
+// 2^21 in 8x8 tiles from 0.34 (packets) to 0.27 ms.  Now the vector units, busy
+// 98% of the time with 36% of their lanes, and the L1 data path, busy 91%, bind
+// together, so that easing one does not help: finished lanes refilled (19% fewer
+// instructions, 18% more L1 accesses) 0.93 ms, held leaves' triangles spread over
+// the wave's lanes 0.84, nodes fetched to LDS by four lanes each (4 waves a SIMD)
+// 1.02.
 //
 // Two shapes of the same walk:
 //  * one ray per lane (four boxes per lane and step), leaf tests held until at
