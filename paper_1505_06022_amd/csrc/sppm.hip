@@ -1481,12 +1481,12 @@ int sppm_status(pm_sppm *s, hipStream_t st) {
 }
 
 // The adjoint's replay with consecutive iterations overlapped, as in the
-// forward iteration: the replayed photon pass of k + 1 (with its flux
-// maximum) runs on the photon stream beside the grid, gather and path sums of
-// k, into the other photon store, (path, bounce) tables and maxima; the
-// replayed eye pass of k, R_max and the |G| wk maximum run on its eye stream
-// once iteration k - 1 is done with the hit points.  Every sum is an integer
-// sum, so the gradient equals the serial schedule's bit for bit.
+// forward iteration: the replayed photon passes (each with its flux maximum)
+// and the replayed eye passes (with R_max and the |G| wk maximum) of the next
+// iterations run on their slots' streams beside the grid, gather and path sums
+// of k, into the photon store, (path, bounce) tables, hit points and maxima of
+// their slot (k % ring), once iteration k - ring has read them.  Every sum is
+// an integer sum, so the gradient equals the serial schedule's bit for bit.
 static int adjoint_overlapped(pm_sppm *s, const float *g, hipStream_t caller) {
     hipStream_t st = work_stream(s, caller);
     const uint32_t T = 1u << s->table_bits;
