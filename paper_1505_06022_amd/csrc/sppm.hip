@@ -1210,16 +1210,25 @@ static hipStream_t work_stream(const pm_sppm *s, hipStream_t caller) {
     return s->streams.main;
 }
 
+// The streams that a call has forked from its caller's so far.
+struct Forked {
+    hipStream_t q[kRing + 1];
+    int n = 0;
+};
+
 // Forks the work stream and those that the first iterations from k0 on use from
 // the caller's stream; a stream without work stays out of it (in a recording it
 // could not be joined).
-static hipError_t fork_streams(pm_sppm *s, uint32_t k0, uint32_t n_iter, hipStream_t work, hipStream_t st) {
+static hipError_t fork_streams(pm_sppm *s, uint32_t k0, uint32_t n_iter, hipStream_t work, hipStream_t st,
+                               Forked &forked) {
     hipError_t e = hipEventRecord(s->ev_fork, st);
     for (hipStream_t q : {work, s->streams.pass[0], s->streams.pass[1], s->streams.pass[2]}) {
         bool used = q == work && q != st;
         for (uint32_t k = k0; k < k0 + std::min(n_iter, kRing); ++k)
             used = used || q == photon_queue(s, k) || q == eye_queue(s, k);
-        if (used && e == hipSuccess) e = hipStreamWaitEvent(q, s->ev_fork, 0);
+        if (!used || e != hipSuccess) continue;
+        e = hipStreamWaitEvent(q, s->ev_fork, 0);
+        if (e == hipSuccess) forked.q[forked.n++] = q;
     }
     return e;
 }
@@ -1228,6 +1237,12 @@ static hipError_t join_streams(pm_sppm *s, hipStream_t work, hipStream_t st) {
     if (work == st) return hipSuccess;
     hipError_t e = hipEventRecord(s->ev_join, work);
     return e == hipSuccess ? hipStreamWaitEvent(st, s->ev_join, 0) : e;
+}
+// A call that failed on the way: what it has enqueued still ends before
+// anything that the caller enqueues later, and a recording has no loose ends.
+static void join_after_error(pm_sppm *s, const Forked &forked, hipStream_t st) {
+    for (int i = 0; i < forked.n; ++i)
+        if (hipEventRecord(s->ev_join, forked.q[i]) == hipSuccess) (void)hipStreamWaitEvent(st, s->ev_join, 0);
 }
 
 // The photon pass of iteration k (its counters cleared first) on stream q.
@@ -1298,10 +1313,7 @@ static int enqueue_photon(pm_sppm *s, const SppmDev &dk, uint32_t k, bool count,
 // stochastic gather at 640x360 with 2^18 from 2.2 to 1.8, with the shares of the
 // device at kHeadShare.  At the end of the call the caller's stream has waited
 // for every stream.  Results are those of the serial order.
-int sppm_iterate(pm_sppm *s, int32_t n_iter, hipStream_t caller) {
-    if (!s || n_iter < 0) return set_error("invalid handle or iteration count"), PM_ERR_ARG;
-    if (!s->cell_count) return set_error("handle belongs to a batch: iterate the batch"), PM_ERR_STATE;
-    if (n_iter == 0) return PM_OK;
+static int run_iterations(pm_sppm *s, int32_t n_iter, hipStream_t caller, Forked &forked) {
     const uint32_t T = 1u << s->table_bits;
     const uint32_t ph_blocks = std::min<uint32_t>(blocks_for(s->cap), 256u * 64u);
     const bool count = (s->prm.profile & PM_PROFILE_COUNT) != 0, timed = (s->prm.profile & PM_PROFILE_TIME) != 0;
@@ -1332,7 +1344,7 @@ int sppm_iterate(pm_sppm *s, int32_t n_iter, hipStream_t caller) {
     };
     uint32_t sent = k0;  // iterations whose photon and eye passes are enqueued
     hipStream_t st = pipe ? work_stream(s, caller) : caller;
-    if (pipe) PM_HIP(fork_streams(s, k0, (uint32_t)n_iter, st, caller));
+    if (pipe) PM_HIP(fork_streams(s, k0, (uint32_t)n_iter, st, caller, forked));
     for (int32_t it = 0; it < n_iter; ++it) {
         const uint32_t k = k0 + (uint32_t)it;
         const SppmDev dk = iteration_view(s, k);
@@ -1352,6 +1364,8 @@ int sppm_iterate(pm_sppm *s, int32_t n_iter, hipStream_t caller) {
             hipStream_t side = s->streams.pass[1];
             PM_HIP(hipEventRecord(s->ev_fork, st));
             PM_HIP(hipStreamWaitEvent(side, s->ev_fork, 0));
+            forked.q[0] = side;
+            forked.n = 1;
             if (timed) PM_HIP(hipEventRecord(ev[1], side));
             hipLaunchKernelGGL(k_rmax_clear, dim3(1), dim3(64), 0, side, dk);
             eye_pass(dk, k, side);
@@ -1414,6 +1428,16 @@ int sppm_iterate(pm_sppm *s, int32_t n_iter, hipStream_t caller) {
     }
     if (pipe) PM_HIP(join_streams(s, st, caller));
     return PM_OK;
+}
+
+int sppm_iterate(pm_sppm *s, int32_t n_iter, hipStream_t st) {
+    if (!s || n_iter < 0) return set_error("invalid handle or iteration count"), PM_ERR_ARG;
+    if (!s->cell_count) return set_error("handle belongs to a batch: iterate the batch"), PM_ERR_STATE;
+    if (n_iter == 0) return PM_OK;
+    Forked forked;
+    const int rc = run_iterations(s, n_iter, st, forked);
+    if (rc) join_after_error(s, forked, st);
+    return rc;
 }
 
 int sppm_get_stats(pm_sppm *s, pm_sppm_stats *out, int32_t reset, hipStream_t st) {
@@ -1487,7 +1511,7 @@ int sppm_status(pm_sppm *s, hipStream_t st) {
 // of k, into the photon store, (path, bounce) tables, hit points and maxima of
 // their slot (k % ring), once iteration k - ring has read them.  Every sum is
 // an integer sum, so the gradient equals the serial schedule's bit for bit.
-static int adjoint_overlapped(pm_sppm *s, const float *g, hipStream_t caller) {
+static int adjoint_overlapped(pm_sppm *s, const float *g, hipStream_t caller, Forked &forked) {
     hipStream_t st = work_stream(s, caller);
     const uint32_t T = 1u << s->table_bits;
     const uint32_t np = (uint32_t)s->prm.n_photons;
@@ -1544,7 +1568,7 @@ static int adjoint_overlapped(pm_sppm *s, const float *g, hipStream_t caller) {
         PM_HIP(hipEventRecord(s->ev_eye[k % s->ring], q));
         return PM_OK;
     };
-    PM_HIP(fork_streams(s, 0u, K, st, caller));
+    PM_HIP(fork_streams(s, 0u, K, st, caller, forked));
     uint32_t sent = 0;  // iterations whose replays are enqueued
     for (uint32_t k = 0; k < K; ++k) {
         const SppmDev dk = iteration_view(s, k);
@@ -1579,18 +1603,8 @@ static int adjoint_overlapped(pm_sppm *s, const float *g, hipStream_t caller) {
     return PM_OK;
 }
 
-int sppm_adjoint(pm_sppm *s, const float *g, const int32_t *pmat, int32_t n_par, double *grad, hipStream_t st) {
-    if (!s || !g || !grad || n_par < 0 || (n_par > 0 && !pmat))
-        return set_error("invalid handle, gradient or parameter pointers"), PM_ERR_ARG;
-    if (!s->cell_count) return set_error("handle belongs to a batch"), PM_ERR_STATE;
-    if (s->K < 1) return set_error("no iteration has run"), PM_ERR_STATE;
-    if (s->K > s->rec_iters)
-        return set_error("the forward iterations were not recorded: set record_iterations >= K"), PM_ERR_STATE;
-    if (n_par >= kMaxAdjMat) return set_error("too many parameters"), PM_ERR_ARG;
-    for (int32_t i = 0; i < n_par; ++i) {
-        if (pmat[i] < 0 || pmat[i] >= s->n_mat) return set_error("parameter material out of range"), PM_ERR_ARG;
-        if (!(s->rho_host[pmat[i]] > 0.0f)) return set_error("albedo parameters must have rho > 0"), PM_ERR_ARG;
-    }
+// The same, one iteration after another (a handle with one slot).
+static int adjoint_serial(pm_sppm *s, const float *g, hipStream_t st, Forked &forked) {
     const uint32_t T = 1u << s->table_bits;
     const uint32_t np = (uint32_t)s->prm.n_photons;
     const int32_t mb = s->prm.max_photon_bounces;
@@ -1598,15 +1612,7 @@ int sppm_adjoint(pm_sppm *s, const float *g, const int32_t *pmat, int32_t n_par,
     const double K = (double)s->K;
     const SppmDev &d = s->dev;
     const int hits = hits_per_wave(s->P);
-    ParamMats pms;
-    for (int32_t i = 0; i < n_par; ++i) pms.m[i] = (uint8_t)pmat[i];
-    hipLaunchKernelGGL(k_fill_f64, dim3(blocks_for(s->n_mat + 1)), dim3(kBlock), 0, st, s->grad_mat,
-                       (int64_t)s->n_mat + 1);
-    if (s->ring > 1) {
-        int rc = adjoint_overlapped(s, g, st);
-        if (rc) return rc;
-    }
-    for (int32_t k = 0; k < (s->ring > 1 ? 0 : s->K); ++k) {
+    for (int32_t k = 0; k < s->K; ++k) {
         const double *R2k = s->R2_hist + (size_t)k * s->P;
         hipLaunchKernelGGL(k_begin, dim3(1), dim3(64), 0, st, d);
         hipLaunchKernelGGL(k_adj_begin, dim3(1), dim3(kBlock), 0, st, s->adj_max, s->adj_wide, s->n_mat);
@@ -1615,6 +1621,8 @@ int sppm_adjoint(pm_sppm *s, const float *g, const int32_t *pmat, int32_t n_par,
         hipStream_t side = s->streams.pass[1];
         PM_HIP(hipEventRecord(s->ev_fork, st));
         PM_HIP(hipStreamWaitEvent(side, s->ev_fork, 0));
+        forked.q[0] = side;
+        forked.n = 1;
         hipLaunchKernelGGL(k_eye, dim3(blocks_for(s->P)), dim3(kBlock), 0, side, d, (uint32_t)k, 0);
         hipLaunchKernelGGL(k_rmax, dim3(std::min(blocks_for(s->P), kRmaxBlocks)), dim3(kBlock), 0, side, d, R2k);
         hipLaunchKernelGGL(k_adj_gmax, dim3(std::min<uint32_t>(blocks_for(s->P), kAdjMaxBlocks)), dim3(kBlock), 0,
@@ -1639,6 +1647,32 @@ int sppm_adjoint(pm_sppm *s, const float *g, const int32_t *pmat, int32_t n_par,
         hipLaunchKernelGGL(k_adj_fold, dim3(1), dim3(kMaxAdjMat), 0, st, (const unsigned long long *)s->adj_wide,
                            s->n_mat, (const double *)s->adj_scale, d.sc.mat_rho, s->grad_mat);
         PM_HIP(hipGetLastError());
+    }
+    return PM_OK;
+}
+
+int sppm_adjoint(pm_sppm *s, const float *g, const int32_t *pmat, int32_t n_par, double *grad, hipStream_t st) {
+    if (!s || !g || !grad || n_par < 0 || (n_par > 0 && !pmat))
+        return set_error("invalid handle, gradient or parameter pointers"), PM_ERR_ARG;
+    if (!s->cell_count) return set_error("handle belongs to a batch"), PM_ERR_STATE;
+    if (s->K < 1) return set_error("no iteration has run"), PM_ERR_STATE;
+    if (s->K > s->rec_iters)
+        return set_error("the forward iterations were not recorded: set record_iterations >= K"), PM_ERR_STATE;
+    if (n_par >= kMaxAdjMat) return set_error("too many parameters"), PM_ERR_ARG;
+    for (int32_t i = 0; i < n_par; ++i) {
+        if (pmat[i] < 0 || pmat[i] >= s->n_mat) return set_error("parameter material out of range"), PM_ERR_ARG;
+        if (!(s->rho_host[pmat[i]] > 0.0f)) return set_error("albedo parameters must have rho > 0"), PM_ERR_ARG;
+    }
+    const double K = (double)s->K;
+    const SppmDev &d = s->dev;
+    ParamMats pms;
+    for (int32_t i = 0; i < n_par; ++i) pms.m[i] = (uint8_t)pmat[i];
+    hipLaunchKernelGGL(k_fill_f64, dim3(blocks_for(s->n_mat + 1)), dim3(kBlock), 0, st, s->grad_mat,
+                       (int64_t)s->n_mat + 1);
+    Forked forked;
+    if (int rc = s->ring > 1 ? adjoint_overlapped(s, g, st, forked) : adjoint_serial(s, g, st, forked)) {
+        join_after_error(s, forked, st);
+        return rc;
     }
     const uint32_t n_part = blocks_for(s->P);
     hipLaunchKernelGGL(k_le_grad, dim3(n_part), dim3(kBlock), 0, st, d, K, g, s->le_part);

@@ -1,0 +1,68 @@
+"""Runs Python code against libpm.so with tests/fake_hip.cpp in the HIP runtime's place.
+
+The code runs in a process of its own (a library binds its runtime once); its
+names: np, api, scenes, log() (the runtime's calls since the last log(), one
+list of words each), fail(name, nth, code), fake (the stand-in itself), new_stream(),
+unjoined(calls, stream).
+"""
+import os
+import subprocess
+import sys
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+OOM, INVALID = 2, 1  # hipErrorOutOfMemory, hipErrorInvalidValue
+
+PRELUDE = """
+import ctypes, sys
+sys.path.insert(0, {root!r})
+fake = ctypes.CDLL({lib!r}, ctypes.RTLD_GLOBAL)
+fake.fake_take_log.restype = ctypes.c_char_p
+fake.fake_fail.argtypes = [ctypes.c_char_p, ctypes.c_long, ctypes.c_int]
+fake.fake_capture.argtypes = [ctypes.c_ssize_t, ctypes.c_int]
+fake.fake_take_log()
+import numpy as np
+from paper_1505_06022_amd import api, scenes
+OOM, INVALID = {oom}, {invalid}
+def log():
+    return [l.split() for l in fake.fake_take_log().decode().splitlines()]
+def fail(name, nth, code):
+    fake.fake_fail(name.encode(), nth, code)
+class Stream:
+    def __init__(self):
+        s = ctypes.c_void_p()
+        assert fake.hipStreamCreateWithFlags(ctypes.byref(s), 1) == 0
+        self.cuda_stream = s.value
+def new_stream():
+    return Stream()
+def unjoined(calls, stream):
+    '''Streams with work that the work enqueued on `stream` after these calls would not wait for.'''
+    done, seen, events = dict(), dict(), dict()  # per stream: its work, the work of others it follows
+    for c in calls:
+        if c[0] in ("launch", "copy", "fill", "graph"):
+            done[c[-1]] = done.get(c[-1], 0) + 1
+        elif c[0] == "record":
+            s = dict(seen.get(c[2], dict()))
+            s[c[2]] = done.get(c[2], 0)
+            events[c[1]] = s
+        elif c[0] == "wait":
+            mine = seen.setdefault(c[1], dict())
+            for k, v in events.get(c[2], dict()).items():
+                mine[k] = max(mine.get(k, 0), v)
+    return [s for s, n in done.items() if s != str(stream) and seen.get(str(stream), dict()).get(s, 0) < n]
+"""
+
+
+def build(folder) -> str:
+    out = os.path.join(str(folder), "libfake_hip.so")
+    hipcc = os.environ.get("HIPCC") or "/opt/rocm/bin/hipcc"
+    subprocess.run([hipcc, "-std=c++17", "-O1", "-fPIC", "-shared", "-x", "hip", "--offload-host-only",
+                    os.path.join(HERE, "fake_hip.cpp"), "-o", out], check=True)
+    return out
+
+
+def run(lib: str, code: str) -> str:
+    """Output of the code; an assertion that fails in it fails the caller."""
+    text = PRELUDE.format(root=os.path.dirname(HERE), lib=lib, oom=OOM, invalid=INVALID) + code
+    r = subprocess.run([sys.executable, "-c", text], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+    return r.stdout
