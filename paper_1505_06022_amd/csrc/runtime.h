@@ -81,7 +81,8 @@ void free_bvh(pm_bvh *b);
 
 // Merges the binary tree of a BVH's link set 0 into the four-child nodes of the
 // wide walk: launch() enqueues the work once the binary nodes are enqueued on
-// s, finish() synchronises s and fills the handle.  The handle's node count and
+// s, finish() synchronises s and fills the handle (or leaves it without them: a
+// tree too deep, or no device memory for them).  The handle's node count and
 // box grid are read, the nodes must outlive the object.
 class WideBuild {
   public:

@@ -197,6 +197,17 @@ WideBuild::~WideBuild() {
     if (mem_) (void)hipFree(mem_);
 }
 
+// *mem stays NULL where the device has no room: a BVH without four-child nodes
+// takes the binary walks.
+static int allocate(void **mem, size_t bytes) {
+    const hipError_t e = hipMalloc(mem, bytes);
+    if (e == hipSuccess) return PM_OK;
+    *mem = nullptr;
+    if (e != hipErrorOutOfMemory) return hip_fail(e, "hipMalloc");
+    (void)hipGetLastError();
+    return PM_OK;
+}
+
 int WideBuild::expand(const pm_bvh *b, hipStream_t s, uint32_t upto) {
     GridStep g;
     for (int a = 0; a < 3; ++a) g.s[a] = b->qstep[a];
@@ -215,8 +226,10 @@ int WideBuild::launch(const pm_bvh *b, hipStream_t s) {
     const uint32_t np = tiles_ * pmd::kScanTile;
     // one allocation: two lists of nodes, flags, their exclusive scan (two arrays), tile sums, counters
     const size_t list = n_ / 2 + 1;
-    PM_HIP(hipMalloc(&mem_, sizeof(uint2) * 2 * list + sizeof(uint32_t) * ((size_t)np + (np + 1) + np + (tiles_ + 1) +
-                                                                          kWideCounters)));
+    if (int rc = allocate(&mem_, sizeof(uint2) * 2 * list +
+                                     sizeof(uint32_t) * ((size_t)np + (np + 1) + np + (tiles_ + 1) + kWideCounters)))
+        return rc;
+    if (!mem_) return PM_OK;
     list_[0] = (uint2 *)mem_;
     list_[1] = list_[0] + list;
     flag_ = (uint32_t *)(list_[1] + list);
@@ -231,6 +244,10 @@ int WideBuild::launch(const pm_bvh *b, hipStream_t s) {
 
 int WideBuild::finish(pm_bvh *b, hipStream_t s) {
     uint32_t read[1 + kWideCounters], *const c = read + 1;  // wide nodes, then the counters
+    if (!mem_) {
+        PM_HIP(hipStreamSynchronize(s));
+        return PM_OK;
+    }
     for (;;) {
         PM_HIP(hipMemcpyAsync(read, bsum_ + tiles_, sizeof(read), hipMemcpyDeviceToHost, s));
         PM_HIP(hipStreamSynchronize(s));
@@ -241,7 +258,8 @@ int WideBuild::finish(pm_bvh *b, hipStream_t s) {
     }
     GridStep g;
     for (int a = 0; a < 3; ++a) g.s[a] = b->qstep[a];
-    PM_HIP(hipMalloc(&b->d_wide, sizeof(uint4) * 4 * (size_t)read[0]));
+    if (int rc = allocate((void **)&b->d_wide, sizeof(uint4) * 4 * (size_t)read[0])) return rc;
+    if (!b->d_wide) return PM_OK;
     b->n_wide = read[0];
     hipLaunchKernelGGL(k_wide_emit, dim3((n_ + kWb - 1) / kWb), dim3(kWb), 0, s, (const uint4 *)b->d_nodes, n_,
                        (const uint32_t *)flag_, (const uint32_t *)index_, g, b->d_wide);

@@ -22,6 +22,8 @@ namespace {
 std::string g_log, g_copy;
 std::map<const void *, std::string> g_kernels;
 std::map<std::string, std::pair<long, hipError_t>> g_fail;  // calls until the one that fails
+std::map<void *, size_t> g_blocks;
+size_t g_used = 0, g_memory = ~size_t(0);
 std::set<intptr_t> g_streams, g_capturing;
 intptr_t g_next = 1;
 hipError_t g_last = hipSuccess;
@@ -72,6 +74,9 @@ const char *fake_take_log() {
 }
 // Call number `nth` (0: the next) of `name` fails with `code`.
 void fake_fail(const char *name, long nth, int code) { g_fail[name] = {nth, (hipError_t)code}; }
+// Device memory in bytes, and what is allocated of it.
+void fake_memory(size_t bytes) { g_memory = bytes; }
+size_t fake_used() { return g_used; }
 void fake_capture(intptr_t stream, int on) {
     if (on) g_capturing.insert(stream);
     else g_capturing.erase(stream);
@@ -129,9 +134,14 @@ hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, in
 hipError_t hipDeviceSynchronize() { FAKE_CALL("hipDeviceSynchronize", line("sync %d", -1)); }
 
 hipError_t hipMalloc(void **p, size_t bytes) {
-    FAKE_CALL("hipMalloc", line("malloc %zu", bytes); *p = std::calloc(bytes + 256, 1));
+    if (g_used + bytes > g_memory) return g_last = hipErrorOutOfMemory;
+    FAKE_CALL("hipMalloc", line("malloc %zu", bytes); *p = std::calloc(bytes + 256, 1); g_blocks[*p] = bytes;
+              g_used += bytes);
 }
-hipError_t hipFree(void *p) { FAKE_CALL("hipFree", line("%s", "free"); std::free(p)); }
+hipError_t hipFree(void *p) {
+    if (p && !g_blocks.count(p)) return g_last = hipErrorInvalidValue;
+    FAKE_CALL("hipFree", line("%s", "free"); if (p) g_used -= g_blocks[p]; g_blocks.erase(p); std::free(p));
+}
 hipError_t hipMemcpyAsync(void *to, const void *from, size_t bytes, hipMemcpyKind, hipStream_t s) {
     FAKE_ON("hipMemcpyAsync", s, line("copy %zu %ld", bytes, id(s)); std::memcpy(to, from, bytes));
 }

@@ -2,8 +2,8 @@
 
 The code runs in a process of its own (a library binds its runtime once); its
 names: np, api, scenes, log() (the runtime's calls since the last log(), one
-list of words each), fail(name, nth, code), fake (the stand-in itself), new_stream(),
-unjoined(calls, stream).
+list of words each), fail(name, nth, code), memory(bytes), used(), fake (the
+stand-in itself), new_stream(), unjoined(calls, stream).
 """
 import os
 import subprocess
@@ -18,6 +18,8 @@ sys.path.insert(0, {root!r})
 fake = ctypes.CDLL({lib!r}, ctypes.RTLD_GLOBAL)
 fake.fake_take_log.restype = ctypes.c_char_p
 fake.fake_fail.argtypes = [ctypes.c_char_p, ctypes.c_long, ctypes.c_int]
+fake.fake_memory.argtypes = [ctypes.c_size_t]
+fake.fake_used.restype = ctypes.c_size_t
 fake.fake_capture.argtypes = [ctypes.c_ssize_t, ctypes.c_int]
 fake.fake_take_log()
 import numpy as np
@@ -27,6 +29,10 @@ def log():
     return [l.split() for l in fake.fake_take_log().decode().splitlines()]
 def fail(name, nth, code):
     fake.fake_fail(name.encode(), nth, code)
+def memory(size):
+    fake.fake_memory(size)
+def used():
+    return fake.fake_used()
 class Stream:
     def __init__(self):
         s = ctypes.c_void_p()
