@@ -134,8 +134,11 @@ __global__ __launch_bounds__(64) void k_segment_ends(const uint32_t *__restrict_
 
 namespace pm {
 
-DeviceHash::~DeviceHash() {
+DeviceHash::~DeviceHash() { release(); }
+
+void DeviceHash::release() {
     if (mem_) (void)hipFree(mem_);
+    mem_ = nullptr;
 }
 
 int DeviceHash::launch(uint64_t h, const void *a, size_t words_a, const void *b, size_t words_b, hipStream_t st) {

@@ -783,7 +783,8 @@ class Arena {
 // it); from kDeviceHash on the device does, in less time than the chain takes
 // there: creating the handle of 250,000 triangles went from 2.16 ms (with the
 // thread) to 0.8, while for 13,600 the device takes longer (0.41 ms instead of
-// 0.25).  The description is not read after finish().
+// 0.25).  Where the device has no room for the words the host does it.  The
+// description is not read after finish().
 class SceneFingerprint {
   public:
     static constexpr int64_t kHashThread = 8192, kDeviceHash = 1 << 15;
@@ -795,19 +796,34 @@ class SceneFingerprint {
         add(&d->n_tri, sizeof(d->n_tri));
         const size_t nt = (size_t)d->n_tri;
         device_ = d->n_tri >= kDeviceHash && d->n_tri < (int64_t(1) << 28);
-        if (device_) return hash_.launch(h_, d->tri_verts, 9 * nt, d->tri_mat, nt, st);
+        if (device_) {
+            const int rc = hash_.launch(h_, d->tri_verts, 9 * nt, d->tri_mat, nt, st);
+            if (rc != PM_ERR_NOMEM) return rc;
+            (void)hipGetLastError();
+            device_ = false;
+        }
         if (d->n_tri >= kHashThread) try {
                 thread_ = std::thread([this] { triangles(); });
             } catch (const std::system_error &) {  // no thread to be had: finish() does it
             }
         return PM_OK;
     }
+    // Ends the device's part and gives its memory back; false: there was none.
+    bool settle(hipStream_t st, int &rc) {
+        if (!device_) return false;
+        rc = hash_.finish(h_, st);
+        hash_.release();
+        device_ = false;
+        settled_ = true;
+        return true;
+    }
     int finish(uint64_t &out, hipStream_t st) {
-        if (device_) {
-            if (int rc = hash_.finish(h_, st)) return rc;
+        int rc = PM_OK;
+        if (settle(st, rc)) {
+            if (rc) return rc;
         } else if (thread_.joinable()) {
             thread_.join();
-        } else {
+        } else if (!settled_) {
             triangles();
         }
         const size_t nm = (size_t)d_->n_mat;
@@ -842,7 +858,7 @@ class SceneFingerprint {
     }
     const pm_scene_desc *d_ = nullptr;
     uint64_t h_ = 0xcbf29ce484222325ull;
-    bool device_ = false;
+    bool device_ = false, settled_ = false;
     DeviceHash hash_;
     std::thread thread_;
 };
@@ -961,8 +977,9 @@ int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t 
         (uint32_t)std::min<int64_t>(p->n_photons, (int64_t)std::max(s->head_grid, s->head_grid_rec) * kBlock);
     const size_t queue_bytes = (size_t)56 * queue_slots + 256;
     s->rec_iters = p->record_iterations;
-    // a handle that does not fit with all slots makes do with two
-    for (s->ring = slots;; s->ring = 2u) {
+    // a handle that does not fit with all slots makes do with fewer (one: an iteration at a time)
+    s->ring = slots;
+    for (;;) {
         Arena arena;
         arena.add(s->mat_type, sizeof(int32_t) * nm);
         arena.add(s->mat_f, sizeof(float) * 4 * nm);
@@ -1012,7 +1029,14 @@ int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t 
         }
         const hipError_t e = arena.allocate(&s->arena);
         if (e == hipSuccess) break;
-        if (s->ring <= 2u) return fail(hip_fail(e, "hipMalloc"));
+        // first without the fingerprint's buffer beside it
+        if (e == hipErrorOutOfMemory && fingerprint.settle(st, rc)) {
+            if (rc) return fail(rc);
+        } else if (s->ring == 1u || e != hipErrorOutOfMemory) {
+            return fail(hip_fail(e, "hipMalloc"));
+        } else {
+            s->ring--;
+        }
         (void)hipGetLastError();
     }
 

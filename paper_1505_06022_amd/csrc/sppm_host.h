@@ -110,7 +110,8 @@ constexpr uint64_t kHashPrime = 0x100000001b3ull;
 
 // The hash h = (h ^ w) kHashPrime over the words a[0 .. words_a), b[0 .. words_b)
 // (at least one, below 2^32 together) from the state h: launch() uploads them and
-// enqueues the work on st, finish() waits for it and gives the final state.
+// enqueues the work on st (PM_ERR_NOMEM: none, for want of device memory),
+// finish() waits for it and gives the final state, release() frees the memory.
 class DeviceHash {
   public:
     DeviceHash() = default;
@@ -118,6 +119,7 @@ class DeviceHash {
     ~DeviceHash();
     int launch(uint64_t h, const void *a, size_t words_a, const void *b, size_t words_b, hipStream_t st);
     int finish(uint64_t &h, hipStream_t st);
+    void release();
 
   private:
     void *mem_ = nullptr;
