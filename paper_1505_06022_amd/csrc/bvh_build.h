@@ -43,6 +43,9 @@ constexpr int kNodeWords = 4;
 constexpr int kTriWords = 12;
 constexpr int kLinkSets = 6;
 
+// Index of the first infinite or NaN value of v[0 .. n), or -1.
+int64_t first_not_finite(const float *v, int64_t n);
+
 bool build_bvh_host(const float *verts, const uint32_t *mats, int64_t n_tri, const BuildOptions &opt, HostBvh &out,
                     std::string &err);
 

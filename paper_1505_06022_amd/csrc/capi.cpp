@@ -127,15 +127,11 @@ int pm_build_bvh(const float *tri_verts, const uint32_t *tri_mat, int64_t n_tri,
             if (n_tri < 1 || n_tri >= (int64_t(1) << 28)) return pm::set_error("n_tri must be in [1, 2^28)"), PM_ERR_ARG;
             if (bo.max_leaf < 1 || bo.max_leaf > 7 || !(bo.trav_cost > 0.0) || bo.trav_cost > 64.0)
                 return pm::set_error("max_leaf must be in [1,7] and trav_cost in (0,64]"), PM_ERR_ARG;
+            const int64_t bad = pm::first_not_finite(tri_verts, 9 * n_tri);
+            if (bad >= 0)
+                return pm::set_error("non-finite vertex coordinate at triangle " + std::to_string(bad / 9)), PM_ERR_ARG;
             b = new pm_bvh();
             rc = pm::build_bvh_gpu(tri_verts, tri_mat, n_tri, bo.max_leaf, bo.trav_cost, (hipStream_t)stream, b);
-            // the build looks for non-finite vertices on the device; name the first
-            for (int64_t i = 0; rc && i < 9 * n_tri; ++i)
-                if (!std::isfinite(tri_verts[i])) {
-                    pm::set_error("non-finite vertex coordinate at triangle " + std::to_string(i / 9));
-                    rc = PM_ERR_ARG;
-                    break;
-                }
         } else {
             pm::HostBvh hb;
             std::string err;

@@ -54,7 +54,6 @@ struct LbOut {
     float lo[3], hi[3], qlo[3], qstep[3];
     QuantGrid grid;
     CentreMap cells;
-    uint32_t not_finite;  // a vertex coordinate is infinite or NaN
     uint32_t bad;         // a walk too long, a full list or an index out of range
     int32_t n_nodes;      // collapsed size of the root
     uint32_t depth;
@@ -68,7 +67,7 @@ static_assert(sizeof(LbOut) % sizeof(int32_t) == 0, "read back as words");
 // vertices (vlo, vhi) and of the box centres (clo, chi).
 __global__ __launch_bounds__(kLb) void k_lb_boxes(const float *__restrict__ verts, uint32_t n,
                                                   float *__restrict__ tbox, float *__restrict__ part,
-                                                  uint4 *__restrict__ link, LbOut *__restrict__ out) {
+                                                  uint4 *__restrict__ link) {
     __shared__ float red[kLb / 64][12];
     const uint32_t i = blockIdx.x * kLb + threadIdx.x;
     float v[12];
@@ -80,10 +79,8 @@ __global__ __launch_bounds__(kLb) void k_lb_boxes(const float *__restrict__ vert
     }
     if (i < n) {
         float lo[3], hi[3];
-        bool finite = true;
         for (int a = 0; a < 3; ++a) {
             float x0 = verts[9 * (size_t)i + a], x1 = verts[9 * (size_t)i + 3 + a], x2 = verts[9 * (size_t)i + 6 + a];
-            finite = finite && isfinite(x0) && isfinite(x1) && isfinite(x2);
             lo[a] = fminf(fminf(x0, x1), x2);
             hi[a] = fmaxf(fmaxf(x0, x1), x2);
             tbox[6 * (size_t)i + a] = lo[a];
@@ -94,7 +91,6 @@ __global__ __launch_bounds__(kLb) void k_lb_boxes(const float *__restrict__ vert
             v[6 + a] = c;
             v[9 + a] = c;
         }
-        if (!finite) atomicOr(&out->not_finite, 1u);
         link[2 * (size_t)i] = link[2 * (size_t)i + 1] = make_uint4(0u, 0u, ~0u, 0u);  // no parent yet
     }
     for (int off = 32; off > 0; off >>= 1)
@@ -522,8 +518,7 @@ int build_bvh_gpu(const float *verts_h, const uint32_t *mats_h, int64_t n_tri, i
     PM_HIP(hipMemsetAsync(out, 0, sizeof(LbOut), s));
 
     // 1-2. boxes, bounds, Morton codes and a stable sort by code
-    hipLaunchKernelGGL(k_lb_boxes, dim3(nblk), dim3(kLb), 0, s, (const float *)verts, (uint32_t)n, tbox, part, link,
-                       out);
+    hipLaunchKernelGGL(k_lb_boxes, dim3(nblk), dim3(kLb), 0, s, (const float *)verts, (uint32_t)n, tbox, part, link);
     hipLaunchKernelGGL(k_lb_reduce, dim3(1), dim3(kReduce), 0, s, (const float *)part, nblk, out);
     hipLaunchKernelGGL(k_lb_morton, dim3(nblk), dim3(kLb), 0, s, (const float *)tbox, (uint32_t)n, (const LbOut *)out,
                        code, idx);
@@ -556,7 +551,6 @@ int build_bvh_gpu(const float *verts_h, const uint32_t *mats_h, int64_t n_tri, i
     LbOut r;
     PM_HIP(hipMemcpyAsync(&r, out, sizeof(r), hipMemcpyDeviceToHost, s));
     PM_HIP(hipStreamSynchronize(s));
-    if (r.not_finite) return set_error("non-finite vertex coordinate"), PM_ERR_ARG;
     if (r.bad || r.n_nodes < 1 || (size_t)r.n_nodes > n_all)
         return set_error("GPU BVH build: inconsistent tree"), PM_ERR_STATE;
 
