@@ -19,16 +19,24 @@ namespace {
 
 using namespace pmd;
 
-// The wide walk's stacks of a workgroup, and its wave's share.
-#define PM_STACK()                                           \
-    __shared__ uint32_t wide_stack[kBlock / 64][kStackWords]; \
-    uint32_t *const stk = wide_stack[threadIdx.x >> 6]
+// The kernels that trace paths have two forms.  kWide: the wide walk, with its
+// stacks in LDS (24 KB a workgroup) and PM_PASS_WAVES; else the binary walk
+// only, for handles whose rays never take the other (one link set forced, or a
+// BVH without four-child nodes): its registers and the photons' LDS leave room
+// for five waves a SIMD, and the eye pass for six.  One form for both took 2.25
+// ms an iteration with one link set (1280x720, 2^20 photons, calls of 8) instead
+// of 1.79, and 1.90 with the eye pass at five waves.
+#define PM_STACK()                                                                          \
+    __shared__ uint32_t wide_stack[kWide ? kBlock / 64 : 1][kWide ? kStackWords : 1];       \
+    uint32_t *const stk = kWide ? wide_stack[threadIdx.x >> 6] : nullptr
 // The same for the photons on their way to the store.
 #define PM_SINK()                                   \
     __shared__ float4 photon_buf[kBlock / 64][kSinkWords]; \
     const PhotonSink sink{photon_buf[threadIdx.x >> 6], 0u}
 
-__global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_eye(SppmDev d, uint32_t k, int32_t emission) {
+template <bool kWide>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWide ? 4 : 6)))
+void k_eye(SppmDev d, uint32_t k, int32_t emission) {
     int64_t p = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
     PM_STACK();
     eye_elem(d, k, p, p < d.P, emission != 0, stk);
@@ -50,7 +58,7 @@ __device__ __forceinline__ int64_t wave_index() {
 }
 
 // One path per lane, the first per_wave lanes of each wave.
-template <bool kRecord>
+template <bool kRecord, bool kWide>
 __global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon(SppmDev d, uint32_t k, uint32_t per_wave,
                                                                uint16_t *__restrict__ mat_tab,
                                                                long long *__restrict__ adj_tab) {
@@ -62,6 +70,7 @@ __global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon(SppmDev d, uint
 }
 
 // Persistent photon lanes with path regeneration.
+template <bool kWide>
 __global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_regen(SppmDev d, uint32_t k) {
     PM_STACK();
     PM_SINK();
@@ -76,14 +85,14 @@ __global__ __launch_bounds__(kBlock) void k_photon_regen_stats(SppmDev d, uint32
 // Two-phase photon pass (PM_PHOTON_TWO_PHASE): regeneration that sets the
 // last paths of each wavefront aside once the path counter has run out, then
 // a launch over the paths set aside.
-template <bool kStats>
+template <bool kStats, bool kWide>
 __global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_head(SppmDev d, uint32_t k, PathQueue q) {
     PM_STACK();
     PM_SINK();
     photon_regen_loop<false, kStats, true>(d, k, d.refill, stk, sink, nullptr, nullptr, q);
 }
 
-template <bool kStats>
+template <bool kStats, bool kWide>
 __global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_tail(SppmDev d, PathQueue q) {
     PM_STACK();
     PM_SINK();
@@ -92,6 +101,7 @@ __global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_tail(SppmDev d,
 
 // The same two launches, recording each path's stored-photon materials for
 // the adjoint (a queued path keeps its row of the tables).
+template <bool kWide>
 __global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_head_rec(SppmDev d, uint32_t k, PathQueue q,
                                                             uint16_t *__restrict__ mat_tab,
                                                             long long *__restrict__ adj_tab) {
@@ -100,6 +110,7 @@ __global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_head_rec(SppmDe
     photon_regen_loop<true, false, true>(d, k, d.refill, stk, sink, mat_tab, adj_tab, q);
 }
 
+template <bool kWide>
 __global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_tail_rec(SppmDev d, PathQueue q,
                                                             uint16_t *__restrict__ mat_tab,
                                                             long long *__restrict__ adj_tab) {
@@ -126,6 +137,7 @@ __global__ __launch_bounds__(kBlock) void k_photon_stream_stats(SppmDev d, uint3
 }
 
 // The same, recording each path's stored-photon materials for the adjoint.
+template <bool kWide>
 __global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_regen_rec(SppmDev d, uint32_t k, uint16_t *__restrict__ mat_tab,
                                                              long long *__restrict__ adj_tab) {
     PM_STACK();
@@ -135,6 +147,7 @@ __global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_regen_rec(SppmD
 
 // One pass of the one-bounce-per-pass schedule; the grid covers the slots
 // with the same workgroup-to-slot map in every pass.
+template <bool kWide>
 __global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_pass(SppmDev d, uint32_t k, PassSlots ps) {
     PM_STACK();
     PM_SINK();
@@ -146,6 +159,7 @@ __global__ void k_pass_tally(SppmDev d) {
     if (threadIdx.x == 0) d.counters[3] = d.n_paths - min(d.counters[2], d.n_paths);
 }
 
+template <bool kWide>
 __global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_drain(SppmDev d, uint32_t k, PassSlots ps) {
     PM_STACK();
     PM_SINK();
@@ -557,6 +571,12 @@ __global__ __launch_bounds__(kMaxAdjMat) void k_collect_grad(const double *__res
     if (i == n_par) out[i] = lds[0] * inv_Le;
 }
 
+// The form of a kernel that a handle launches.
+template <class K>
+K *pick(const pm_sppm *s, K *wide, K *binary) {
+    return s->wide ? wide : binary;
+}
+
 inline uint32_t blocks_for(int64_t n) { return (uint32_t)((n + kBlock - 1) / kBlock); }
 // Workgroups for n elements, per_wave to a wave.
 inline uint32_t blocks_for_waves(int64_t n, uint32_t per_wave) {
@@ -734,10 +754,15 @@ constexpr uint32_t kThinPaths = 64;
 // of theirs keeps its slot (and its LDS) for most of a pass, and two passes, an
 // eye pass and a range query are under way at once.  With all slots taken the
 // eye pass, whose waves mostly wait, became the longest stage: 1.9 ms instead of
-// 0.4.  1280x720, 2^20 photons, ms an iteration in calls of 8: all waves for
-// either launch 1.20, half for the first and a quarter for the second 1.09
-// (3/4 and 1/4 1.10, 3/8 and 1/4 1.10, 1/2 and 1/8 1.19).
-constexpr uint32_t kHeadShare = 2, kTailShare = 4;
+// 0.4.  1280x720, 2^20 photons, ms an iteration in calls of 8 (and of 1): all
+// waves for either launch 1.20, half for the first and a quarter for the second
+// 1.09 (3/4 and 1/4 1.10, 3/8 and 1/4 1.10, 1/2 and 1/8 1.19).  With the binary
+// walk, whose passes are bound by waiting and gain from more waves, all and a
+// half: 1.79 (2.67); all and all 1.96 (2.66), half and a quarter 1.91 (3.09).
+struct Shares {
+    uint32_t head, tail;
+};
+static Shares shares_of(const pm_sppm *s) { return s->wide ? Shares{2, 4} : Shares{1, 2}; }
 
 // The photon schedule a handle runs: the default is the two-phase pass on
 // single-scene handles and regeneration for a batch member (whose photon
@@ -894,6 +919,7 @@ int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t 
         if ((rc = upload_bvh(hb, st, s->bvh))) return fail(rc);
     }
     const pm_bvh *b = s->bvh;
+    s->wide = b->d_wide != nullptr && p->single_link_set == 0;
     s->P = (int64_t)d->width * d->height;
     // emitters in original triangle order, by power = area * Le
     std::vector<uint32_t> epos;
@@ -927,22 +953,19 @@ int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t 
         PM_HIPF(hipGetDevice(&dev));
         s->device = dev;
         PM_HIPF(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_regen, kBlock, 0));
-        s->regen_grid = (uint32_t)std::max(1, cus * std::max(1, per_cu));
-        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_regen_rec, kBlock, 0));
-        s->regen_grid_rec = (uint32_t)std::max(1, cus * std::max(1, per_cu));
-        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_stream, kBlock, 0));
-        s->stream_grid = (uint32_t)std::max(1, cus * std::max(1, per_cu));
-        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_pool<false>, kBlock, 0));
-        s->pool_grid = (uint32_t)std::max(1, cus * std::max(1, per_cu));
-        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_head<false>, kBlock, 0));
-        s->head_grid = (uint32_t)std::max(1, cus * std::max(1, per_cu));
-        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_tail<false>, kBlock, 0));
-        s->tail_grid = (uint32_t)std::max(1, cus * std::max(1, per_cu));
-        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_head_rec, kBlock, 0));
-        s->head_grid_rec = (uint32_t)std::max(1, cus * std::max(1, per_cu));
-        PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_photon_tail_rec, kBlock, 0));
-        s->tail_grid_rec = (uint32_t)std::max(1, cus * std::max(1, per_cu));
+        const std::pair<uint32_t *, const void *> grids[] = {
+            {&s->regen_grid, (const void *)pick(s, k_photon_regen<true>, k_photon_regen<false>)},
+            {&s->regen_grid_rec, (const void *)pick(s, k_photon_regen_rec<true>, k_photon_regen_rec<false>)},
+            {&s->stream_grid, (const void *)k_photon_stream},
+            {&s->pool_grid, (const void *)k_photon_pool<false>},
+            {&s->head_grid, (const void *)pick(s, k_photon_head<false, true>, k_photon_head<false, false>)},
+            {&s->tail_grid, (const void *)pick(s, k_photon_tail<false, true>, k_photon_tail<false, false>)},
+            {&s->head_grid_rec, (const void *)pick(s, k_photon_head_rec<true>, k_photon_head_rec<false>)},
+            {&s->tail_grid_rec, (const void *)pick(s, k_photon_tail_rec<true>, k_photon_tail_rec<false>)}};
+        for (const auto &g : grids) {
+            PM_HIPF(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, g.second, kBlock, 0));
+            *g.first = (uint32_t)std::max(1, cus * std::max(1, per_cu));
+        }
     }
     const int32_t photon_kernel = photon_kernel_of(p, own_grid);
     const bool pipelined = own_grid && !(p->profile & PM_PROFILE_TIME);
@@ -952,10 +975,9 @@ int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t 
             np <= waves * kThinPaths)
             s->thin = (uint32_t)std::min<int64_t>(std::max<int64_t>((2 * np + waves - 1) / waves, kMinPathsPerWave),
                                                   kThinPaths);
-        if (pipelined)
-            for (uint32_t *head : {&s->head_grid, &s->head_grid_rec}) *head = std::max(1u, *head / kHeadShare);
-        if (pipelined)
-            for (uint32_t *tail : {&s->tail_grid, &s->tail_grid_rec}) *tail = std::max(1u, *tail / kTailShare);
+        const Shares part = pipelined ? shares_of(s) : Shares{1, 1};
+        for (uint32_t *head : {&s->head_grid, &s->head_grid_rec}) *head = std::max(1u, *head / part.head);
+        for (uint32_t *tail : {&s->tail_grid, &s->tail_grid_rec}) *tail = std::max(1u, *tail / part.tail);
     }
     // a stream per slot (two where the photon passes share one): see photon_queue
     const uint32_t slots = !pipelined ? 1u : (photon_kernel == PM_PHOTON_TWO_PHASE ? kRing : 2u);
@@ -1274,7 +1296,7 @@ static int enqueue_photon(pm_sppm *s, const SppmDev &dk, uint32_t k, bool count,
     const uint32_t np = (uint32_t)s->prm.n_photons;
     hipLaunchKernelGGL(k_photon_begin, dim3(1), dim3(64), 0, q, dk, s->thin ? np : 0u);
     if (s->thin) {
-        hipLaunchKernelGGL(k_photon<false>, dim3(blocks_for_waves(np, s->thin)), dim3(kBlock), 0, q, dk, k, s->thin,
+        hipLaunchKernelGGL(pick(s, k_photon<false, true>, k_photon<false, false>), dim3(blocks_for_waves(np, s->thin)), dim3(kBlock), 0, q, dk, k, s->thin,
                            (uint16_t *)nullptr, (long long *)nullptr);
         PM_HIP(hipGetLastError());
         return PM_OK;
@@ -1283,13 +1305,13 @@ static int enqueue_photon(pm_sppm *s, const SppmDev &dk, uint32_t k, bool count,
         const PathQueue &pq = s->queue[k % s->ring];
         hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, q, pq.cnt, 1u, 0u);
         if (count)
-            hipLaunchKernelGGL(k_photon_head<true>, dim3(s->head_grid), dim3(kBlock), 0, q, dk, k, pq);
+            hipLaunchKernelGGL((k_photon_head<true, false>), dim3(s->head_grid), dim3(kBlock), 0, q, dk, k, pq);
         else
-            hipLaunchKernelGGL(k_photon_head<false>, dim3(s->head_grid), dim3(kBlock), 0, q, dk, k, pq);
+            hipLaunchKernelGGL(pick(s, k_photon_head<false, true>, k_photon_head<false, false>), dim3(s->head_grid), dim3(kBlock), 0, q, dk, k, pq);
         if (count)
-            hipLaunchKernelGGL(k_photon_tail<true>, dim3(s->tail_grid), dim3(kBlock), 0, q, dk, pq);
+            hipLaunchKernelGGL((k_photon_tail<true, false>), dim3(s->tail_grid), dim3(kBlock), 0, q, dk, pq);
         else
-            hipLaunchKernelGGL(k_photon_tail<false>, dim3(s->tail_grid), dim3(kBlock), 0, q, dk, pq);
+            hipLaunchKernelGGL(pick(s, k_photon_tail<false, true>, k_photon_tail<false, false>), dim3(s->tail_grid), dim3(kBlock), 0, q, dk, pq);
     } else if (dk.photon_kernel == PM_PHOTON_RAY_REGEN) {
         if (count)
             hipLaunchKernelGGL(k_photon_stream_stats, dim3(s->stream_grid), dim3(kBlock), 0, q, dk, k);
@@ -1304,17 +1326,17 @@ static int enqueue_photon(pm_sppm *s, const SppmDev &dk, uint32_t k, bool count,
         if (count)
             hipLaunchKernelGGL(k_photon_regen_stats, dim3(s->regen_grid), dim3(kBlock), 0, q, dk, k);
         else
-            hipLaunchKernelGGL(k_photon_regen, dim3(s->regen_grid), dim3(kBlock), 0, q, dk, k);
+            hipLaunchKernelGGL(pick(s, k_photon_regen<true>, k_photon_regen<false>), dim3(s->regen_grid), dim3(kBlock), 0, q, dk, k);
     } else if (dk.photon_kernel == PM_PHOTON_PASSES) {
         const PassSlots &ps = s->slots;
         hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(2 * (int64_t)ps.S)), dim3(kBlock), 0, q, (uint32_t *)ps.nb,
                            2u * ps.S, kSlotIdle);
         for (int32_t j = 0; j < s->n_pass; ++j)
-            hipLaunchKernelGGL(k_photon_pass, dim3(blocks_for(ps.S)), dim3(kBlock), 0, q, dk, k, ps);
+            hipLaunchKernelGGL(pick(s, k_photon_pass<true>, k_photon_pass<false>), dim3(blocks_for(ps.S)), dim3(kBlock), 0, q, dk, k, ps);
         hipLaunchKernelGGL(k_pass_tally, dim3(1), dim3(64), 0, q, dk);
-        hipLaunchKernelGGL(k_photon_drain, dim3(blocks_for(ps.S)), dim3(kBlock), 0, q, dk, k, ps);
+        hipLaunchKernelGGL(pick(s, k_photon_drain<true>, k_photon_drain<false>), dim3(blocks_for(ps.S)), dim3(kBlock), 0, q, dk, k, ps);
     } else {
-        hipLaunchKernelGGL(k_photon<false>, dim3(blocks_for(np)), dim3(kBlock), 0, q, dk, k, 64u, (uint16_t *)nullptr,
+        hipLaunchKernelGGL(pick(s, k_photon<false, true>, k_photon<false, false>), dim3(blocks_for(np)), dim3(kBlock), 0, q, dk, k, 64u, (uint16_t *)nullptr,
                            (long long *)nullptr);
     }
     PM_HIP(hipGetLastError());
@@ -1335,7 +1357,7 @@ static int enqueue_photon(pm_sppm *s, const SppmDev &dk, uint32_t k, bool count,
 // passes on one stream, the next pass waited out a whole photon pass: 8
 // iterations at 1280x720 with 2^20 photons went from 10.6 to 8.8 ms, 4 of the
 // stochastic gather at 640x360 with 2^18 from 2.2 to 1.8, with the shares of the
-// device at kHeadShare.  At the end of the call the caller's stream has waited
+// device at shares_of.  At the end of the call the caller's stream has waited
 // for every stream.  Results are those of the serial order.
 static int run_iterations(pm_sppm *s, int32_t n_iter, hipStream_t caller, Forked &forked) {
     const uint32_t T = 1u << s->table_bits;
@@ -1349,7 +1371,8 @@ static int run_iterations(pm_sppm *s, int32_t n_iter, hipStream_t caller, Forked
         if (count)
             hipLaunchKernelGGL(k_eye_stats, dim3(blocks_for(s->P)), dim3(kBlock), 0, q, dv, kk, 1);
         else
-            hipLaunchKernelGGL(k_eye, dim3(blocks_for(s->P)), dim3(kBlock), 0, q, dv, kk, 1);
+            hipLaunchKernelGGL(pick(s, k_eye<true>, k_eye<false>), dim3(blocks_for(s->P)), dim3(kBlock), 0, q, dv, kk,
+                               1);
     };
     // photon and eye pass of iteration k, once their slot's readers of ring
     // iterations ago (the first `ring` of a call follow all earlier work) are done
@@ -1555,17 +1578,17 @@ static int adjoint_overlapped(pm_sppm *s, const float *g, hipStream_t caller, Fo
         hipLaunchKernelGGL(k_photon_begin, dim3(1), dim3(64), 0, q, dk, s->thin ? np : 0u);
         hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, q, (uint32_t *)(max_of(k) + 1), 2u, 0u);
         if (s->thin) {
-            hipLaunchKernelGGL(k_photon<true>, dim3(blocks_for_waves(np, s->thin)), dim3(kBlock), 0, q, dk, k, s->thin,
+            hipLaunchKernelGGL(pick(s, k_photon<true, true>, k_photon<true, false>), dim3(blocks_for_waves(np, s->thin)), dim3(kBlock), 0, q, dk, k, s->thin,
                                mat_of(k), tab_of(k));
         } else if (s->dev.photon_kernel == PM_PHOTON_TWO_PHASE) {
             const PathQueue &pq = s->queue[k % s->ring];
             hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, q, pq.cnt, 1u, 0u);
-            hipLaunchKernelGGL(k_photon_head_rec, dim3(s->head_grid_rec), dim3(kBlock), 0, q, dk, k, pq,
+            hipLaunchKernelGGL(pick(s, k_photon_head_rec<true>, k_photon_head_rec<false>), dim3(s->head_grid_rec), dim3(kBlock), 0, q, dk, k, pq,
                                mat_of(k), tab_of(k));
-            hipLaunchKernelGGL(k_photon_tail_rec, dim3(s->tail_grid_rec), dim3(kBlock), 0, q, dk, pq, mat_of(k),
+            hipLaunchKernelGGL(pick(s, k_photon_tail_rec<true>, k_photon_tail_rec<false>), dim3(s->tail_grid_rec), dim3(kBlock), 0, q, dk, pq, mat_of(k),
                                tab_of(k));
         } else {
-            hipLaunchKernelGGL(k_photon_regen_rec, dim3(s->regen_grid_rec), dim3(kBlock), 0, q, dk, k,
+            hipLaunchKernelGGL(pick(s, k_photon_regen_rec<true>, k_photon_regen_rec<false>), dim3(s->regen_grid_rec), dim3(kBlock), 0, q, dk, k,
                                mat_of(k), tab_of(k));
         }
         hipLaunchKernelGGL(k_adj_phimax, dim3(std::min<uint32_t>(ph_blocks, kAdjMaxBlocks)), dim3(kBlock), 0, q, dk,
@@ -1583,7 +1606,7 @@ static int adjoint_overlapped(pm_sppm *s, const float *g, hipStream_t caller, Fo
         const double *R2k = s->R2_hist + (size_t)k * s->P;
         if (k >= s->ring) PM_HIP(hipStreamWaitEvent(q, s->ev_upd[k % s->ring], 0));
         hipLaunchKernelGGL(k_rmax_clear, dim3(1), dim3(64), 0, q, dk);
-        hipLaunchKernelGGL(k_eye, dim3(blocks_for(s->P)), dim3(kBlock), 0, q, dk, k, 0);
+        hipLaunchKernelGGL(pick(s, k_eye<true>, k_eye<false>), dim3(blocks_for(s->P)), dim3(kBlock), 0, q, dk, k, 0);
         hipLaunchKernelGGL(k_rmax, dim3(std::min(blocks_for(s->P), kRmaxBlocks)), dim3(kBlock), 0, q, dk, R2k);
         hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, q, (uint32_t *)max_of(k), 2u, 0u);
         hipLaunchKernelGGL(k_adj_gmax, dim3(std::min<uint32_t>(blocks_for(s->P), kAdjMaxBlocks)), dim3(kBlock), 0,
@@ -1647,12 +1670,12 @@ static int adjoint_serial(pm_sppm *s, const float *g, hipStream_t st, Forked &fo
         PM_HIP(hipStreamWaitEvent(side, s->ev_fork, 0));
         forked.q[0] = side;
         forked.n = 1;
-        hipLaunchKernelGGL(k_eye, dim3(blocks_for(s->P)), dim3(kBlock), 0, side, d, (uint32_t)k, 0);
+        hipLaunchKernelGGL(pick(s, k_eye<true>, k_eye<false>), dim3(blocks_for(s->P)), dim3(kBlock), 0, side, d, (uint32_t)k, 0);
         hipLaunchKernelGGL(k_rmax, dim3(std::min(blocks_for(s->P), kRmaxBlocks)), dim3(kBlock), 0, side, d, R2k);
         hipLaunchKernelGGL(k_adj_gmax, dim3(std::min<uint32_t>(blocks_for(s->P), kAdjMaxBlocks)), dim3(kBlock), 0,
                            side, d, R2k, g, K, s->adj_max);
         PM_HIP(hipEventRecord(s->ev_join, side));
-        hipLaunchKernelGGL(k_photon_regen_rec, dim3(s->regen_grid_rec), dim3(kBlock), 0, st, d, (uint32_t)k,
+        hipLaunchKernelGGL(pick(s, k_photon_regen_rec<true>, k_photon_regen_rec<false>), dim3(s->regen_grid_rec), dim3(kBlock), 0, st, d, (uint32_t)k,
                            s->mat_tab[0], s->adj_tab[0]);
         hipLaunchKernelGGL(k_adj_phimax, dim3(std::min<uint32_t>(ph_blocks, kAdjMaxBlocks)), dim3(kBlock), 0, st, d,
                            s->adj_max);

@@ -98,11 +98,11 @@ constexpr int kStackWords = 64 * kWideStack;
 // at 1280x720 with 2^20 photons, a refill of 16 lanes: 8.66 ms with 8, 8.50 with
 // 12, 8.46 with 16, 8.7 with 24).
 constexpr uint32_t kSppmLate = 16;
-// Wavefronts per SIMD that the kernels with a path and a walk ask for: at most
-// 128 registers.  At 5 (96 registers) up to 27 of them spill: 7.2 against 6.3
-// ms for a 333x187 render, 9.6 and 9.7 for 8 iterations at 1280x720; at 6
-// every case is slower than at 5.
-#define PM_PASS_WAVES __attribute__((amdgpu_waves_per_eu(4)))
+// Wavefronts per SIMD that the kernels with a path and a walk ask for.  With the
+// wide walk four, at most 128 registers: at 5 (96 registers) up to 27 of them
+// spill: 7.2 against 6.3 ms for a 333x187 render, 9.6 and 9.7 for 8 iterations
+// at 1280x720; at 6 every case is slower than at 5.  The binary walk fits in 96.
+#define PM_PASS_WAVES __attribute__((amdgpu_waves_per_eu(kWide ? 4 : 5)))
 
 // Closest hits of one ray per lane, called by all lanes of a wave (active:
 // this lane has a ray; the others return -1).  stk is the wave's stack

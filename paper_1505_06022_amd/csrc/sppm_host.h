@@ -33,6 +33,7 @@ struct pm_sppm {
     uint32_t tail_grid = 1;       // and of its second
     uint32_t head_grid_rec = 1;   // the same two launches recording for the adjoint replay
     uint32_t tail_grid_rec = 1;
+    bool wide = false;            // its rays take the wide walk (else the binary one)
     uint32_t thin = 0;            // paths per wave of a small default photon pass (one launch), else 0
     float phi0 = 0.0f;
     // device buffers, all within the one allocation `arena`

@@ -72,3 +72,35 @@ def run(lib: str, code: str) -> str:
     r = subprocess.run([sys.executable, "-c", text], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout + r.stderr
     return r.stdout
+
+
+def kernels(library: str) -> dict:
+    """Name -> metadata (registers, LDS) of the kernels that this repository's build put into a library."""
+    import struct
+
+    import msgpack
+    data, out, at = open(library, "rb").read(), {}, 0
+    while (at := data.find(b"__CLANG_OFFLOAD_BUNDLE__", at)) >= 0:
+        (n,), p = struct.unpack_from("<Q", data, at + 24), at + 32
+        for _ in range(n):
+            offset, size, length = struct.unpack_from("<QQQ", data, p)
+            name = data[p + 24:p + 24 + length]
+            p += 24 + length
+            if b"gfx950" in name:
+                out.update(_elf_kernels(data[at + offset:at + offset + size], struct, msgpack))
+        at += 24
+    return out
+
+
+def _elf_kernels(elf, struct, msgpack):
+    sections, = struct.unpack_from("<Q", elf, 40)
+    size, count = struct.unpack_from("<HH", elf, 58)
+    for i in range(count):
+        kind, = struct.unpack_from("<I", elf, sections + i * size + 4)
+        offset, length = struct.unpack_from("<QQ", elf, sections + i * size + 24)
+        if kind == 7:  # a note: name and description, each padded to four bytes
+            names, desc, _ = struct.unpack_from("<III", elf, offset)
+            start = offset + 12 + (names + 3) // 4 * 4
+            meta = msgpack.unpackb(elf[start:start + desc], strict_map_key=False)
+            return {k[".name"]: k for k in meta["amdhsa.kernels"]}
+    return {}
