@@ -90,15 +90,16 @@ __device__ __forceinline__ int64_t stage_elems(const SppmDev &d) {
 // Persistent stage kernel: every workgroup loops taking items until the
 // stage's item count is exhausted (each item is taken exactly once, so every
 // workgroup reaches the exit).  kHits: hit points per wave of the range query.
-template <int kStage, int kBs, int kHits = 64>
-__global__ __launch_bounds__(kBs) __attribute__((amdgpu_waves_per_eu(kStage <= kStPhoton ? 4 : 1)))
+// kWide: the stages that trace rays have the wide walk's stacks, for a batch
+// with a scene that takes it.  32 scenes that all force one link set take 26.3 ms
+// an iteration without its LDS and registers (five waves a SIMD), 32.6 with them.
+template <int kStage, int kBs, int kHits = 64, bool kWide = false>
+__global__ __launch_bounds__(kBs) __attribute__((amdgpu_waves_per_eu(kStage > kStPhoton ? 1 : (kWide ? 4 : 5))))
 void k_batch(BatchDev b) {
     __shared__ uint32_t s_item;
-    // the wide walk's stacks (the stages that trace rays)
-    __shared__ uint32_t wide_stack[kStage == kStEye || kStage == kStPhoton ? kBs / 64 : 1]
-                                  [kStage == kStEye || kStage == kStPhoton ? kStackWords : 1];
+    __shared__ uint32_t wide_stack[kWide ? kBs / 64 : 1][kWide ? kStackWords : 1];
     __shared__ float4 photon_buf[kStage == kStPhoton ? kBs / 64 : 1][kStage == kStPhoton ? kSinkWords : 1];
-    uint32_t *const stk = kStage == kStEye || kStage == kStPhoton ? wide_stack[threadIdx.x >> 6] : nullptr;
+    uint32_t *const stk = kWide ? wide_stack[threadIdx.x >> 6] : nullptr;
     const uint32_t *off = b.item_off + kStage * (b.S + 1);
     const uint32_t total = off[b.S];
     const uint32_t k = *b.iter;
@@ -207,6 +208,7 @@ struct pm_batch {
     uint32_t chunk = 1024;
     int32_t block = 256;
     int32_t hits = 64;  // hit points per wave of the range query
+    bool wide = false;  // some scene's rays take the wide walk
     RayItems rays{};
     int64_t pixels = 0, paths = 0;  // of all scenes
     bool use_graph = true;
@@ -252,7 +254,10 @@ int occupancy_grids(pm_batch *b) {
     int dev = 0, cus = 0;
     PM_HIP(hipGetDevice(&dev));
     PM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    const void *kern[kNumStages] = {(const void *)k_batch<kStEye, kBs>, (const void *)k_batch<kStPhoton, kBs>,
+    const void *kern[kNumStages] = {b->wide ? (const void *)k_batch<kStEye, kBs, 64, true>
+                                            : (const void *)k_batch<kStEye, kBs>,
+                                    b->wide ? (const void *)k_batch<kStPhoton, kBs, 64, true>
+                                            : (const void *)k_batch<kStPhoton, kBs>,
                                     (const void *)k_batch<kStRmax, kBs>, (const void *)k_batch<kStCount, kBs>,
                                     (const void *)k_batch<kStScatter, kBs>,
                                     b->hits == 64 ? (const void *)k_batch<kStGather, kBs>
@@ -270,8 +275,14 @@ template <int kBs>
 void enqueue_stage(const pm_batch *b, int stage, const BatchDev &bd, hipStream_t st) {
     dim3 g(b->grid[stage]), blk(kBs);
     switch (stage) {
-        case kStEye: hipLaunchKernelGGL((k_batch<kStEye, kBs>), g, blk, 0, st, bd); break;
-        case kStPhoton: hipLaunchKernelGGL((k_batch<kStPhoton, kBs>), g, blk, 0, st, bd); break;
+        case kStEye:
+            if (b->wide) hipLaunchKernelGGL((k_batch<kStEye, kBs, 64, true>), g, blk, 0, st, bd);
+            else hipLaunchKernelGGL((k_batch<kStEye, kBs>), g, blk, 0, st, bd);
+            break;
+        case kStPhoton:
+            if (b->wide) hipLaunchKernelGGL((k_batch<kStPhoton, kBs, 64, true>), g, blk, 0, st, bd);
+            else hipLaunchKernelGGL((k_batch<kStPhoton, kBs>), g, blk, 0, st, bd);
+            break;
         case kStRmax: hipLaunchKernelGGL((k_batch<kStRmax, kBs>), g, blk, 0, st, bd); break;
         case kStCount: hipLaunchKernelGGL((k_batch<kStCount, kBs>), g, blk, 0, st, bd); break;
         case kStScatter: hipLaunchKernelGGL((k_batch<kStScatter, kBs>), g, blk, 0, st, bd); break;
@@ -544,6 +555,7 @@ int batch_create(const pm_scene_desc *const *descs, const pm_sppm_params *const 
         cap += m->cap;
         b->pixels += m->P;
         b->paths += m->prm.n_photons;
+        b->wide = b->wide || m->wide;
         devs[i] = m->dev;
     }
     if (tot >= (uint64_t(1) << 31) || cap >= (uint64_t(1) << 31))

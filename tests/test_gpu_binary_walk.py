@@ -36,3 +36,18 @@ def test_equals_the_wide_walk(torch_cuda, kernel, photons, link_set):
     assert float(out[0][-1].abs().max()) > 0.0
     for a, b in zip(*out):
         assert torch_cuda.equal(a, b)
+
+
+@pytest.mark.parametrize("chunk", [64, 1024])
+def test_batch(torch_cuda, chunk):
+    """Without, with some and with all scenes on the binary walk."""
+    scs = [scenes.box_scene(64, 48), scenes.procedural_scene(width=80, height=50, hf_cells=20, sphere_level=2,
+                                                             glass_level=2, seed=4)]
+    images = []
+    for sets in ((0, 0), (0, 2), (5, 2)):
+        print("case: batch, chunk", chunk, "sets", sets, flush=True)
+        prm = [api.sppm_params(9_001, r0=0.05, seed=7 + i, single_link_set=k) for i, k in enumerate(sets)]
+        images.append(api.render_batch(scs, prm, 3, chunk=chunk))
+    for other in images[1:]:
+        for a, b in zip(images[0], other):
+            assert torch_cuda.equal(a, b)

@@ -1,5 +1,5 @@
-"""Handles whose rays take only the binary walk launch kernels without the other
-walk's stacks, and their photon passes take the device they need.
+"""Handles and batches whose rays take only the binary walk launch kernels without
+the other walk's stacks, and their photon passes take the device they need.
 
 On the CPU: the kernels that a stand-in for the HIP runtime is asked to launch,
 and the LDS that the built library reserves for them.
@@ -71,3 +71,28 @@ def test_binary_walk_kernels_have_no_stacks(lib, lds, why):
         grid = {g for k, g in binary["auto"] if part in k}
         assert grid == {256 * 4 // share}, (part, grid)
         assert {g for k, g in wide["auto"] if part in k} == {256 * 4 // share // 2}
+
+
+BATCH = """
+import json
+st = new_stream()
+out = dict()
+for name, sets in dict(wide=(0, 0), mixed=(0, 2), binary=(1, 6)).items():
+    scs = [scenes.box_scene(16, 16), scenes.box_scene(24, 16)]
+    prm = [api.sppm_params(1 << 12, single_link_set=k) for k in sets]
+    b = api.Batch(scs, prm, stream=st, {opts})
+    b.iterate(1, stream=st)
+    out[name] = [c[1] for c in log() if c[0] == "launch" and "k_batchILi" in c[1]]
+    b.destroy()
+print(json.dumps(out))
+"""
+
+
+@pytest.mark.parametrize("opts", ["block=128", "block=256", "block=256, use_graph=False"])
+def test_batch_of_binary_walks_has_no_stacks(lib, lds, opts):
+    out = json.loads(fake_hip.run(lib, BATCH.format(opts=opts)).splitlines()[-1])
+    waves = 2 if "128" in opts else 4
+    for name, kernels in out.items():
+        assert len(kernels) == 7
+        most = max(lds[k] for k in kernels)
+        assert most >= waves * STACK if name != "binary" else most <= waves * SINK + 4, (name, most)
