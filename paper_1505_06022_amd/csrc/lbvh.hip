@@ -556,8 +556,12 @@ int build_bvh_gpu(const float *verts_h, const uint32_t *mats_h, int64_t n_tri, i
 
     // 5. records
     const uint32_t n_nodes = (uint32_t)r.n_nodes;
-    // zeroed pad nodes after the six arrays (a packet walk reads the node after the one it visits)
-    PM_HIP(hipMalloc(&b->d_nodes, sizeof(uint4) * (kLinkSets * (size_t)n_nodes + pm::kPadNodes)));
+    // zeroed pad nodes after the six arrays (a packet walk reads the node after the one it visits),
+    // then the four-child nodes of a small tree: at most one for each inner node
+    const bool small = n_nodes <= kHostMerge;
+    const size_t node_bytes = sizeof(uint4) * (kLinkSets * (size_t)n_nodes + pm::kPadNodes),
+                 o_wide = (node_bytes + 255) & ~(size_t)255;
+    PM_HIP(hipMalloc(&b->d_nodes, small ? o_wide + 4 * sizeof(uint4) * (n_nodes / 2 + 1) : node_bytes));
     PM_HIP(hipMemsetAsync(b->d_nodes + kLinkSets * (size_t)n_nodes, 0, sizeof(uint4) * pm::kPadNodes, s));
     hipLaunchKernelGGL(k_lb_thread, dim3(lb_blocks((int64_t)n_all)), dim3(kLb), 0, s, n, max_leaf,
                        (const uint4 *)link, (const int4 *)kids, (const UpNode *)node, n_nodes, trav_cost, b->d_nodes,
@@ -576,11 +580,26 @@ int build_bvh_gpu(const float *verts_h, const uint32_t *mats_h, int64_t n_tri, i
         b->qstep[a] = r.qstep[a];
     }
 
-    // 6. four-child nodes (their first launches do not need the results read here)
-    WideBuild wide;
-    if (int rc = wide.launch(b, s)) return rc;
-    PM_HIP(hipMemcpyAsync(back.data(), pos, sizeof(int32_t) * back.size(), hipMemcpyDeviceToHost, s));
-    if (int rc = wide.finish(b, s)) return rc;
+    // 6. four-child nodes
+    if (small) {
+        std::vector<uint32_t> binary(4 * (size_t)n_nodes), merged;
+        PM_HIP(hipMemcpyAsync(binary.data(), b->d_nodes, sizeof(uint4) * n_nodes, hipMemcpyDeviceToHost, s));
+        PM_HIP(hipMemcpyAsync(back.data(), pos, sizeof(int32_t) * back.size(), hipMemcpyDeviceToHost, s));
+        PM_HIP(hipStreamSynchronize(s));
+        if (int rc = merge_wide_host(b, binary.data(), merged)) return rc;
+        if (!merged.empty()) {
+            b->n_wide = (int64_t)(merged.size() / 16);
+            b->d_wide = (uint4 *)((char *)b->d_nodes + o_wide);
+            b->wide_inside = true;
+            PM_HIP(hipMemcpyAsync(b->d_wide, merged.data(), sizeof(uint32_t) * merged.size(), hipMemcpyHostToDevice, s));
+            PM_HIP(hipStreamSynchronize(s));
+        }
+    } else {
+        WideBuild wide;
+        if (int rc = wide.launch(b, s)) return rc;  // (does not need the results read here)
+        PM_HIP(hipMemcpyAsync(back.data(), pos, sizeof(int32_t) * back.size(), hipMemcpyDeviceToHost, s));
+        if (int rc = wide.finish(b, s)) return rc;
+    }
     memcpy(&r, back.data() + pos_words, sizeof(r));
     back.resize((size_t)n);
     b->pos_of = std::move(back);

@@ -42,6 +42,7 @@ struct pm_bvh {
     uint4 *d_wide = nullptr;    // [n_wide][4] four-child nodes of the wide walk (NULL: binary walks only)
     int64_t n_wide = 0;
     float4 *d_tris = nullptr;   // [n_refs][3]
+    bool wide_inside = false, tris_inside = false;  // they lie in the nodes' allocation
     uint32_t *d_next = nullptr; // work counter of the persistent traversal kernel, after the triangles
     uint32_t *d_perm = nullptr; // ray order of the reordering traversal (perm_cap entries)
     uint64_t perm_cap = 0;
@@ -78,6 +79,19 @@ int build_bvh_gpu(const float *verts, const uint32_t *mats, int64_t n_tri, int m
 // Upload a host-built BVH; fills b (device buffers owned by b).
 int upload_bvh(const HostBvh &h, hipStream_t s, pm_bvh *b);
 void free_bvh(pm_bvh *b);
+
+// Nodes up to which a tree's four-child nodes are merged on the host: the device
+// takes 50 to 80 us for a small tree, the host less below some 10,000 nodes.  Builds on
+// the device, us, merged on the device and on the host: 1 node 183 and 139, 1,103
+// nodes 247 and 184, 7,825 nodes 323 and 271, 15,665 nodes 401 and 377, 38,363
+// nodes 537 and 658; on the host 1,103 nodes 1,127 and 980, 7,825 nodes 7,330 and
+// 7,156.
+constexpr int64_t kHostMerge = 8192;
+
+// That merge: the nodes of link set 0 (host) to the words of the four-child
+// nodes, 16 each (none: the tree is too deep).  The handle's node count and box
+// grid are read.
+int merge_wide_host(const pm_bvh *b, const uint32_t *nodes, std::vector<uint32_t> &out);
 
 // Merges the binary tree of a BVH's link set 0 into the four-child nodes of the
 // wide walk: launch() enqueues the work once the binary nodes are enqueued on

@@ -16,9 +16,14 @@
 // its threads) or when its list is full.  For 92,000 binary nodes two launches
 // do it in 67 us where one launch for each of 16 levels took 117, and 160 with
 // the gaps between them.
+//
+// A small tree (kHostMerge) is merged on the host by the same code: the launches,
+// two allocations and two synchronisations of the merge were half of the build of
+// a 36-triangle box.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <vector>
 
 #include "runtime.h"
 #include "sppm_scan.h"
@@ -47,9 +52,9 @@ struct GridStep {
     float s[3];
 };
 
-__device__ __forceinline__ bool is_leaf(const uint4 &q) { return (q.w >> 31) != 0u; }
+__host__ __device__ __forceinline__ bool is_leaf(const uint4 &q) { return (q.w >> 31) != 0u; }
 
-__device__ __forceinline__ float box_area(const uint4 &q, const GridStep &g) {
+__host__ __device__ __forceinline__ float box_area(const uint4 &q, const GridStep &g) {
     const float x = (float)((q.x >> 16) - (q.x & 0xffffu)) * g.s[0], y = (float)((q.y >> 16) - (q.y & 0xffffu)) * g.s[1],
                 z = (float)((q.z >> 16) - (q.z & 0xffffu)) * g.s[2];
     return x * y + y * z + z * x;
@@ -58,8 +63,8 @@ __device__ __forceinline__ float box_area(const uint4 &q, const GridStep &g) {
 // The (at most four) children of the wide node at binary node v.  A tree of
 // one leaf gives that leaf as the only child.  A link outside the n nodes (an
 // inconsistent tree) gives n = -1.
-__device__ __forceinline__ Kids wide_children(const uint4 *__restrict__ nodes, uint32_t n, uint32_t v,
-                                              const GridStep &g) {
+__host__ __device__ __forceinline__ Kids wide_children(const uint4 *__restrict__ nodes, uint32_t n, uint32_t v,
+                                                       const GridStep &g) {
     Kids k;
     const uint4 root = nodes[v];
     if (is_leaf(root)) {
@@ -105,6 +110,13 @@ __device__ __forceinline__ Kids wide_children(const uint4 *__restrict__ nodes, u
         open = k.id[at];
     }
     return k;
+}
+
+// Record i of the wide node with these children, an inner child's still with
+// the binary node's link.
+__host__ __device__ __forceinline__ uint4 wide_record(const Kids &k, int i) {
+    // an unused slot: an inverted box, and a leaf of no triangles should its test pass all the same
+    return i < k.n ? k.rec[i] : make_uint4(0x0000ffffu, 0x0000ffffu, 0x0000ffffu, 0x80000000u);
 }
 
 // A node to expand: binary node, level of its wide node.
@@ -179,19 +191,54 @@ __global__ __launch_bounds__(kWb) void k_wide_emit(const uint4 *__restrict__ nod
     const Kids k = wide_children(nodes, n, v, g);
     uint4 *out = wide + 4 * (size_t)index[v];
     for (int i = 0; i < 4; ++i) {
-        // an unused slot: an inverted box, and a leaf of no triangles should its test pass all the same
-        uint4 q = make_uint4(0x0000ffffu, 0x0000ffffu, 0x0000ffffu, 0x80000000u);
-        if (i < k.n) {
-            q = k.rec[i];
-            if (!is_leaf(q)) q.w = index[k.id[i]];
-        }
+        uint4 q = wide_record(k, i);
+        if (i < k.n && !is_leaf(q)) q.w = index[k.id[i]];
         out[i] = q;
     }
+}
+
+GridStep grid_step(const pm_bvh *b) {
+    GridStep g;
+    for (int a = 0; a < 3; ++a) g.s[a] = b->qstep[a];
+    return g;
 }
 
 }  // namespace
 
 namespace pm {
+
+int merge_wide_host(const pm_bvh *b, const uint32_t *binary, std::vector<uint32_t> &out) {
+    const uint4 *nodes = (const uint4 *)binary;
+    const uint32_t n = (uint32_t)b->n_nodes;
+    const GridStep g = grid_step(b);
+    // in the order of the binary nodes: a node's inner children are taken in theirs, a subtree before the next
+    struct Todo {
+        uint32_t node, level, slot;  // slot: where its parent has its index
+    };
+    std::vector<Todo> todo;
+    out.clear();
+    out.reserve(4 * (size_t)n + 16);
+    todo.push_back({0u, 0u, 0u});
+    while (!todo.empty()) {
+        const Todo e = todo.back();
+        todo.pop_back();
+        const Kids k = wide_children(nodes, n, e.node, g);
+        if (k.n < 0) return set_error("inconsistent binary tree"), PM_ERR_STATE;
+        const uint32_t at = (uint32_t)out.size();
+        if (at) out[e.slot] = at / 16;
+        out.resize(at + 16);
+        const size_t first = todo.size();
+        for (int i = 0; i < 4; ++i) {
+            const uint4 q = wide_record(k, i);
+            const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+            std::copy(w, w + 4, out.begin() + at + 4 * i);
+            if (i < k.n && !is_leaf(k.rec[i])) todo.push_back({k.id[i], e.level + 1u, at + 4u * i + 3u});
+        }
+        if (todo.size() > first && e.level + 1u >= kWideLevels) return out.clear(), PM_OK;  // too deep
+        std::sort(todo.begin() + first, todo.end(), [](const Todo &x, const Todo &y) { return x.node > y.node; });
+    }
+    return PM_OK;
+}
 
 WideBuild::~WideBuild() {
     if (mem_) (void)hipFree(mem_);
@@ -209,8 +256,7 @@ static int allocate(void **mem, size_t bytes) {
 }
 
 int WideBuild::expand(const pm_bvh *b, hipStream_t s, uint32_t upto) {
-    GridStep g;
-    for (int a = 0; a < 3; ++a) g.s[a] = b->qstep[a];
+    const GridStep g = grid_step(b);
     for (; launches_ < upto; ++launches_)
         hipLaunchKernelGGL(k_wide_expand, dim3(launches_ == 0 ? 1u : kWideGrid), dim3(kWb), 0, s,
                            (const uint4 *)b->d_nodes, n_, launches_, g, cnt_, (const uint2 *)list_[launches_ & 1u],
@@ -256,8 +302,7 @@ int WideBuild::finish(pm_bvh *b, hipStream_t s) {
         if (launches_ == kWideLevels || c[launches_] == 0u) break;
         if (int rc = expand(b, s, std::min(launches_ + kWideFirst, kWideLevels))) return rc;
     }
-    GridStep g;
-    for (int a = 0; a < 3; ++a) g.s[a] = b->qstep[a];
+    const GridStep g = grid_step(b);
     if (int rc = allocate((void **)&b->d_wide, sizeof(uint4) * 4 * (size_t)read[0])) return rc;
     if (!b->d_wide) return PM_OK;
     b->n_wide = read[0];
