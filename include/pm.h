@@ -535,7 +535,12 @@ typedef struct pm_batch pm_batch;
 
 typedef struct {
     uint32_t size;     /* sizeof(pm_batch_opts) */
-    int32_t chunk;     /* elements (pixels, paths, photons) per work item; 0 = 1024 */
+    int32_t chunk;     /* elements per work item (pixels; eight times as many paths;
+                          the photons of the grid stages), 0 = 1024.  Pixel and path
+                          items of the stages that trace rays are smaller where a
+                          batch would not give every workgroup two of them, and the
+                          range query of a batch of up to 2^19 pixels has items of
+                          its own */
     int32_t block;     /* workgroup size: 0 (= 256), 128 or 256 */
     int32_t autotune;  /* 1: time every (chunk, block) candidate and keep the fastest
                           (result cached on disk: $PM_AUTOTUNE_CACHE, default

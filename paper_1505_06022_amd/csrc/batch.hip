@@ -42,7 +42,7 @@ constexpr int64_t kBatchSmall = 1 << 19;
 
 // Elements of the items of the stages that trace rays: a chunk of pixels,
 // kPhotonItem chunks of paths, but no more than gives every resident workgroup
-// kItemsPerGroup items (at least one round of the workgroup).  Items of 8,192
+// kItemsPerGroup items, where that is at least one round of the workgroup.  Items of 8,192
 // paths gave a batch of 2^20 paths 128 items for 1,024 workgroups: 3.6 ms a
 // photon stage, 1.4 now.
 constexpr int64_t kItemsPerGroup = 2;
@@ -408,12 +408,17 @@ int reset_all(pm_batch *b, hipStream_t st) {
     return PM_OK;
 }
 
+// What a measured (chunk, block) holds for.  kItemRules is raised whenever what
+// chunk and block mean for the items changes: a pair measured under other rules
+// is not found again.
+constexpr int kItemRules = 2;
+
 std::string signature(const pm_batch *b) {
     std::ostringstream os;
     int dev = 0;
     hipDeviceProp_t prop;
     if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess) os << prop.gcnArchName;
-    os << ":" << b->S;
+    os << ":rules" << kItemRules << (b->wide ? "w" : "b") << ":" << b->S;
     for (const pm_sppm *m : b->members)
         os << ":" << m->P << "," << m->prm.n_photons << "," << (m->bvh ? m->bvh->n_tri : 0);
     std::string s = os.str();
