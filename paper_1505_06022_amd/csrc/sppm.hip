@@ -627,6 +627,17 @@ static void destroy_streams(PassStreams &p) {
     }
 }
 
+// Whether the streams of a kept set still exist: a device reset ends them.
+static bool alive(const PassStreams &p) {
+    bool ok = true;
+    for (hipStream_t q : {p.pass[0], p.pass[1], p.pass[2], p.main}) {
+        const hipError_t e = hipStreamQuery(q);
+        ok = ok && (e == hipSuccess || e == hipErrorNotReady);
+    }
+    (void)hipGetLastError();
+    return ok;
+}
+
 // A set of streams of the current device.
 static hipError_t take_streams(int device, PassStreams &out) {
     {
@@ -635,7 +646,8 @@ static hipError_t take_streams(int device, PassStreams &out) {
             if (g_pool[i].device == device) {
                 out = g_pool[i].set;
                 g_pool[i] = g_pool[--g_pool_n];
-                return hipSuccess;
+                if (alive(out)) return hipSuccess;
+                out = PassStreams{};
             }
     }
     hipStream_t even[3] = {};
