@@ -324,7 +324,8 @@ typedef struct {
     int32_t record_iterations; /* > 0: record what pm_sppm_adjoint needs for
                                   up to this many iterations (8 B per pixel
                                   per iteration, plus 10 B x n_photons x
-                                  max_photon_bounces of replay scratch);
+                                  max_photon_bounces of replay scratch for
+                                  each slot, see pm_sppm_create);
                                   needs gather_mode 0, at most 256 materials
                                   and fewer than 2^24 pixels */
     int32_t photon_kernel;    /* PM_PHOTON_*: 0 = default (two-phase
@@ -399,10 +400,11 @@ enum { PM_GATHER_EXACT = 0, PM_GATHER_STOCHASTIC = 1 };
  * device memory (56 B per path, at most one per lane of the launch) and the
  * second launch continues them.  A path that reflects inside a glass object
  * can run to max_photon_bounces, so the last paths of a pass leave the device
- * almost idle: on a pipelined handle the second launch runs on a stream of
- * its own, beside the next iteration's first launch.  AUTO runs a pass of few
- * paths (up to 64 for each wavefront the device holds) in one launch instead,
- * the paths spread evenly over the wavefronts. */
+ * almost idle: the two launches follow each other on one of the handle's
+ * streams, beside the passes of the next iterations on its others, and each
+ * takes a part of the device.  AUTO runs a pass of few paths (up to 64 for each
+ * wavefront the device holds) in one launch instead, the paths spread evenly
+ * over the wavefronts. */
 enum {
     PM_PHOTON_AUTO = 0,
     PM_PHOTON_PER_PATH = 1,
@@ -415,16 +417,26 @@ enum {
 
 /* Create a renderer: uploads the scene (building a BVH if desc->bvh is NULL)
  * and allocates the per-pixel state (N = 0, R^2 = r0^2, tau = 0, D = 0).
- * The handle owns all device buffers it allocates. */
+ * The handle owns all device buffers it allocates.
+ * Iterations overlap: what an iteration writes before its grid is built lies in
+ * one of three slots (photon kernels REGEN, PASSES, RAY_REGEN, POOL and PER_PATH:
+ * two; with PM_PROFILE_TIME one), each 40 B per pixel, 32 B per photon of the
+ * store's capacity and, with record_iterations, the replay scratch.  Where
+ * device memory does not hold them, the handle makes do with fewer; results do
+ * not change.  PM_ERR_NOMEM: not even one fits.
+ * A handle uses four streams of the default priority.  Up to four such sets are
+ * kept for later handles when handles are destroyed, for the life of the
+ * process; a set is used by one handle at a time. */
 PM_API int pm_sppm_create(const pm_scene_desc *desc, const pm_sppm_params *params, void *stream, pm_sppm **out);
 PM_API int pm_sppm_destroy(pm_sppm *s);
 
 /* Enqueue n_iter iterations (eye pass, photon pass, hashed-grid build,
  * range query, progressive update).  Counts stay on the device; a photon
  * store overflow sets a sticky device flag reported by pm_sppm_status.
- * Within an iteration the eye pass runs on a stream the handle owns, forked
- * from `stream` and joined back to it by events before the range query, so
- * everything enqueued later on `stream` sees the finished iteration. */
+ * The iterations of a call run on streams the handle owns, forked from `stream`
+ * and joined back to it by events (while `stream` is being captured the grid,
+ * range query and update stay on it), so everything enqueued later on `stream`
+ * sees the finished iterations, also after a call that failed on the way. */
 PM_API int pm_sppm_iterate(pm_sppm *s, int32_t n_iter, void *stream);
 
 /* Radiance estimate of the iterations so far into `image` (device, float32

@@ -497,7 +497,7 @@ using Walker = WalkerT<false>;
 // Wide walk: the closest hit through nodes of four children (64 bytes: four
 // records in the layout of the binary node, whose link word names an inner
 // child's wide node or a leaf's triangles).  The nodes are the binary tree of
-// link set 0 with levels merged (build_wide), so the boxes and the box test,
+// link set 0 with levels merged (wide.hip), so the boxes and the box test,
 // and with them the proof that no accepted hit is culled, are those of the
 // binary walk; children are taken by entry distance and the rest wait on a
 // stack in LDS.  The closest hit under the lower-index tie rule does not

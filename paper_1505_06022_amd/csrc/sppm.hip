@@ -166,8 +166,9 @@ __global__ __launch_bounds__(kBlock) PM_PASS_WAVES void k_photon_drain(SppmDev d
     photon_drain_elem(d, k, ps, xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x, stk, sink);
 }
 
-// Start of a photon pass: clear its store's photon count; handed: paths that
-// are handed out from the start (all, in a pass without the path counter).
+// Start of a photon pass: clear its store's photon count; handed: where the path
+// counter starts (0; the default pass of few paths, which does not use it, leaves
+// the number of its paths there).
 __global__ void k_photon_begin(SppmDev d, uint32_t handed) {
     if (threadIdx.x == 0) {
         d.counters[0] = 0u;
@@ -1180,9 +1181,11 @@ int sppm_create_ex(const pm_scene_desc *d, const pm_sppm_params *p, hipStream_t 
     // default schedule: 8.71 ms with 16, 8.87 with 32, 9.73 with 44 for 8 iterations at 1280x720 with 2^20 photons
     dv.refill = p->refill > 0 ? (uint32_t)p->refill : (p->photon_kernel == PM_PHOTON_AUTO ? 16u : 32u);
     dv.force_set = p->single_link_set - 1;
-    // Paired node requests pay off on one large scene (2.65 -> 2.55 ms per
-    // iteration of the 250k-triangle scene) but not on the many small scenes
-    // of a batch, whose BVHs stay in cache (24.5 -> 25.3 ms).
+    // Binary walks only (one link set, ray regeneration, the pool, a BVH without
+    // four-child nodes): paired node requests pay off on one large scene (2.65 ->
+    // 2.55 ms an iteration of the 250k-triangle scene when all passes took that
+    // walk) but not on the many small scenes of a batch, whose BVHs stay in cache
+    // (24.5 -> 25.3 ms).
     dv.paired_walk = own_grid ? 1 : 0;
     dv.gather_mode = p->gather_mode;
     dv.sh_key = s->sh_key;
@@ -1417,7 +1420,7 @@ static int run_iterations(pm_sppm *s, int32_t n_iter, hipStream_t caller, Forked
             hipLaunchKernelGGL(k_rmax, dim3(std::min(blocks_for(s->P), kRmaxBlocks)), dim3(kBlock), 0, st, dk,
                                (const double *)s->R2);
         } else {
-            // eye pass and R_max on a second stream, beside the photon pass:
+            // one iteration at a time: eye pass and R_max on a second stream, beside the photon pass:
             // they share no data, and the eye pass's long specular paths would
             // otherwise leave the device idle at its end
             hipStream_t side = s->streams.pass[1];
@@ -1447,7 +1450,7 @@ static int run_iterations(pm_sppm *s, int32_t n_iter, hipStream_t caller, Forked
             if (timed) PM_HIP(hipEventRecord(ev[6], st));
             hipLaunchKernelGGL(k_sh_gather, dim3(blocks_for(s->P)), dim3(kBlock), 0, st, dk,
                                (const uint32_t *)s->cell_count);
-            // this gather reads the photon store itself: only now may the pass of k + 2 refill it
+            // this gather reads the photon store itself: only now may the pass of k + ring refill it
             if (pipe) PM_HIP(hipEventRecord(s->ev_scat[k % s->ring], st));
         } else {
             hipLaunchKernelGGL(k_count, dim3(ph_blocks), dim3(kBlock), 0, st, dk, s->cell_count);

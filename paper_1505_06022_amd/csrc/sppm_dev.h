@@ -44,7 +44,7 @@ struct SppmDev {
     int32_t photon_kernel;    // PM_PHOTON_* (resolved: per path or regenerating)
     uint32_t refill;          // regeneration: idle lanes that trigger a refill
     int32_t force_set;        // -1: link set by ray direction; 0..5: that set for every ray
-    int32_t paired_walk;      // 1: walks request nodes i and i + 1 together (single-scene handles)
+    int32_t paired_walk;      // 1: binary walks request nodes i and i + 1 together (single-scene handles)
     int32_t gather_mode;      // PM_GATHER_EXACT or PM_GATHER_STOCHASTIC
     unsigned long long *sh_key;  // stochastic hashing: smallest (depth, photon id) per entry
     uint32_t *sh_surv;           // stochastic hashing: store index of each entry's survivor
@@ -475,8 +475,9 @@ __device__ __forceinline__ void slot_store(const PassSlots &ps, uint32_t s, cons
 // on an almost idle device.  The first launch (regeneration) stops once the
 // path counter has run out and at most kParkLive lanes of a wavefront still
 // hold a path: those paths go to a queue in device memory and the wavefront
-// exits.  A second launch, on a stream of its own, continues the queued
-// paths, so the first launch of the next iteration can start beside it.
+// exits.  A second launch continues the queued paths.  It follows the first on
+// that iteration's stream and on a part of the device, so the passes of the next
+// iterations, on their streams, run beside it.
 // Each path consumes its random stream as in photon_elem, so the photons are
 // the same.
 constexpr uint32_t kParkLive = 32;
