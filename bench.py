@@ -8,8 +8,8 @@ rays plus 2^21 incoherent rays.  One step = closest-hit traversal of all
 tiles, one per wavefront (--coherent), the incoherent batch after bucketing by
 (origin cell, link set) (--incoherent), both through the four-child nodes; every
 option listed in KERNEL_VARIANTS gives identical results and is also timed.
-The JSON line reports Mrays/s, the traversal's bytes against the memory roofline,
-the CPU oracle timed on the host, the SPPM iteration on the 250k-triangle
+The JSON line reports Mrays/s, the shares of issue cycles and of memory bandwidth
+that the committed counters give the timed call, the CPU oracle timed on the host, the SPPM iteration on the 250k-triangle
 procedural scene, the adjoint-to-forward time ratio and the batched renderer.
 
 python bench.py [--steps K] [--warmup W] [--no-cpu-baseline] [--no-sppm] [--no-adjoint] [--no-batch]
@@ -26,8 +26,8 @@ import numpy as np
 
 HBM_PEAK_GBS = 8000.0
 ROOT = os.path.dirname(os.path.abspath(__file__))
-TRACE_SOURCES = ["paper_1505_06022_amd/csrc/pm_device.h", "paper_1505_06022_amd/csrc/trace.hip",
-                 "paper_1505_06022_amd/csrc/wide.hip", "paper_1505_06022_amd/csrc/bvh_build.cpp"]
+TRACE_SOURCES = ["paper_1505_06022_amd/csrc/" + f for f in ("pm_device.h", "trace.hip", "wide.hip", "bvh_build.cpp",
+                                                            "sppm_scan.h", "runtime.h")]
 
 
 # Traversal options compared by the bench (names usable with --coherent/--incoherent)
@@ -77,10 +77,10 @@ def _kw_for(kw: dict, batch: int) -> dict:
     return d
 
 
-def measured_traffic():
-    """HBM bytes per traversal call (both batches) from the committed counter
-    record, or None when the traversal sources changed since the counters were
-    taken."""
+def measured_counters():
+    """What the committed counter record says of one traversal call: bytes between
+    L2 and memory (both batches) and the busy shares of the launch that walks
+    them; None when the traversal sources changed since the counters were taken."""
     import hashlib
     h = hashlib.sha256()
     for f in TRACE_SOURCES:
@@ -95,7 +95,8 @@ def measured_traffic():
     if rec["sources_sha256_16"] != h.hexdigest()[:16]:
         return None
     # the record lists each batch; one timed call traces all of them
-    return 1024.0 * (rec["fetch_factor"] * sum(rec["fetch_kib"]) + rec["write_factor"] * sum(rec["write_kib"]))
+    return dict(bytes=1024.0 * (rec["fetch_factor"] * sum(rec["fetch_kib"]) + rec["write_factor"] * sum(rec["write_kib"])),
+                valu_busy=rec["valu_busy"], valu_lanes=rec["valu_lanes"], l1_data_busy=rec["l1_data_busy"])
 
 
 def measured_sppm_traffic():
@@ -339,16 +340,23 @@ def traversal_bench(args, torch, api, scenes):
                                          "step_ms": round(ms, 4), "mrays_s": round(n_rays / ms / 1e3, 1)}
             bv.destroy()
         variants["spatial_splits"] = spl
-    avg_launch_ms = kern_ms.mean()
-    # bytes of a call, both batches: between L2 and memory where the counters were taken on these sources, else those
-    # of the binary walk's visits
-    traffic = measured_traffic()
-    per_launch_bytes = traffic if traffic else alg_bytes
-    achieved = per_launch_bytes / (avg_launch_ms * 1e-3) / 1e9
+    # the incoherent batch on the binary tree's per-ray walk, whose visits the counters above count
+    e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    binary_ms = []
+    for rep in range(4):
+        e[0].record(stream)
+        api.trace_rays(bvh, batches[1], *outs[1], kernel=api.TRACE_PER_RAY, reorder=1, block=64)
+        e[1].record(stream)
+        torch.cuda.synchronize()
+        binary_ms.append(e[0].elapsed_time(e[1]))
+    # bytes of a call, both batches, between L2 and memory, where the counters were taken on these sources
+    counters = measured_counters()
+    achieved = counters["bytes"] / (kern_ms.mean() * 1e-3) / 1e9 if counters else None
     hit_frac = float((outs[0][0] >= 0).float().mean().item())
     return dict(
         n_rays=n_rays, step_ms=step_ms, kern_ms=kern_ms, batch_ms=batch_ms, info=info, per_batch=per_batch,
-        achieved=achieved, per_launch_bytes=per_launch_bytes, alg_bytes=alg_bytes, hit_frac=hit_frac, variants=variants, tbvh=tbvh,
+        achieved=achieved, counters=counters, alg_bytes=alg_bytes, hit_frac=hit_frac, variants=variants, tbvh=tbvh,
+        binary_ms=float(np.mean(binary_ms[1:])),
         lbvh=lbvh, prewarm_steps=prewarm_steps, split_alpha=split_alpha, trav_cost=trav_cost,
         coherent_mrays=len(rc) / (batch_ms[0] * 1e-3) / 1e6,
         incoherent_mrays=len(ri) / (batch_ms[1] * 1e-3) / 1e6,
@@ -363,8 +371,8 @@ def sppm_roofline(api, sc, p_kw, bvh, iters=4):
     with HIP events on the streams they run on (PM_PROFILE_TIME); both run
     `iters` iterations after two warm-up ones.  Bytes per unit:
       eye pass + R_max  per eye ray 32 B ray + 8 B result + 16 B per box test
-                        + 48 B per triangle test; per pixel 32 B hit point
-                        written, 16 B of D read and written, 12 B for R_max
+                        + 48 B per triangle test; per pixel 32 B hit point and
+                        8 B emission written, 12 B for R_max
       photon pass       the same per photon ray, + 32 B per stored photon
       hashed grid       per stored photon: count 16 B read + 4 B atomic + 8 B
                         (bucket, rank) written; scatter 8 + 32 + 4 B read and
@@ -374,9 +382,11 @@ def sppm_roofline(api, sc, p_kw, bvh, iters=4):
                         per bucket visited; 16 B per photon examined and 16 B
                         more per photon accepted (a lower bound: a photon inside
                         the disc that faces away is read but not counted)
-      update            per pixel 8 B (M, hit-point flag); per hit point 32 B
-                        read and 24 B written (an upper bound: hit points with
-                        M = 0 are skipped)"""
+      update            per pixel 8 B (M, hit-point flag) and 24 B (emission, D
+                        read and written); per hit point 32 B read and 24 B
+                        written (an upper bound: hit points with M = 0 are skipped)
+    The visits counted are the binary tree's; the four-child walk of the eye and
+    photon passes makes fewer, so their rates come from the committed counters."""
     res = {}
     for flag in (api.PROFILE_COUNT, api.PROFILE_TIME):
         h = api.Sppm(sc, api.sppm_params(profile=flag, **p_kw), bvh=bvh)
@@ -399,19 +409,24 @@ def sppm_roofline(api, sc, p_kw, bvh, iters=4):
         return 40.0 * q[prefix + "_rays"] + 16.0 * q[prefix + "_box_tests"] + 48.0 * q[prefix + "_tri_tests"]
 
     stages = {
-        "eye": (rays("eye") + 60.0 * P, t["ms_eye"] / nt),
+        "eye": (rays("eye") + 52.0 * P, t["ms_eye"] / nt),
         "photon": (rays("photon") + 32.0 * q["photons_stored"], t["ms_photon"] / nt),
         "grid": (104.0 * q["photons_stored"] + 8.0 * T, t["ms_grid"] / nt),
         "gather": (28.0 * P + 24.0 * q["gather_hit_points"] + 8.0 * q["gather_buckets"] +
                    16.0 * q["gather_examined"] + 16.0 * q["gather_accepted"], t["ms_gather"] / nt),
-        "update": (8.0 * P + 56.0 * q["gather_hit_points"], t["ms_update"] / nt),
+        "update": (32.0 * P + 56.0 * q["gather_hit_points"], t["ms_update"] / nt),
     }
+    # the passes that trace rays: what counts is the memory traffic of the walk that runs, where the committed counters
+    # hold for these sources (the counted visits are the binary tree's)
     traffic = measured_sppm_traffic()
     out = {}
     for name, (b, ms) in stages.items():
-        gbs = b / (ms * 1e-3) / 1e9
-        out[name] = {"bytes": round(b), "ms": round(ms, 4), "GBps": round(gbs, 1),
-                     "frac": round(gbs / HBM_PEAK_GBS, 4),
+        walks = name in ("eye", "photon")
+        used = traffic[name] if traffic and walks else None if walks else b
+        gbs = used / (ms * 1e-3) / 1e9 if used else None
+        out[name] = {"binary_walk_bytes" if walks else "bytes": round(b), "ms": round(ms, 4),
+                     "GBps": round(gbs, 1) if gbs else None,
+                     "frac": round(gbs / HBM_PEAK_GBS, 4) if gbs else None,
                      "traffic": round(traffic[name]) if traffic else None}
     counts = {k: round(v, 1) for k, v in q.items()}
     per_unit = {"eye_rays_per_pixel": round(q["eye_rays"] / P, 3),
@@ -781,6 +796,7 @@ def main():
                           "workload": sp["workload"]}), flush=True)
         return
     tb = traversal_bench(args, torch, api, scenes)
+    counters = tb["counters"] or dict.fromkeys(("bytes", "valu_busy", "valu_lanes", "l1_data_busy"))
     out = {
         "metric": "Mrays/s traversal + SPPM photons/s; fwd+adjoint vs fwd time at matched RMSE",
         # value: the first part (closest-hit traversal, MTBVH); the other two are
@@ -820,28 +836,34 @@ def main():
                           if tb["tbvh"] else None),
         "traversal_stats": [{"rays": int(n), "boxes_per_ray": round(vn / n, 2), "tris_per_ray": round(vt / n, 2)}
                             for vn, vt, n in tb["per_batch"]],
-        "roofline": {"bound": "hbm", "achieved": round(tb["achieved"], 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": round(tb["achieved"] / HBM_PEAK_GBS, 4), "traffic": measured_traffic(),
+        # the walk is bound by vector issue and the L1 data path together: their busy shares in the launch that walks
+        # both batches, and its memory traffic, all from the committed counters (null where the sources changed since)
+        "roofline": {"bound": "vector issue", "unit": "share of issue cycles", "peak": 1.0,
+                     "achieved": counters["valu_busy"], "frac": counters["valu_busy"],
+                     "valu_lanes": counters["valu_lanes"], "l1_data_busy": counters["l1_data_busy"],
+                     "hbm": {"achieved": round(tb["achieved"], 1) if tb["achieved"] else None, "peak": HBM_PEAK_GBS,
+                             "unit": "GB/s", "frac": round(tb["achieved"] / HBM_PEAK_GBS, 4) if tb["achieved"] else None,
+                             "bytes_per_call": counters["bytes"]},
                      "kernel": "pm_trace_rays_multi call: k_hist_count + column and bucket scans + k_hist_scatter, then one launch of "
                                "k_trace_perm_then_tiles (the incoherent batch, then the camera batch's 8x8 pixel "
                                "tiles, both through the four-child nodes)",
-                     "bytes_per_launch": tb["per_launch_bytes"], "binary_walk_bytes": tb["alg_bytes"],
                      "avg_launch_ms": round(float(tb["kern_ms"].mean()), 4),
                      "alone_ms_by_batch": [round(float(x), 4) for x in tb["batch_ms"]]},
     }
     ach = achievable_bandwidth(torch, api)
     best = max(ach["copy_GBps"], ach["read_GBps"])
-    out["roofline"]["achievable"] = dict(ach, frac=round(tb["achieved"] / best, 4))
-    # the incoherent walk (visits of the binary walk per second, bucketing included) against chains of dependent
-    # random reads of that length per lane: over a BVH-sized buffer (reads served by the Infinity Cache and
-    # HBM) and over 4 MiB (one XCD's L2 holds it: the most that the binary walk could reach)
+    out["roofline"]["hbm"]["achievable"] = dict(ach, frac=round(tb["achieved"] / best, 4) if tb["achieved"] else None)
+    # the binary tree's per-ray walk of the incoherent batch (its visits per second, bucketing included) against chains
+    # of dependent random reads of that length per lane: over a BVH-sized buffer (reads served by the Infinity Cache
+    # and HBM) and over 4 MiB (one XCD's L2 holds it: the most that this walk could reach)
     vn_inc, _, n_inc = tb["per_batch"][1]
     steps = max(1, int(round(vn_inc / n_inc)))
-    node_rate = vn_inc / (float(tb["batch_ms"][1]) * 1e-3)
+    node_rate = vn_inc / (tb["binary_ms"] * 1e-3)
     far = dependent_read_rate(torch, api, n_inc, steps, log2_rows=24)
     near = dependent_read_rate(torch, api, n_inc, steps, log2_rows=18)
-    out["roofline"]["achievable"]["dependent_reads"] = {
-        "binary_walk_visits_per_s": round(node_rate, 1), "random_256MiB": far, "random_4MiB": near,
+    out["binary_walk"] = {
+        "incoherent_ms": round(tb["binary_ms"], 4), "counted_bytes_both_batches": tb["alg_bytes"],
+        "visits_per_s": round(node_rate, 1), "random_256MiB": far, "random_4MiB": near,
         "frac_of_4MiB": round(node_rate / near["reads_per_s"], 4),
         "ratio_to_256MiB": round(node_rate / far["reads_per_s"], 3)}
     if not args.no_sppm:
