@@ -484,22 +484,48 @@ inline uint32_t fbits(float f) {
 // Checked in runs without a branch on each value, which the compiler turns into
 // vector code: 131,072 triangles take 35 us (65 with 16-byte vectors, 240 value
 // by value).
-__attribute__((target_clones("avx2", "default")))
-int64_t first_not_finite(const float *v, int64_t n) {
+#ifdef __HIP_DEVICE_COMPILE__  // (the device's pass over host code knows no such clones)
+#define PM_VECTOR_CLONES
+#else
+#define PM_VECTOR_CLONES __attribute__((target_clones("avx2", "default")))
+#endif
+PM_VECTOR_CLONES
+int64_t not_finite_in(const float *v, int64_t b0, int64_t n) {
     constexpr int64_t kCheck = 4096;
-    for (int64_t b = 0; b < n; b += kCheck) {
+    for (int64_t b = b0; b < n; b += kCheck) {
         const int64_t e = std::min(b + kCheck, n);
-        uint32_t over = 0;  // an exponent of all ones carries into the sign bit
+        uint32_t most = 0;
         for (int64_t i = b; i < e; ++i) {
             uint32_t w;
             std::memcpy(&w, v + i, sizeof(w));
-            over |= (w & 0x7fffffffu) + 0x00800000u;
+            most = std::max(most, w & 0x7fffffffu);
         }
-        if (over >> 31)
+        if (most >= 0x7f800000u)  // an exponent of all ones
             for (int64_t i = b; i < e; ++i)
                 if (!std::isfinite(v[i])) return i;
     }
     return -1;
+}
+
+// Parts of at least kPart values, each on a thread: one core's memory bandwidth
+// bounds the check, 0.83 ms for 2^20 triangles on one thread and 0.4 on four; at
+// 2^18 triangles (0.08 ms) a second thread gains nothing.
+int64_t first_not_finite(const float *v, int64_t n) {
+    constexpr int64_t kPart = int64_t(1) << 21, kParts = 8;
+    const int64_t parts = std::min(n / kPart, kParts);
+    if (parts < 2) return not_finite_in(v, 0, n);
+    const int64_t len = (n / parts + 4095) & ~int64_t(4095);
+    std::vector<std::future<int64_t>> rest;
+    for (int64_t p = 1; p < parts; ++p) {
+        const int64_t b = std::min(p * len, n), e = p + 1 == parts ? n : std::min(b + len, n);
+        rest.push_back(std::async(std::launch::async | std::launch::deferred, not_finite_in, v, b, e));
+    }
+    int64_t bad = not_finite_in(v, 0, len);
+    for (auto &f : rest) {
+        const int64_t at = f.get();
+        if (bad < 0) bad = at;
+    }
+    return bad;
 }
 
 bool build_bvh_host(const float *verts, const uint32_t *mats, int64_t n_tri, const BuildOptions &opt, HostBvh &out,
