@@ -31,6 +31,7 @@ const char *last_error() { return g_err.c_str(); }
 
 int hip_fail(hipError_t e, const char *what) {
     g_err = std::string(what) + ": " + hipGetErrorString(e);
+    (void)hipGetLastError();  // returned here: not the next call's (the runtime keeps it until it is read)
     return e == hipErrorOutOfMemory ? PM_ERR_NOMEM : PM_ERR_HIP;
 }
 

@@ -1,4 +1,5 @@
-"""A call that fails on the way leaves no work that its caller's stream does not wait for.
+"""A call that fails on the way leaves no work that its caller's stream does not wait for,
+and no error for the next call to report.
 
 On the CPU, with a stand-in for the HIP runtime: each runtime call that an
 iteration or an adjoint makes fails once, and the streams and events that the
@@ -52,9 +53,9 @@ def sweep(call):
                 assert False, ("no error", what, nth)
             except api.PMError as e:
                 assert e.code == api.PM_ERR_HIP
-            fake.hipGetLastError()  # reported: not the next call's
             loose = unjoined(log(), st.cuda_stream)
             assert not loose, (call.__name__, what, nth, loose)
+            assert fake.hipGetLastError() == 0, (call.__name__, what, nth)
 iterate()
 if recorded:
     sweep(adjoint)
