@@ -581,11 +581,16 @@ int build_bvh_gpu(const float *verts_h, const uint32_t *mats_h, int64_t n_tri, i
     }
 
     // 6. four-child nodes
+    auto results = [&]() -> int {
+        memcpy(&r, back.data() + pos_words, sizeof(r));
+        return r.bad ? (set_error("GPU BVH build: inconsistent tree"), PM_ERR_STATE) : PM_OK;
+    };
     if (small) {
         std::vector<uint32_t> binary(4 * (size_t)n_nodes), merged;
         PM_HIP(hipMemcpyAsync(binary.data(), b->d_nodes, sizeof(uint4) * n_nodes, hipMemcpyDeviceToHost, s));
         PM_HIP(hipMemcpyAsync(back.data(), pos, sizeof(int32_t) * back.size(), hipMemcpyDeviceToHost, s));
         PM_HIP(hipStreamSynchronize(s));
+        if (int rc = results()) return rc;
         if (int rc = merge_wide_host(b, binary.data(), merged)) return rc;
         if (!merged.empty()) {
             b->n_wide = (int64_t)(merged.size() / 16);
@@ -599,11 +604,10 @@ int build_bvh_gpu(const float *verts_h, const uint32_t *mats_h, int64_t n_tri, i
         if (int rc = wide.launch(b, s)) return rc;  // (does not need the results read here)
         PM_HIP(hipMemcpyAsync(back.data(), pos, sizeof(int32_t) * back.size(), hipMemcpyDeviceToHost, s));
         if (int rc = wide.finish(b, s)) return rc;
+        if (int rc = results()) return rc;
     }
-    memcpy(&r, back.data() + pos_words, sizeof(r));
     back.resize((size_t)n);
     b->pos_of = std::move(back);
-    if (r.bad) return set_error("GPU BVH build: inconsistent tree"), PM_ERR_STATE;
     b->n_leaves = (int64_t)r.leaves;
     b->depth = (int32_t)r.depth;
     b->sah_cost = r.sah;

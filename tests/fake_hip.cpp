@@ -77,6 +77,9 @@ void fake_fail(const char *name, long nth, int code) { g_fail[name] = {nth, (hip
 // Device memory in bytes, and what is allocated of it.
 void fake_memory(size_t bytes) { g_memory = bytes; }
 size_t fake_used() { return g_used; }
+// The block allocated last.
+void *g_last_block = nullptr;
+void *fake_last_block() { return g_last_block; }
 void fake_capture(intptr_t stream, int on) {
     if (on) g_capturing.insert(stream);
     else g_capturing.erase(stream);
@@ -136,7 +139,7 @@ hipError_t hipDeviceSynchronize() { FAKE_CALL("hipDeviceSynchronize", line("sync
 hipError_t hipMalloc(void **p, size_t bytes) {
     if (g_used + bytes > g_memory) return g_last = hipErrorOutOfMemory;
     FAKE_CALL("hipMalloc", line("malloc %zu", bytes); *p = std::calloc(bytes + 256, 1); g_blocks[*p] = bytes;
-              g_used += bytes);
+              g_used += bytes; g_last_block = *p);
 }
 hipError_t hipFree(void *p) {
     if (p && !g_blocks.count(p)) return g_last = hipErrorInvalidValue;

@@ -20,6 +20,7 @@ fake.fake_take_log.restype = ctypes.c_char_p
 fake.fake_fail.argtypes = [ctypes.c_char_p, ctypes.c_long, ctypes.c_int]
 fake.fake_memory.argtypes = [ctypes.c_size_t]
 fake.fake_used.restype = ctypes.c_size_t
+fake.fake_last_block.restype = ctypes.c_void_p
 fake.fake_capture.argtypes = [ctypes.c_ssize_t, ctypes.c_int]
 fake.fake_take_log()
 import numpy as np
