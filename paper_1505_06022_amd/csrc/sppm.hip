@@ -1783,7 +1783,6 @@ int sppm_save(pm_sppm *s, void *buf, uint64_t *size, hipStream_t st) {
     }
     uint32_t c[4 * kRing];
     PM_HIP(hipMemcpyAsync(c, s->counters, sizeof(c), hipMemcpyDeviceToHost, st));
-    c[1] |= c[5] | c[9];
     CheckpointHeader h{};
     memcpy(h.magic, "PMSPPMCK", 8);
     h.version = kCheckpointVersion;
@@ -1809,7 +1808,7 @@ int sppm_save(pm_sppm *s, void *buf, uint64_t *size, hipStream_t st) {
     if (n_hist > 0)
         PM_HIP(hipMemcpyAsync(out + sizeof(h) + 4 * pb, s->R2_hist, pb * (size_t)n_hist, hipMemcpyDeviceToHost, st));
     PM_HIP(hipStreamSynchronize(st));
-    h.overflow = c[1];
+    h.overflow = c[1] | c[5] | c[9];  // the sticky flags of all slots, now that the copy has ended
     memcpy(out, &h, sizeof(h));
     *size = need;
     return PM_OK;

@@ -1,8 +1,9 @@
 // A stand-in for the HIP runtime on the CPU, for tests of the library's host
 // code: which calls it makes, in which order, on which streams, and what it does
 // when one fails.  Loaded with RTLD_GLOBAL before libpm.so, whose calls then
-// resolve here.  Memory is the host's, copies and fills are made, kernels are
-// logged and not run.  One thread at a time.
+// resolve here.  Memory is the host's; copies and fills are made, those to the
+// host when their stream is waited for, as late as the runtime may make them;
+// kernels are logged and not run.  One thread at a time.
 //
 // Log lines (streams and events by number; stream 0 is the null stream):
 //   malloc BYTES | free | copy BYTES STREAM | fill BYTES STREAM | sync STREAM (-1: the device)
@@ -16,6 +17,7 @@
 #include <map>
 #include <set>
 #include <string>
+#include <vector>
 
 namespace {
 
@@ -24,6 +26,13 @@ std::map<const void *, std::string> g_kernels;
 std::map<std::string, std::pair<long, hipError_t>> g_fail;  // calls until the one that fails
 std::map<void *, size_t> g_blocks;
 size_t g_used = 0, g_memory = ~size_t(0);
+struct Late {
+    intptr_t stream;
+    void *to;
+    const void *from;
+    size_t bytes;
+};
+std::vector<Late> g_late;  // copies to the host
 std::set<intptr_t> g_streams, g_capturing;
 intptr_t g_next = 1;
 hipError_t g_last = hipSuccess;
@@ -40,6 +49,16 @@ bool fails(const char *name) {
 }
 hipError_t known(hipStream_t s) {
     return s && !g_streams.count(id(s)) ? g_last = hipErrorInvalidHandle : hipSuccess;
+}
+
+// The stream (-1: every one) has been waited for.
+void arrive(intptr_t stream) {
+    std::vector<Late> rest;
+    for (const Late &c : g_late) {
+        if (stream == -1 || c.stream == stream) std::memcpy(c.to, c.from, c.bytes);
+        else rest.push_back(c);
+    }
+    g_late.swap(rest);
 }
 
 template <class... A>
@@ -134,7 +153,7 @@ hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600 *p, int) {
 hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size_t) {
     FAKE_CALL("hipOccupancy", *n = 4);
 }
-hipError_t hipDeviceSynchronize() { FAKE_CALL("hipDeviceSynchronize", line("sync %d", -1)); }
+hipError_t hipDeviceSynchronize() { FAKE_CALL("hipDeviceSynchronize", line("sync %d", -1); arrive(-1)); }
 
 hipError_t hipMalloc(void **p, size_t bytes) {
     if (g_used + bytes > g_memory) return g_last = hipErrorOutOfMemory;
@@ -143,10 +162,12 @@ hipError_t hipMalloc(void **p, size_t bytes) {
 }
 hipError_t hipFree(void *p) {
     if (p && !g_blocks.count(p)) return g_last = hipErrorInvalidValue;
-    FAKE_CALL("hipFree", line("%s", "free"); if (p) g_used -= g_blocks[p]; g_blocks.erase(p); std::free(p));
+    FAKE_CALL("hipFree", line("%s", "free"); arrive(-1); if (p) g_used -= g_blocks[p]; g_blocks.erase(p); std::free(p));
 }
-hipError_t hipMemcpyAsync(void *to, const void *from, size_t bytes, hipMemcpyKind, hipStream_t s) {
-    FAKE_ON("hipMemcpyAsync", s, line("copy %zu %ld", bytes, id(s)); std::memcpy(to, from, bytes));
+hipError_t hipMemcpyAsync(void *to, const void *from, size_t bytes, hipMemcpyKind kind, hipStream_t s) {
+    FAKE_ON("hipMemcpyAsync", s, line("copy %zu %ld", bytes, id(s));
+            if (kind == hipMemcpyDeviceToHost) g_late.push_back({id(s), to, from, bytes});
+            else std::memcpy(to, from, bytes));
 }
 hipError_t hipMemsetAsync(void *to, int v, size_t bytes, hipStream_t s) {
     FAKE_ON("hipMemsetAsync", s, line("fill %zu %ld", bytes, id(s)); std::memset(to, v, bytes));
@@ -163,7 +184,7 @@ hipError_t hipStreamDestroy(hipStream_t s) {
     FAKE_ON("hipStreamDestroy", s, line("stream- %ld", id(s)); g_streams.erase(id(s)));
 }
 hipError_t hipStreamQuery(hipStream_t s) { FAKE_ON("hipStreamQuery", s, (void)0); }
-hipError_t hipStreamSynchronize(hipStream_t s) { FAKE_ON("hipStreamSynchronize", s, line("sync %ld", id(s))); }
+hipError_t hipStreamSynchronize(hipStream_t s) { FAKE_ON("hipStreamSynchronize", s, line("sync %ld", id(s)); arrive(id(s))); }
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
     FAKE_ON("hipStreamWaitEvent", s, line("wait %ld %ld", id(s), id(e)));
 }
