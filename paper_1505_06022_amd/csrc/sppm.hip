@@ -767,11 +767,17 @@ constexpr uint32_t kThinPaths = 64;
 // of theirs keeps its slot (and its LDS) for most of a pass, and two passes, an
 // eye pass and a range query are under way at once.  With all slots taken the
 // eye pass, whose waves mostly wait, became the longest stage: 1.9 ms instead of
-// 0.4.  1280x720, 2^20 photons, ms an iteration in calls of 8 (and of 1): all
-// waves for either launch 1.20, half for the first and a quarter for the second
-// 1.09 (3/4 and 1/4 1.10, 3/8 and 1/4 1.10, 1/2 and 1/8 1.19).  With the binary
-// walk, whose passes are bound by waiting and gain from more waves, all and a
-// half: 1.79 (2.67); all and all 1.96 (2.66), half and a quarter 1.91 (3.09).
+// 0.4.  1280x720, 2^20 photons, ms an iteration in calls of 8: all waves for
+// either launch 1.20, half for the first and a quarter for the second 1.09 (3/4
+// and 1/4 1.10, 3/8 and 1/4 1.10, 1/2 and 1/8 1.19).  The shares are the handle's,
+// whatever its calls: with nothing beside it a pass would rather have the device.
+// Calls of 1, 4 and 8 with half and a quarter, and with all and a half: 1.83,
+// 1.16, 1.08 and 1.72, 1.18, 1.09; 400,000 photons 1.19, 0.76, 0.69 and 1.23,
+// 0.80, 0.71; 1920x1080 with 2^22 5.57, 3.70, 3.53 and 4.74, 3.74, 3.49; 320x180
+// with 2^20 1.58, 1.02, 0.89 and 1.38, 0.91, 0.90.
+// With the binary walk, whose passes are bound by waiting and gain from more
+// waves, all and a half: 1.79 in calls of 8 and 2.67 of 1; all and all 1.96 and
+// 2.66, half and a quarter 1.91 and 3.09.
 struct Shares {
     uint32_t head, tail;
 };
